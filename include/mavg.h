@@ -281,7 +281,9 @@ int32_t ngsgd_precondition(void* state, int32_t dim, int32_t rank,
 
 /* ---- the dense contraction all of the above are built from (exported for tests and tuning) -------- */
 /*
- * C(m,n) = epilogue( sum_{kk<k} A(m,kk) B(kk,n) ), float32 operands, float32 MFMA accumulation.
+ * C(m,n) = epilogue( sum_{kk<k} A(m,kk) B(kk,n) ), float32 operands, float32 accumulation.  Either float32 MFMAs, or every
+ * operand element split exactly into three bf16 parts and the six products of parts that float32 can tell apart
+ * accumulated by bf16 MFMAs: errors against float64 are those of float32 products and sums with both.
  *   a_kc != 0: A(m,kk) = a[m*lda + kk], else a[kk*lda + m];   b_kc != 0: B(kk,n) = b[n*ldb + kk], else b[kk*ldb + n]
  *   C(m,n) = c[m*ldc + n]
  *   epi: 0  C = v            1  C = v + bias[n]          2  C = alpha*sigmoid(v + bias[n])
@@ -289,10 +291,12 @@ int32_t ngsgd_precondition(void* state, int32_t dim, int32_t rank,
  *   cfg: -1 = choose the kernel, else:
  *        0  64x64 tiles, operands loaded global -> LDS directly when they allow it (16-byte aligned rows, k a
  *           multiple of 16, widths of m/n-contiguous operands multiples of 4), else through registers
- *        1  64x64 tiles, always through registers (guarded loads: any shape and alignment);  2  128x128 likewise
- *        3 / 4 / 5  direct-to-LDS 128x64 / 64x128 / 128x128 tiles;  6  as 0 with a shallower LDS ring
+ *        1  64x64 tiles, always through registers (guarded loads: any shape and alignment)
+ *        3 / 4 / 5  split-operand kernels (bf16 parts) with 64x64 / 64x128 / 128x128 tiles, any alignment;  2  as 5
+ *        6  as 0 with a shallower LDS ring
  *        7 / 8  direct-to-LDS 32x64 / 32x32 tiles whose contraction is split four ways inside the workgroup
- *        (3, 4, 5, 7, 8 run as 1 when the operands do not allow direct loads)
+ *        9  split-operand kernel with 32x64 tiles
+ *        (7, 8 run as 1 when the operands do not allow direct loads, the split-operand kernels when k < 16)
  *   splits: 0 = choose how many ways the contraction is split across workgroups (partial sums are combined
  *   in split order by a second kernel), else that many; ignored by 7 and 8.
  * All pointers device.  Results are bitwise reproducible for a given (shape, cfg, splits).
@@ -304,8 +308,8 @@ int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const float* b, int
                   int32_t cfg, int32_t splits, void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
- * Several independent contractions C_i = epilogue(A_i B_i) of the same operand layouts in ONE launch (64x64 tiles,
- * unsplit contraction): the form in which dnn_backward_update issues the weight gradients and SGD updates of all
+ * Several independent contractions C_i = epilogue(A_i B_i) of the same operand layouts in ONE launch (unsplit
+ * contraction; problems that need different kernels go into up to three launches): the form in which dnn_backward_update issues the weight gradients and SGD updates of all
  * layers of a step (eq. 3).  Exported for tests and for timing that launch by itself.
  *   problems  host array of `count` records (1 <= count <= 8), read during the call; all pointers inside device
  *   a_kc, b_kc  as in mavg_gemm, shared by all problems

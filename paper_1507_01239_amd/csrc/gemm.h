@@ -77,22 +77,29 @@ enum GemmCfg : int {
     CFG_AUTO = -1,
     CFG_64 = 0,          // 64x64 tiles, 2x2 wavefronts of 32x32: direct-to-LDS (ring of four stages) whenever the operands allow
     CFG_64_REG = 1,      // 64x64 tiles, always register-staged (guarded loads: any shape, any alignment)
-    CFG_128_REG = 2,     // 128x128 tiles, 2x4 wavefronts of 64x32, register-staged
-    CFG_128x64 = 3,      // direct-to-LDS only from here on (replanned as CFG_64_REG when the operands do not allow it):
-    CFG_64x128 = 4,      //   2x2 wavefronts of 64x32 / 32x64 / 64x64
-    CFG_128 = 5,
+    CFG_S128_ALIAS = 2,  // another name of CFG_S128
+    CFG_S64 = 3,         // split-operand kernels (any alignment, K >= 16): 64x64 tiles with two k-groups,
+    CFG_S64x128 = 4,     //   64x128 tiles with four,
+    CFG_S128 = 5,        //   128x128 tiles with two
     CFG_64_RING3 = 6,    // as CFG_64 with a ring of three LDS stages
     CFG_KG_32x64 = 7,    // 32x64 tile, contraction split four ways inside the workgroup
     CFG_KG_32x32 = 8,    // 32x32 tile, likewise, one wavefront per k-group (no barrier in the loop)
-    CFG_COUNT = 9
+    CFG_S32x64 = 9,      // split-operand kernel, 32x64 tiles with eight k-groups of one wavefront
+    CFG_COUNT = 10
 };
 
 struct GemmPlan { int cfg; int splits; int bm, bn; };
 
-GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits);
-// float32 elements of scratch the plan for this problem needs (0 when it is not split)
+// `ragged`: the rows of an operand are not 16-byte aligned (the direct-to-LDS kernels are out then).  ws_floats: the
+// scratch there is for partial sums; plans that need more are not considered.
+GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged = false,
+                   int64_t ws_floats = INT64_MAX);
+// float32 elements of scratch the plan for this problem needs (0 when it is not split), whatever the operands' alignment
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg = -1, int force_splits = 0);
-// enqueue; returns hipError_t as int (0 = ok).  ws must hold gemm_ws_floats() floats when that is > 0.
+// ... when only the fp32-MFMA kernels are considered: the least that gemm_launch accepts (it then plans with that much)
+int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch);
+// enqueue; returns hipError_t as int (0 = ok).  ws must hold gemm_ws_floats_fp32() floats when that is > 0;
+// with less than gemm_ws_floats() the plan makes do with fewer splits.
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream);
 
 // Several independent GEMMs of the same operand layouts and batch count in ONE launch (64x64 tiles, unsplit

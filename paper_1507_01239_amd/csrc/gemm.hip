@@ -1,17 +1,16 @@
-// fp32 GEMM on the CDNA4 matrix cores (v_mfma_f32_32x32x2_f32) with the fused epilogues the training path
-// needs and a deterministic split of the contraction for problems with too few output tiles to fill 256
-// compute units.
+// fp32 GEMM on the CDNA4 matrix cores with the fused epilogues the training path needs and a deterministic split of the
+// contraction for problems with too few output tiles to fill 256 compute units.
 //
-// This file: the plan (tile shape, splits), the dispatch to the kernel families, the split-contraction reducer and
-// the exported entry points.  The kernels live in gemm_device.h and are instantiated per family in
-// gemm_dma64.hip, gemm_dma128.hip, gemm_kg.hip and gemm_legacy.hip (separate files so that they compile in parallel).
-//
-// Two families of kernels share the epilogues, the tile order and the split-contraction reducer:
-//  - gemm_dma_kernel: 64x64 tiles whose operands go from global memory straight into an LDS ring
-//    (global_load_lds_dwordx4); the kernel of the training step whenever the loads need no masking;
-//  - gemm_kernel<BM,BN,BK,...>: register-staged tiles of several shapes, with guarded loads for ragged and
-//    unaligned operands.  One workgroup = WM x WN wavefronts over a BM x BN tile, each wavefront owning a grid
-//    of 32x32 MFMA accumulators; operand tiles staged in LDS k-major ([k][m], [k][n]), double-buffered.
+// This file: the plan (kernel family, tile shape, splits), the dispatch to the kernel families, the split-contraction
+// reducer and the exported entry points.  The kernels live in gemm_device.h and gemm_split.h and are instantiated per
+// family in gemm_split*.hip, gemm_dma64.hip, gemm_kg.hip and gemm_legacy.hip (separate files so that they compile in
+// parallel).  They share the epilogues, the tile order and the split-contraction reducer:
+//  - gemm_split_kernel: every fp32 element in three bf16 parts, six bf16 MFMAs (v_mfma_f32_32x32x16_bf16) per product;
+//    tiles from 32x64 to 128x128, any alignment: everything large, and everything the next two cannot take;
+//  - gemm_dma_kernel / gemm_dma_kg_kernel: v_mfma_f32_32x32x2_f32 on operands that go from global memory straight into
+//    an LDS ring (global_load_lds_dwordx4): problems that do not fill the chip with large tiles, 16-byte aligned rows;
+//  - gemm_kernel: register-staged 64x64 tiles of the same MFMA with guarded loads, for what is left (contractions of fewer
+//    than 16 steps, fused row sums of ragged operands).
 #include "gemm_device.h"
 #include "gemm_launchers.h"
 
@@ -67,33 +66,36 @@ struct TileCfg { int bm, bn, bk, threads; };
 static const TileCfg kCfgs[CFG_COUNT] = {
     {64, 64, 16, 256},     // CFG_64
     {64, 64, 16, 256},     // CFG_64_REG
-    {128, 128, 16, 512},   // CFG_128_REG
-    {128, 64, 16, 256},    // CFG_128x64
-    {64, 128, 16, 256},    // CFG_64x128
-    {128, 128, 16, 256},   // CFG_128
+    {128, 128, 16, 512},   // CFG_S128_ALIAS
+    {64, 64, 16, 256},     // CFG_S64
+    {64, 128, 16, 512},    // CFG_S64x128
+    {128, 128, 16, 512},   // CFG_S128
     {64, 64, 16, 256},     // CFG_64_RING3
     {32, 64, 16, 512},     // CFG_KG_32x64
     {32, 32, 16, 256},     // CFG_KG_32x32
+    {32, 64, 16, 512},     // CFG_S32x64
 };
 constexpr int kNumCfgs = CFG_COUNT;
-static inline bool cfg_dma_only(int cfg) { return cfg >= CFG_128x64 && cfg != CFG_64_RING3; }
 static inline bool cfg_kg(int cfg) { return cfg == CFG_KG_32x64 || cfg == CFG_KG_32x32; }
+static inline bool cfg_split(int cfg) { return (cfg >= CFG_S128_ALIAS && cfg <= CFG_S128) || cfg == CFG_S32x64; }
+static inline int64_t tiles_of(int cfg, int M, int N, int batch) {
+    return (int64_t)((M + kCfgs[cfg].bm - 1) / kCfgs[cfg].bm) * ((N + kCfgs[cfg].bn - 1) / kCfgs[cfg].bn) * batch;
+}
 
-GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits) {
+// The plan with the fp32 MFMA kernels alone (or the configuration that is asked for).
+static GemmPlan gemm_plan_fp32(int M, int N, int K, int batch, int force_cfg, int force_splits) {
     GemmPlan pl;
     // Measured on MI355X (layer shapes at minibatch 256 to 1024, 1 and 8 replicas): the 64x64 direct-to-LDS
     // kernel wins everywhere; many small workgroups per compute unit run out of phase and hide each other's
     // load, barrier and epilogue latencies.
     int cfg = force_cfg;
-    // Only GEMMs that are large in all three dimensions (none of the training shapes: there one of the three is
-    // the minibatch) gain from 128x128 tiles: 141 against 127 TFLOP/s at 4096^3.
     // A short contraction over many tiles (the weight gradients: K is the minibatch) runs better with a ring of
     // three stages: a quarter less LDS lets one more workgroup share the compute unit, and it is the overlap of
     // one workgroup's read-modify-write epilogue with its neighbours' multiplies that is short there
     // (8000x2048x256: 90 against 95 us); the long contractions want the deeper ring (256x8000x2048: 73 against 81).
     if (cfg < 0 || cfg >= kNumCfgs) {
         const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
-        cfg = (M >= 2048 && N >= 2048 && K >= 2048) ? CFG_128 : (K <= 1024 && t64 >= 1024) ? CFG_64_RING3 : CFG_64;
+        cfg = (K <= 1024 && t64 >= 1024) ? CFG_64_RING3 : CFG_64;
         // A skinny problem whose 32x64 tiles come to about one per compute unit (the 256 x 2048 x 2048 hidden
         // layers of the minibatch-256 step) does its contraction split inside the workgroup: 24.5 against
         // 26.9 us including the reducer (13.1 against 15.9 us for the 440-wide first layer).  Not at half or
@@ -156,14 +158,71 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
     return pl;
 }
 
-int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg, int force_splits) {
-    const GemmPlan pl = gemm_plan(M, N, K, batch, force_cfg, force_splits);
-    int splits = pl.splits;
-    if (cfg_dma_only(pl.cfg)) {      // direct-to-LDS only: also cover what runs if the operands rule it out
-        const GemmPlan fb = gemm_plan(M, N, K, batch, CFG_64_REG, force_splits);
-        if (fb.splits > splits) splits = fb.splits;
+// Estimated microseconds of a launch (and its reducer), from measurements at 32 to 4096 rows, 440 to 8000 contraction
+// steps and 1 to 2000 tiles (operands of ordinary values: with every compute unit busy the split-operand kernels run
+// into the power limit, which the share `full` of busy compute units stands for; on zeros they take a quarter less).
+static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool ragged) {
+    const int64_t w = tiles_of(pl.cfg, M, N, batch) * pl.splits;
+    const double rounds = (double)((w + kNumCU - 1) / kNumCU), full = w < kNumCU ? (double)w / kNumCU : 1.0;
+    const double ks = (double)((K + pl.splits - 1) / pl.splits);
+    double c;
+    switch (pl.cfg) {
+    case CFG_S128: c = 3 + rounds * (9 + ks * (0.0318 + 0.0100 * full)); break;
+    case CFG_S64x128: c = 3 + rounds * (5 + ks * (0.0185 + 0.0066 * full)); break;
+    case CFG_S64: c = 5 + rounds * (2 + ks * 0.0151); break;      // (up to three workgroups per compute unit)
+    case CFG_S32x64: c = 3 + rounds * (4 + ks * (0.0062 + 0.0022 * full)); break;
+    case CFG_KG_32x64: c = 5 + rounds * ks * 0.0075; break;
+    case CFG_KG_32x32: c = 5 + rounds * ks * 0.0049; break;
+    default: c = 5 + rounds * ks * 0.0158 * (rounds == 1 ? 1.2 : 1.0) * (ragged ? 2.2 : 1.0); break;
     }
-    return splits > 1 ? (int64_t)splits * batch * M * N : 0;
+    if (pl.splits > 1) c += 4 + 8.0 * pl.splits * M * N * batch / 6e6;
+    return c;
+}
+
+// Which kernel family: the cheapest by plan_cost among the fp32 MFMA plan and the split-operand kernels, unsplit or with 2,
+// 4 or 8 contraction splits of at least 256 steps.  Measured (us; fp32 MFMA kernels against the split-operand kernel taken):
+//   4096 x 8000 x 2048: 976 / 753 (128x128)       1999 x 2048 x 2048: 138 / 99 (128x128)     1024 x 8000 x 2048: 261 / 191 (128x128)
+//   256 x 8000 x 2048: 67 / 60 (64x128)           1024 x 2048 x 8000: 244 / 206 (64x128)     512 x 2048 x 8000: 135 / 100 (128x128, 4 splits)
+//   768 x 2048 x 2048: 57 / 51 (64x128)           384 x 8000 x 2048: 96 / 82 (128x128)
+//   256 x 2048 x 2048: 21.7 / 24.9 (not taken)    128 x 2048 x 8000: 38 / 43 (not taken)     2048 x 2048 x 256: 22.5 / 24.5 (not taken)
+// and with rows that are not 16-byte aligned:
+//   200 x 1021 x 1021: 27 / 16 (32x64)            1000 x 3003 x 1021: 126 / 50 (128x128)     200 x 3003 x 1021: 55 / 26 (64x64)
+// Small products stay with the fp32 MFMAs: every operand element has to be split once per tile it is used in, and LDS takes
+// the three parts at 64 bytes per cycle, which small tiles cannot hide.
+// Summation error: a split-operand plan has at least 0.75 times as many partial sums as the plan it replaces.
+GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged, int64_t ws_floats) {
+    if (force_cfg == CFG_S128_ALIAS) force_cfg = CFG_S128;
+    GemmPlan best = gemm_plan_fp32(M, N, K, batch, force_cfg, force_splits);
+    if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < 16) return best;
+    if (ragged && best.cfg != CFG_64) best = gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits);
+    double least = plan_cost(best, M, N, K, batch, ragged) * 0.97;
+    const int sums = best.splits * (cfg_kg(best.cfg) ? 4 : 1);
+    static const struct { int cfg, kgroups; } kSplitCfgs[] = {{CFG_S128, 2}, {CFG_S64x128, 4}, {CFG_S64, 2}, {CFG_S32x64, 8}};
+    for (const auto& sc : kSplitCfgs)
+        for (int sp = 1; sp <= 8; sp *= 2) {
+            if (force_splits > 0 && sp != force_splits) continue;
+            if (sp > 1 && (K < 256 * sp || (int64_t)sp * batch * M * N > ws_floats)) continue;
+            if (4 * sp * sc.kgroups < 3 * sums) continue;
+            const GemmPlan pl = gemm_plan_fp32(M, N, K, batch, sc.cfg, sp);
+            const double c = plan_cost(pl, M, N, K, batch, ragged);
+            if (c < least) { least = c; best = pl; }
+        }
+    return best;
+}
+
+static int64_t plan_floats(const GemmPlan& pl, int M, int N, int batch) { return pl.splits > 1 ? (int64_t)pl.splits * batch * M * N : 0; }
+
+int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch) {
+    return plan_floats(gemm_plan_fp32(M, N, K, batch, CFG_AUTO, 0), M, N, batch);
+}
+
+int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg, int force_splits) {
+    int64_t f = plan_floats(gemm_plan(M, N, K, batch, force_cfg, force_splits), M, N, batch);
+    auto cover = [&](const GemmPlan& pl) { const int64_t g = plan_floats(pl, M, N, batch); if (g > f) f = g; };
+    // what runs when the operands' alignment rules a plan out
+    cover(gemm_plan(M, N, K, batch, force_cfg, force_splits, true));
+    cover(gemm_plan_fp32(M, N, K, batch, force_cfg < 0 || force_cfg >= kNumCfgs ? CFG_AUTO : CFG_64_REG, force_splits));
+    return f;
 }
 
 static bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
@@ -180,9 +239,11 @@ static bool dma_eligible(const GemmDesc& d, const GemmKParams& p) {
     return true;
 }
 
-static void launch_dma(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) {
-    if (cfg == CFG_128x64 || cfg == CFG_64x128 || cfg == CFG_128) launch_dma128(cfg, p, a_kc, b_kc, grid, s);
-    else launch_dma64(cfg, p, a_kc, b_kc, grid, s);
+// May the split-operand kernels run this problem?  Their per-lane offsets inside a tile are 32-bit byte offsets, and their
+// loads of whole k-tiles need 16 contraction steps.
+static bool split_eligible(const GemmDesc& d) {
+    const int64_t lim = (int64_t)1 << 22;
+    return d.K >= 16 && d.lda < lim && d.ldb < lim;
 }
 
 static GemmKParams fill_params(const GemmDesc& d, const GemmPlan& pl, float* ws) {
@@ -210,31 +271,29 @@ static GemmKParams fill_params(const GemmDesc& d, const GemmPlan& pl, float* ws)
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {
     if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return 0;
     if (d.epi.rowsum_dst != nullptr && d.a_kc) return note_hip_error(hipErrorInvalidValue);
-    // fused row sums and the side sum are the work of the kernel that owns a whole tile: unsplit, not the in-workgroup split
+    // fused row sums and the side sum are the work of the kernels that own a whole tile: unsplit, no k-groups
     const bool rowsum = d.epi.rowsum_dst != nullptr || d.epi.side_sum_src != nullptr;
-    GemmPlan pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, rowsum ? 1 : d.force_splits);
+    GemmPlan pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, rowsum && cfg_split(d.force_cfg) ? CFG_64 : d.force_cfg, rowsum ? 1 : d.force_splits);
     GemmKParams p = fill_params(d, pl, ws);
-    const bool kg_cfg = cfg_kg(pl.cfg);
-    if (cfg_dma_only(pl.cfg) &&
-        !(dma_eligible(d, p) && (!kg_cfg || (!rowsum && d.K / (pl.cfg == CFG_KG_32x64 ? kKgWideBK : kDmaBK) >= kKGroups)))) {
-        pl = gemm_plan(d.M, d.N, d.K, d.batch, CFG_64_REG, rowsum ? 1 : d.force_splits);
+    if (!rowsum && split_eligible(d)) {
+        pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, !dma_eligible(d, p), ws ? ws_floats : 0);
         p = fill_params(d, pl, ws);
     }
-    if (d.force_cfg < 0 && pl.splits == 1 && !dma_eligible(d, p)) {
-        // a large problem the direct-to-LDS kernel cannot take (ragged contraction, unaligned rows): among the
-        // register-staged kernels the 128x128 tile with 8 wavefronts is the fastest from about 3000 64x64 tiles on
-        const int64_t t64 = (int64_t)p.tiles_m * p.tiles_n * d.batch;
-        if (t64 >= 3072 && d.M >= 512 && d.N >= 512) {
-            pl = gemm_plan(d.M, d.N, d.K, d.batch, CFG_128_REG, 1);
-            p = fill_params(d, pl, ws);
-        }
+    if ((cfg_split(pl.cfg) && !split_eligible(d)) ||
+        (cfg_kg(pl.cfg) && !(dma_eligible(d, p) && !rowsum && d.K / (pl.cfg == CFG_KG_32x64 ? kKgWideBK : kDmaBK) >= kKGroups))) {
+        pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, CFG_64_REG, rowsum ? 1 : d.force_splits);
+        p = fill_params(d, pl, ws);
     }
     if (pl.splits > 1 && (ws == nullptr || ws_floats < (int64_t)pl.splits * d.batch * d.M * d.N)) return note_hip_error(hipErrorInvalidValue);
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)(d.batch * pl.splits));
-    if (cfg_kg(pl.cfg)) {      // (the plan may have been replaced above)
-        launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
-    } else if ((pl.cfg == CFG_64 || pl.cfg >= CFG_128x64) && dma_eligible(d, p)) launch_dma(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
-    else launch_legacy(pl.cfg == CFG_128_REG, p, d.a_kc, d.b_kc, grid, stream);
+    if (cfg_split(pl.cfg)) {      // (the plan may have been replaced above)
+        if (pl.cfg == CFG_S64x128) launch_split64x128(p, d.a_kc, d.b_kc, grid, stream);
+        else if (pl.cfg == CFG_S64) launch_split64(p, d.a_kc, d.b_kc, grid, stream);
+        else if (pl.cfg == CFG_S32x64) launch_split32x64(p, d.a_kc, d.b_kc, grid, stream);
+        else launch_split128(p, d.a_kc, d.b_kc, grid, stream);
+    } else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
+    else if (pl.cfg != CFG_64_REG && dma_eligible(d, p)) launch_dma64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
+    else launch_legacy(p, d.a_kc, d.b_kc, grid, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return note_hip_error(e);
     if (pl.splits > 1) {
@@ -269,7 +328,7 @@ static int gemm_launch_grouped_thin(const GemmDesc* d, int count, hipStream_t st
         if (di.M <= 0 || di.N <= 0 || di.batch <= 0) continue;
         if (!di.a_kc || !di.b_kc || di.batch != d[0].batch || di.epi.kind != EPI_STORE || di.epi.rowsum_dst != nullptr)
             return note_hip_error(hipErrorInvalidValue);
-        const GemmPlan pl = gemm_plan(di.M, di.N, di.K, di.batch, CFG_KG_32x32, 1);
+        const GemmPlan pl = gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_KG_32x32, 1);
         const GemmKParams q = fill_params(di, pl, nullptr);
         if (!dma_eligible(di, q) || di.K / kDmaBK < kThinKGroups) {
             GemmDesc one = di;
@@ -292,10 +351,22 @@ static int gemm_launch_grouped_thin(const GemmDesc* d, int count, hipStream_t st
 
 int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool thin) {
     if (thin) return gemm_launch_grouped_thin(d, count, stream);
-    // Two passes over the problems: those the direct-to-LDS kernel accepts, then the rest (ragged or unaligned
-    // ones, e.g. a layer whose width is not a multiple of 4) with the register-staged kernel.
-    for (int pass = 0; pass < 2; ++pass) {
-        const bool dma = pass == 0;
+    // Three passes over the problems: those for the split-operand kernel (128x128 tiles; m- and n-contiguous operands), those
+    // the direct-to-LDS kernel accepts, and the rest (register-staged kernel).
+    // The split-operand kernel takes the launch when its tiles come to at least half the compute units and the contraction is
+    // long enough for its faster multiplies to matter next to the read-modify-write of C: the seven weight updates of
+    // 440-6x2048-8000 take 116 us either way at minibatch 128 (memory), 134 against 145 us at 192, 152 against 177 at 256,
+    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from 16 steps on (the alternative
+    // there is the register-staged kernel, 28 against 21 us at 3003 x 1021 x 200).
+    int64_t tiles128 = 0;
+    for (int i = 0; i < count; ++i) tiles128 += tiles_of(CFG_S128, d[i].M > 0 ? d[i].M : 0, d[i].N > 0 ? d[i].N : 0, d[i].batch);
+    auto family = [&](const GemmDesc& di, const GemmKParams& q) {
+        const bool dma = dma_eligible(di, q);
+        const bool split = split_eligible(di) && !di.a_kc && !di.b_kc && di.epi.side_sum_src == nullptr &&
+                           tiles128 >= kNumCU / 2 && di.K >= (dma ? 192 : 16);
+        return split ? 0 : dma ? 1 : 2;
+    };
+    for (int pass = 0; pass < 3; ++pass) {
         GemmGroupParams gp;
         gp.ngroups = 0;
         int tiles = 0, batch = 0;
@@ -304,7 +375,8 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (gp.ngroups == 0) return 0;
             gp.tile_start[gp.ngroups] = tiles;
             const dim3 grid((unsigned)tiles, 1, (unsigned)batch);
-            if (dma) launch_grouped_dma(gp, a_kc, b_kc, grid, stream);
+            if (pass == 0) launch_grouped_split(gp, grid, stream);
+            else if (pass == 1) launch_grouped_dma(gp, a_kc, b_kc, grid, stream);
             else launch_grouped_legacy(gp, a_kc, b_kc, grid, stream);
             gp.ngroups = 0;
             tiles = 0;
@@ -316,9 +388,10 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (di.M <= 0 || di.N <= 0 || di.batch <= 0) continue;
             if (di.a_kc != d[0].a_kc || di.b_kc != d[0].b_kc || di.batch != d[0].batch) return note_hip_error(hipErrorInvalidValue);
             if (di.epi.rowsum_dst != nullptr && di.a_kc) return note_hip_error(hipErrorInvalidValue);
-            const GemmPlan pl = gemm_plan(di.M, di.N, di.K, di.batch, CFG_64, 1);      // 64x64 tiles, unsplit
-            const GemmKParams q = fill_params(di, pl, nullptr);
-            if (dma_eligible(di, q) != dma) continue;
+            // unsplit, 64x64 tiles (128x128 for the split-operand kernel)
+            GemmKParams q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_64, 1), nullptr);
+            if (family(di, q) != pass) continue;
+            if (pass == 0) q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_S128, 1), nullptr);
             a_kc = di.a_kc; b_kc = di.b_kc; batch = di.batch;
             gp.g[gp.ngroups] = q;
             gp.tile_start[gp.ngroups] = tiles;

@@ -113,89 +113,99 @@ __device__ __forceinline__ const float* at_off(const float* ubase, uint32_t off)
 // row 8*(v/4) + 4*(lane/32) + v%4, column lane%32 of its 32x32 block.  `mbase` is uniform over the wavefront.
 // Every access is (uniform row pointer) + (per-lane byte offset): row 8*(v/4) + v%4 of the block goes into the
 // scalar pointer, the lane's 4*(lane/32) rows and its column into one offset register per matrix.
-// `band` (uniform over the wavefront): -1 = all 16 elements; 0..3 = only elements 4 band .. 4 band + 3, i.e. rows
-// 8 band .. 8 band + 7 of each 32x32 block (a workgroup whose wavefronts share the epilogue of one accumulator).
+// `bands` (uniform over the wavefront): bit g = elements 4 g .. 4 g + 3, i.e. rows 8 g .. 8 g + 7 of each 32x32 block,
+// are this wavefront's to write (a workgroup whose wavefronts share the epilogue of one accumulator); -1 = all of them.
+// Read-modify-write epilogues request the old values of all blocks back to back before the first store: loads and stores
+// count in one in-order counter, so a load behind a store would wait for that store to reach memory.
 template <int KIND, int TM, int TN>
 __device__ __forceinline__ void write_tile(const floatx16 (&acc)[TM][TN], const Epilogue& e, const EpiCtx& c,
-                                           int64_t ldc, int M, int N, int mbase, int nbase, int lrow, int lcol, int band = -1) {
+                                           int64_t ldc, int M, int N, int mbase, int nbase, int lrow, int lcol, int bands = -1) {
     constexpr bool kReadsC = KIND == EPI_AXPBY;
     constexpr bool kReadsAux = KIND == EPI_MUL_DSIGMOID || KIND == EPI_ROWSCALE_ADD;
+    constexpr bool kReads = kReadsC || kReadsAux;
     constexpr bool kBias = KIND == EPI_BIAS || KIND == EPI_BIAS_SIGMOID || KIND == EPI_BIAS_SIGMOID_SAMPLE;
     const int mb = __builtin_amdgcn_readfirstlane(mbase);
-    static_for<TM * TN>([&](auto bc) {
-        constexpr int t = decltype(bc)::value;
-        constexpr int i = t / TN, j = t % TN;
-        // Does this 32-column block hold the column that goes to a separate vector (uniform over the wavefront)?
-        // Only then do the accesses need a per-lane choice of destination.
-        bool has_lastcol = false;
-        if constexpr (KIND == EPI_AXPBY)
-            has_lastcol = c.lastcol_dst != nullptr && e.lastcol >= nbase + j * 32 && e.lastcol < nbase + j * 32 + 32;
-        // A block that lies wholly inside the matrix needs no per-element bounds checks (uniform over the wavefront).
-        const bool interior = mb + i * 32 + 32 <= M && nbase + j * 32 + 32 <= N;
-        auto block = [&](auto lcc, auto inc) {
-            constexpr bool LC = decltype(lcc)::value, IN = decltype(inc)::value;
-            const int n = nbase + j * 32 + lcol;
-            const bool n_ok = IN || n < N;
-            const uint32_t offC = (uint32_t)(((int64_t)(4 * lrow) * ldc + n) * 4);
-            const uint32_t offAux = kReadsAux ? (uint32_t)(((int64_t)(4 * lrow) * e.ldaux + n) * 4) : 0u;
-            const uint32_t offC2 = (KIND == EPI_AXPBY || KIND == EPI_BIAS_SIGMOID_SAMPLE) ? (uint32_t)(((int64_t)(4 * lrow) * e.ldc2 + n) * 4) : 0u;
-            const bool lastcol = LC && n == e.lastcol;
-            float bias_n = 0.f;
-            if (kBias && n_ok) bias_n = c.bias[n];
-            float old[16];
-            if constexpr (kReadsC || kReadsAux) {
-                // read-modify-write epilogues: issue the 16 loads of a 32x32 block back to back, then combine and
-                // store, so that their latencies overlap instead of adding up
-                const bool need_old = kReadsAux || e.beta != 0.f;
-                static_for<16>([&](auto vc) {
-                    constexpr int v = decltype(vc)::value;
-                    const int mu = mb + i * 32 + 8 * (v >> 2) + (v & 3);
-                    const int m = mu + 4 * lrow;
-                    old[v] = 0.f;
-                    if (need_old && (band < 0 || band == (v >> 2)) && (IN || m < M) && n_ok) {
-                        if constexpr (kReadsC) old[v] = lastcol ? c.lastcol_dst[m] : *at_off(c.C + (int64_t)mu * ldc, offC);
-                        else old[v] = *at_off(c.aux + (int64_t)mu * e.ldaux, offAux);
-                    }
-                });
+    // Calls body(block, lastcol?, interior?) with what is uniform over the block: does it hold the column that goes to a
+    // separate vector (only then do the accesses need a per-lane choice of destination), and does it lie wholly inside
+    // the matrix (no per-element bounds checks then).
+    auto for_blocks = [&](auto&& body) {
+        static_for<TM * TN>([&](auto bc) {
+            constexpr int t = decltype(bc)::value;
+            constexpr int i = t / TN, j = t % TN;
+            bool has_lastcol = false;
+            if constexpr (KIND == EPI_AXPBY)
+                has_lastcol = c.lastcol_dst != nullptr && e.lastcol >= nbase + j * 32 && e.lastcol < nbase + j * 32 + 32;
+            const bool interior = mb + i * 32 + 32 <= M && nbase + j * 32 + 32 <= N;
+            if (has_lastcol) {
+                if constexpr (KIND == EPI_AXPBY) body(bc, std::true_type{}, std::false_type{});
+            } else if (interior) {
+                body(bc, std::false_type{}, std::true_type{});
+            } else {
+                body(bc, std::false_type{}, std::false_type{});
             }
+        });
+    };
+    float old[kReads ? TM * TN : 1][16];
+    if constexpr (kReads) {
+        const bool need_old = kReadsAux || e.beta != 0.f;
+        for_blocks([&](auto bc, auto lcc, auto inc) {
+            constexpr bool LC = decltype(lcc)::value, IN = decltype(inc)::value;
+            constexpr int t = decltype(bc)::value, i = t / TN, j = t % TN;
+            const int n = nbase + j * 32 + lcol;
+            const bool n_ok = IN || n < N, lastcol = LC && n == e.lastcol;
+            const int64_t ld = kReadsC ? ldc : e.ldaux;
+            const float* src = kReadsC ? c.C : c.aux;
+            const uint32_t off = (uint32_t)(((int64_t)(4 * lrow) * ld + n) * 4);
             static_for<16>([&](auto vc) {
                 constexpr int v = decltype(vc)::value;
                 const int mu = mb + i * 32 + 8 * (v >> 2) + (v & 3);
                 const int m = mu + 4 * lrow;
-                if ((band < 0 || band == (v >> 2)) && (IN || m < M) && n_ok) {
-                    const float a = acc[i][j][v];
-                    float* dst = at_off(c.C + (int64_t)mu * ldc, offC);
-                    if constexpr (KIND == EPI_STORE) {
-                        *dst = a;
-                    } else if constexpr (KIND == EPI_BIAS) {
-                        *dst = a + bias_n;
-                    } else if constexpr (KIND == EPI_BIAS_SIGMOID) {
-                        *dst = c.alpha * (e.act_tanh ? tanhf(a + bias_n) : sigmoidf_dev(a + bias_n));
-                    } else if constexpr (KIND == EPI_MUL_DSIGMOID) {
-                        *dst = e.act_tanh ? a * (1.f - old[v] * old[v]) : a * old[v] * (1.f - old[v]);
-                    } else if constexpr (KIND == EPI_AXPBY) {
-                        const float r = c.alpha * a + e.beta * old[v];
-                        if (lastcol) c.lastcol_dst[m] = r;
-                        else *dst = r;
-                        if (c.C2) *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) += r;
-                    } else if constexpr (KIND == EPI_BIAS_SIGMOID_SAMPLE) {
-                        const float pr = sigmoidf_dev(a + bias_n);
-                        if (c.C) *dst = pr;
-                        const float u = philox_uniform((uint64_t)m * (uint64_t)N + (uint64_t)n, e.key0, e.key1, e.step, e.layer, e.phase);
-                        *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) = (u < pr) ? 1.f : 0.f;
-                    } else {      // EPI_ROWSCALE_ADD
-                        *dst = c.alpha * a + c.rowvec[m] * old[v];
-                    }
-                }
+                old[t][v] = 0.f;
+                if (need_old && ((bands >> (v >> 2)) & 1) && (IN || m < M) && n_ok)
+                    old[t][v] = lastcol ? c.lastcol_dst[m] : *at_off(src + (int64_t)mu * ld, off);
             });
-        };
-        if (has_lastcol) {
-            if constexpr (KIND == EPI_AXPBY) block(std::true_type{}, std::false_type{});
-        } else if (interior) {
-            block(std::false_type{}, std::true_type{});
-        } else {
-            block(std::false_type{}, std::false_type{});
-        }
+        });
+    }
+    for_blocks([&](auto bc, auto lcc, auto inc) {
+        constexpr bool LC = decltype(lcc)::value, IN = decltype(inc)::value;
+        constexpr int t = decltype(bc)::value, i = t / TN, j = t % TN;
+        const int n = nbase + j * 32 + lcol;
+        const bool n_ok = IN || n < N;
+        const uint32_t offC = (uint32_t)(((int64_t)(4 * lrow) * ldc + n) * 4);
+        const uint32_t offC2 = (KIND == EPI_AXPBY || KIND == EPI_BIAS_SIGMOID_SAMPLE) ? (uint32_t)(((int64_t)(4 * lrow) * e.ldc2 + n) * 4) : 0u;
+        const bool lastcol = LC && n == e.lastcol;
+        float bias_n = 0.f;
+        if (kBias && n_ok) bias_n = c.bias[n];
+        static_for<16>([&](auto vc) {
+            constexpr int v = decltype(vc)::value;
+            const int mu = mb + i * 32 + 8 * (v >> 2) + (v & 3);
+            const int m = mu + 4 * lrow;
+            if (((bands >> (v >> 2)) & 1) && (IN || m < M) && n_ok) {
+                const float a = acc[i][j][v];
+                float* dst = at_off(c.C + (int64_t)mu * ldc, offC);
+                if constexpr (KIND == EPI_STORE) {
+                    *dst = a;
+                } else if constexpr (KIND == EPI_BIAS) {
+                    *dst = a + bias_n;
+                } else if constexpr (KIND == EPI_BIAS_SIGMOID) {
+                    *dst = c.alpha * (e.act_tanh ? tanhf(a + bias_n) : sigmoidf_dev(a + bias_n));
+                } else if constexpr (KIND == EPI_MUL_DSIGMOID) {
+                    *dst = e.act_tanh ? a * (1.f - old[t][v] * old[t][v]) : a * old[t][v] * (1.f - old[t][v]);
+                } else if constexpr (KIND == EPI_AXPBY) {
+                    const float r = c.alpha * a + e.beta * old[t][v];
+                    if (lastcol) c.lastcol_dst[m] = r;
+                    else *dst = r;
+                    if (c.C2) *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) += r;
+                } else if constexpr (KIND == EPI_BIAS_SIGMOID_SAMPLE) {
+                    const float pr = sigmoidf_dev(a + bias_n);
+                    if (c.C) *dst = pr;
+                    const float u = philox_uniform((uint64_t)m * (uint64_t)N + (uint64_t)n, e.key0, e.key1, e.step, e.layer, e.phase);
+                    *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) = (u < pr) ? 1.f : 0.f;
+                } else {      // EPI_ROWSCALE_ADD
+                    *dst = c.alpha * a + c.rowvec[m] * old[t][v];
+                }
+            }
+        });
     });
 }
 
@@ -1015,7 +1025,7 @@ __device__ __forceinline__ void gemm_dma_kg_body(const GemmKParams& p, const int
         }
     });
     const EpiCtx c = epi_ctx(p.epi, p.C, p.c_bstride, b);
-    MAVG_EPI_DISPATCH(p.epi.kind, (write_tile<KIND, 1, 1>(acc, p.epi, c, p.ldc, p.M, p.N, m0, n0 + wn, lrow, lcol, kg)))
+    MAVG_EPI_DISPATCH(p.epi.kind, (write_tile<KIND, 1, 1>(acc, p.epi, c, p.ldc, p.M, p.N, m0, n0 + wn, lrow, lcol, 1 << kg)))
 }
 
 // The 32x64 variant (one workgroup per compute unit) takes k-tiles of 32 steps in a ring of three stages (144 KB of

@@ -12,9 +12,8 @@ static void launch_cfg(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hi
     else hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, WM, WN, PF, false, true>), grid, block, 0, s, p);
 }
 
-void launch_legacy(bool big, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) {
-    if (big) launch_cfg<128, 128, 16, 2, 4, 4>(p, a_kc, b_kc, grid, s);
-    else launch_cfg<64, 64, 16, 2, 2, 4>(p, a_kc, b_kc, grid, s);
+void launch_legacy(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) {
+    launch_cfg<64, 64, 16, 2, 2, 4>(p, a_kc, b_kc, grid, s);
 }
 
 void launch_grouped_legacy(const GemmGroupParams& gp, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) {

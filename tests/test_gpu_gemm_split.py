@@ -1,0 +1,106 @@
+"""The split-operand GEMM kernels (three bf16 parts per float32 element) against float64 products of the same float32
+inputs, at the sizes where they can go wrong, and with values that do not survive the split."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_gemm import _run
+from tests.util import dev, host, rel_err, workspace
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = [(1, 1), (1, 0), (0, 0), (0, 1)]
+SPLIT_CFGS = [3, 4, 5, 9]      # 64x64, 64x128, 128x128, 32x64 tiles
+
+
+@pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
+@pytest.mark.parametrize("cfg", SPLIT_CFGS)
+def test_tile_edges_and_contraction_remainders(a_kc, b_kc, cfg):
+    # m and n one below, at and above the tiles' edges; contractions of one to many 16-step tiles, with and without a
+    # partial one, fewer tiles than k-groups, shares that end in a partial tile; rows aligned to 4 bytes only.
+    # Tolerance: a product of k terms of random sign is off by about 2^-24 sqrt(k / 2) where every addition rounds;
+    # k = 1040 gives 1.4e-6, and the k-groups add in parts.
+    for i, (m, n, k, pad) in enumerate([(1, 1, 16, 0), (127, 129, 17, 0), (128, 128, 31, 1), (129, 127, 32, 3), (33, 65, 33, 0),
+                                        (31, 63, 48, 2), (64, 64, 63, 0), (200, 130, 79, 1), (65, 200, 128, 0), (130, 70, 1040, 1)]):
+        assert _run(m, n, k, a_kc, b_kc, cfg=cfg, seed=100 + i, pad=pad) < 2e-6, (m, n, k, pad)
+    assert _run(70, 133, 700, a_kc, b_kc, cfg=cfg, splits=3, seed=120, epi=2, alpha=-0.5) < 2e-6
+    assert _run(70, 133, 15, a_kc, b_kc, cfg=cfg, seed=121) < 2e-6      # below one k-tile: another kernel runs
+
+
+@pytest.mark.parametrize("epi", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("cfg", SPLIT_CFGS)
+def test_epilogues(epi, cfg):
+    assert _run(150, 200, 90, 1, 1, epi=epi, cfg=cfg, seed=130, alpha=-0.5, beta=1.0) < 2e-6
+    assert _run(150, 201, 90, 0, 0, epi=epi, cfg=cfg, seed=131, alpha=0.25, beta=0.5, pad=1) < 2e-6
+
+
+@pytest.mark.parametrize("cfg", SPLIT_CFGS)
+def test_values_that_do_not_survive_the_split(cfg):
+    # infinities, NaNs and floats that round to infinity in bf16 give what float32 arithmetic gives; rows and columns
+    # without them are untouched
+    import torch
+    from paper_1507_01239_amd import binding as B
+    rng = np.random.default_rng(7)
+    m, n, k = 100, 140, 120
+    A, Bt = rng.standard_normal((m, k)).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    A[3, 5], A[40, 119], A[70, 0], A[71, 1] = np.inf, np.nan, 3.4e38, -np.inf
+    Bt[:, 0] = 1e-3 * np.abs(Bt[:, 0])       # 3.4e38 * 1e-3 stays finite
+    Bt[9, 5] = 0.0                           # inf * 0
+    Bt[77, 5] = -np.inf
+    c = torch.zeros(m, n, device="cuda")
+    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, cfg, 1))
+    B.mavg_gemm(dev(A), k, 1, dev(Bt), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, cfg, 1, ws)
+    torch.cuda.synchronize()
+    got = host(c).astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref = (A.astype(np.float64)[:, None, :] * Bt.astype(np.float64)[None]).sum(axis=2)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(got[inf], ref[inf])
+    fine = np.isfinite(ref)
+    assert np.isfinite(got[fine]).all()
+    big = fine & (np.arange(m)[:, None] == 70)
+    assert rel_err(got[big], ref[big]) < 2e-6
+    assert rel_err(got[fine & ~big], ref[fine & ~big]) < 2e-6
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-36])
+def test_small_magnitudes(scale):
+    # parts below 2^-126 are kept as denormals down to 2^-133: at 1e-36 that is 13 bits below the smallest element here
+    rng = np.random.default_rng(8)
+    m, n, k = 70, 90, 64
+    A, Bt = (rng.uniform(1, 2, (m, k)) * scale).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    import torch
+    from paper_1507_01239_amd import binding as B
+    c = torch.zeros(m, n, device="cuda")
+    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, 3, 1))
+    B.mavg_gemm(dev(A), k, 1, dev(Bt), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, 3, 1, ws)
+    torch.cuda.synchronize()
+    assert rel_err(host(c), A.astype(np.float64) @ Bt.astype(np.float64).T) < (2e-6 if scale == 1e-30 else 2.0 ** -13)
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("n", [16, 200, 263])
+def test_grouped_weight_updates(n, aligned):
+    # enough 128x128 tiles for the split-operand kernel of the grouped launch (rows of the second operand aligned to 16
+    # bytes or not; below 192 contraction steps the aligned ones run on another kernel): ragged tile edges, row sums, and
+    # a small problem next to a large one
+    import torch
+    from paper_1507_01239_amd import binding as B
+    rng = np.random.default_rng(50 + n)
+    shapes = [(1027, 1537 if not aligned else 1540), (130, 65 if not aligned else 68), (514, 259 if not aligned else 260)]
+    probs, refs, outs, keep = [], [], [], []
+    for (m, nc) in shapes:
+        ldd = (m + 3) // 4 * 4
+        D = np.zeros((n, ldd), np.float32)
+        D[:, :m] = rng.standard_normal((n, m))
+        A, W, bv = (rng.standard_normal(s).astype(np.float32) for s in ((n, nc), (m, nc), (m,)))
+        d_d, a_d, w_d, b_d = dev(D), dev(A), dev(W), dev(bv)
+        probs.append(B.gemm_problem(d_d, ldd, a_d, nc, w_d, nc, m, nc, n, epi=4, alpha=-0.25, beta=1.0, rowsum_dst=b_d,
+                                    rowsum_alpha=-0.25, rowsum_beta=1.0, a_pad4=True))
+        refs.append((W - 0.25 * D[:, :m].astype(np.float64).T @ A.astype(np.float64), bv - 0.25 * D[:, :m].astype(np.float64).sum(axis=0)))
+        outs.append((w_d, b_d))
+        keep.append((d_d, a_d))
+    B.mavg_gemm_grouped(probs, 0, 0)
+    torch.cuda.synchronize()
+    for (w_d, b_d), (Wr, br) in zip(outs, refs):
+        assert rel_err(host(w_d), Wr) < 2e-6 and rel_err(host(b_d), br) < 2e-6
