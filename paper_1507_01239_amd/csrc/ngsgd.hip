@@ -104,19 +104,10 @@ __device__ __forceinline__ double block_sum_d(double v, double* sh) {
     return r;
 }
 
-// the eigen-solver runs 512 threads: 16 groups of 32 lanes, one group per rotation pair up to rank 32
-constexpr int kEigThreads = 512;
+// the eigen-solver runs 256 threads in groups of 32 lanes, above rank 32 512 threads in groups of 64 lanes
+template <int LW> constexpr int kEigThreads = LW == 32 ? 256 : 512;
 constexpr int kEigSoloLds = 120 * 1024;      // bytes of LDS a solver workgroup asks for to have its compute unit to itself
 constexpr int kEigSoloMax = 64;              // ... in launches of at most this many workgroups
-__device__ __forceinline__ double block_sum_eig(double v, double* sh) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const double r = ((sh[0] + sh[1]) + (sh[2] + sh[3])) + ((sh[4] + sh[5]) + (sh[6] + sh[7]));
-    __syncthreads();
-    return r;
-}
-
 // Table of independent folds finished by one launch of each of ng_z_kernel / ng_eig_kernel / ng_newr_kernel:
 // slot = one preconditioned matrix (a layer's input or output side), times `batch` replicas.
 constexpr int kNgSlots = 32;
@@ -178,20 +169,12 @@ __global__ __launch_bounds__(256) void ng_z_kernel(NgFoldTable tb, int rank, dou
     }
 }
 
-// Reciprocal square root and reciprocal in float64 from the hardware's approximations and two Newton steps each
-// (relative error at rounding level for normal arguments; no special-case handling: the callers pass positive, finite,
-// normal values).
+// Reciprocal square root in float64: the hardware's approximation (relative error below 2^-22) and one step of third order,
+// four dependent operations to rounding level; no special-case handling: the callers pass positive, finite, normal values.
 __device__ __forceinline__ double fast_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * (1.5 - 0.5 * x * y * y);
-    y = y * (1.5 - 0.5 * x * y * y);
-    return y;
-}
-__device__ __forceinline__ double fast_rcp(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = y * (2.0 - x * y);
-    y = y * (2.0 - x * y);
-    return y;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-x * y, y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
 // Symmetric eigen-decomposition of the rank x rank matrix Z by cyclic Jacobi rotations in a round-robin
@@ -199,57 +182,148 @@ __device__ __forceinline__ double fast_rcp(double x) {
 // columns in one pass (the column partner's entries come from a neighbouring lane); then the
 // new d, rho, t and the matrix Wt = diag(c)^-1/2 U^T (rows in descending order of c).
 //
-// Threads form groups of 32 lanes (64 above rank 32), lane l standing for index l of the matrix.  In round `rd` of
-// the tournament among m = rank rounded up to even players, player m-1 meets player rd and every other player l
-// meets (2 rd - l) mod (m - 1); an odd rank leaves the player that would meet the dummy idle.  Every lane works out
+// An odd rank gets one more, zero row and column (never rotated: its entries are zero), which makes m indices.  Threads
+// form groups of LW lanes (32; 64 above rank 32), lane l standing for index l of the matrix.  In round `rd` of the
+// tournament index m-1 meets index rd and every other index l meets (2 rd - l) mod (m - 1).  Every lane works out
 // the rotation of its own index's pair from the three entries it depends on (all groups do so redundantly: no
 // hand-over through LDS, no barrier between computing the rotations and applying them); the group that owns a pair's
 // two rows takes that pair's rotation from its lane p.  Z and U^T are kept twice: a round reads one copy and writes the
-// other (every row belongs to exactly one pair, or is the idle one, and is written once per round), so a wavefront
-// that is ahead never overwrites what a slower one still has to read, and one barrier per round is enough.
-__global__ __launch_bounds__(kEigThreads) void ng_eig_kernel(NgFoldTable tb, int rank, int n, float eta, const double* __restrict__ Zg,
+// other (every row belongs to exactly one pair and is written once per round), so a wavefront that is ahead never
+// overwrites what a slower one still has to read, and one barrier per round is enough.
+//
+// What bounds it: one workgroup per matrix and some 120 to 200 rounds, each a chain of LDS reads, the rotation's float64
+// operations, a lane exchange, the products, LDS writes and the barrier.  So everything a round reads from LDS is
+// requested at once, the partner's column entries among it; the next round's addresses are worked out while those reads
+// are on their way (fixed row stride, both copies at fixed distances: they go into the instructions); the rotation needs
+// two reciprocal square roots and nothing else; up to rank 32 one wavefront per SIMD, because the part that every wavefront
+// repeats is half of what it issues (rank 30: 85 against 104 us for 512 threads; above rank 32 the pairs are many enough for
+// 512, rank 40: 260 against 322).  Four sweeps at rank 30: 86 us, was 117; rank 40: 260, was 296; rank 64: 575, was 815.
+template <int LW> constexpr int kEigLd = LW + 2;       // even: the diagonal (an odd number of doubles apart) spreads over all LDS banks
+template <int LW> constexpr int kEigMat = LW * kEigLd<LW>;
+template <int LW>
+__global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb, int rank, int n, float eta, const double* __restrict__ Zg,
                                                      double* __restrict__ Wt, int bump_t) {
     extern __shared__ double smem[];
-    const int r = rank;
-    const int rs = (r + 1) & ~1;     // even row stride: the diagonal (stride rs + 1 doubles, odd) spreads over all LDS banks
-    double* Zs = smem;               // r x rs, current copy (the two copies swap after every round)
-    double* Us = Zs + r * rs;        // r x rs, holds U TRANSPOSED (row k = eigenvector k), so its update is a row rotation
-    double* Zn = Us + r * rs;        // the copies the current round writes
-    double* Un = Zn + r * rs;
-    double* red = Un + r * rs;       // 16
-    int* order = reinterpret_cast<int*>(red + 16);   // 64
+    constexpr int LD = kEigLd<LW>, MAT = kEigMat<LW>;
+    const int r = rank, m = (r + 1) & ~1, half = m / 2;
+    // Z at 0 and MAT, U^T (row k = eigenvector k, so its update is a row rotation) at 2 MAT and 3 MAT
+    double* red = smem + 4 * MAT;                     // 64: partial sums, then the square roots of the eigenvalues
+    int* order = reinterpret_cast<int*>(red + 64);    // 64
     const int slot = blockIdx.x / tb.batch, b = blockIdx.x - slot * tb.batch, tid = threadIdx.x;
     const int dim = tb.dim[slot];
     const int64_t zi = (int64_t)(tb.first + slot) * tb.batch + b;
     const double* __restrict__ Zb = Zg + zi * kMaxRank * kMaxRank;
-    // thread = (lane: an index along a row, grp: which rotation pair / which row); a group never straddles a wavefront
-    const int lw = r <= 32 ? 32 : 64, ngrp = kEigThreads / lw;
-    const int lane = tid & (lw - 1), grp = tid / lw;
-    for (int i = grp; i < r; i += ngrp)
-        if (lane < r) {
-            Zs[i * rs + lane] = Zb[i * r + lane];
-            Us[i * rs + lane] = (i == lane) ? 1.0 : 0.0;
+    constexpr int NT = kEigThreads<LW>, NG = NT / LW, KPG = LW / 2 / NG;       // groups; pairs of a round per group
+    const int lane = tid & (LW - 1), grp = tid / LW;
+    const bool on = lane < m;
+    if (on)
+        for (int i = grp; i < m; i += NG) {
+            smem[i * LD + lane] = i < r && lane < r ? Zb[i * r + lane] : 0.0;
+            smem[2 * MAT + i * LD + lane] = i == lane ? 1.0 : 0.0;
         }
     __syncthreads();
-    const int m = (r + 1) & ~1;      // even number of players
-    const int half = m / 2;
-    const bool on = lane < r;
-    int sweeps_done = 0;
+    // Element offsets of what this thread reads in a round.  (Lanes past the matrix stand for its last column and groups
+    // past the last pair for the first one; neither writes.)
+    const int lc = min(lane, m - 1);
+    int pp, qq, pq;                                   // (p, p), (q, q), (p, q) of the pair of this lane's index
+    int lp[KPG], pr[KPG], qr[KPG], partner;           // lane p, rows p and q of the group's pairs; the index met
+    auto pairing = [&](int round) {
+        int w = 2 * round - lc;                       // in (-(m-1), 2(m-1)): reduce mod m-1 without a division
+        if (w < 0) w += m - 1;
+        if (w >= m - 1) w -= m - 1;
+        partner = lc == m - 1 ? round : lc == round ? m - 1 : w;
+        const int p = min(lc, partner), q = max(lc, partner);
+        pp = p * (LD + 1);
+        qq = q * (LD + 1);
+        pq = p * LD + q;
+#pragma unroll
+        for (int i = 0; i < KPG; ++i) {
+            const int k = grp + i * NG;
+            int u = round + k, v = round - k;
+            if (u >= m - 1) u -= m - 1;
+            if (v < 0) v += m - 1;
+            const bool first = k == 0 || k >= half;
+            u = first ? m - 1 : u;
+            v = first ? round : v;
+            lp[i] = min(u, v);
+            pr[i] = lp[i] * LD;
+            qr[i] = max(u, v) * LD;
+        }
+    };
+    // One round, from copy CUR to the other one: Z <- J^T Z J, U^T <- J^T U^T with, for every pair (p, q), p < q,
+    // row_p <- c row_p - s row_q,  row_q <- s row_p + c row_q  (and the same for the columns of Z)
+    auto rotate = [&](auto curc, int next_round) {
+        constexpr int CUR = decltype(curc)::value;
+        const double* Z = smem + CUR * MAT;
+        const double* U = smem + (2 + CUR) * MAT;
+        double* Zn = smem + (1 - CUR) * MAT;
+        double* Un = smem + (3 - CUR) * MAT;
+        const double app = Z[pp], aqq = Z[qq], apq = Z[pq];
+        double zp[KPG], zq[KPG], zpo[KPG], zqo[KPG], up[KPG], uq[KPG];
+        int at_p[KPG], at_q[KPG], from[KPG];
+        const bool low = lc < partner;
+#pragma unroll
+        for (int i = 0; i < KPG; ++i) {
+            at_p[i] = pr[i] + lc;
+            at_q[i] = qr[i] + lc;
+            from[i] = lp[i];
+            zp[i] = Z[at_p[i]];            zq[i] = Z[at_q[i]];
+            zpo[i] = Z[pr[i] + partner];   zqo[i] = Z[qr[i] + partner];
+            up[i] = U[at_p[i]];            uq[i] = U[at_q[i]];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        pairing(next_round);
+        // c^2 = (1 + |d| / h) / 2, s = sgn(d) b2 / (2 h c) with d = aqq - app, b2 = 2 apq, h = sqrt(d^2 + b2^2): the
+        // rotation by the smaller angle
+        double cl = 1.0, sl = 0.0;                    // rotation of the pair this lane's index is in
+        const double d = aqq - app, b2 = 2.0 * apq;
+        const double h2 = d * d + b2 * b2;
+        if (apq != 0.0 && h2 > 1e-280) {              // (below that the entry is nothing against any diagonal)
+            const double ih = fast_rsqrt(h2);
+            const double u = 0.5 + 0.5 * fabs(d) * ih;
+            const double iu = fast_rsqrt(u);
+            cl = u * iu;
+            sl = (d >= 0.0 ? 0.5 : -0.5) * b2 * ih * iu;
+        }
+        // column `lane` turns into cl column_lane + bl column_partner
+        const double bl = low ? -sl : sl;
+        double c[KPG], s[KPG];
+#pragma unroll
+        for (int i = 0; i < KPG; ++i) { c[i] = __shfl(cl, from[i], LW); s[i] = __shfl(sl, from[i], LW); }
+#pragma unroll
+        for (int i = 0; i < KPG; ++i) {
+            const double wp = c[i] * zp[i] - s[i] * zq[i], wq = s[i] * zp[i] + c[i] * zq[i];
+            const double wpo = c[i] * zpo[i] - s[i] * zqo[i], wqo = s[i] * zpo[i] + c[i] * zqo[i];
+            if (on && grp + i * NG < half) {
+                Zn[at_p[i]] = cl * wp + bl * wpo;
+                Zn[at_q[i]] = cl * wq + bl * wqo;
+                Un[at_p[i]] = c[i] * up[i] - s[i] * uq[i];
+                Un[at_q[i]] = s[i] * up[i] + c[i] * uq[i];
+            }
+        }
+        __syncthreads();
+    };
+    pairing(0);
+    int sweeps_done = 0, cur = 0;
     bool converged = false;
     for (int sweep = 0; sweep <= kJacobiSweeps; ++sweep) {
         // stop when the off-diagonal mass is negligible against the diagonal
         double off = 0.0, dg = 0.0;
-        for (int i = grp; i < r; i += ngrp)
+        for (int i = grp; i < m; i += NG)
             if (on) {
-                const double v = Zs[i * rs + lane];
+                const double v = smem[cur * MAT + i * LD + lane];
                 if (i == lane) dg += v * v; else off += v * v;
             }
         off = wave_sum(off);
         dg = wave_sum(dg);
         if ((tid & 63) == 0) { red[tid >> 6] = off; red[8 + (tid >> 6)] = dg; }
         __syncthreads();
-        off = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
-        dg = ((red[8] + red[9]) + (red[10] + red[11])) + ((red[12] + red[13]) + (red[14] + red[15]));
+        off = (red[0] + red[1]) + (red[2] + red[3]);
+        dg = (red[8] + red[9]) + (red[10] + red[11]);
+        if constexpr (NT == 512) {
+            off += (red[4] + red[5]) + (red[6] + red[7]);
+            dg += (red[12] + red[13]) + (red[14] + red[15]);
+        }
         __syncthreads();
         // off-diagonal norm below 1e-13 of the diagonal: Z spans many orders of magnitude, and a looser stop (1e-10)
         // leaves its small eigenvalues, hence the weak rows of R, outside the parity tolerance
@@ -257,107 +331,53 @@ __global__ __launch_bounds__(kEigThreads) void ng_eig_kernel(NgFoldTable tb, int
         if (sweep == kJacobiSweeps) break;          // out of sweeps: the state's info word counts it
         ++sweeps_done;
         for (int round = 0; round < m - 1; ++round) {
-            // Z <- J^T Z J, U^T <- J^T U^T with, for every pair (p, q), p < q, of the round,
-            // row_p <- c row_p - s row_q,  row_q <- s row_p + c row_q  (and the same for the columns of Z)
-            int pl = lane;                               // the index this lane's index meets (itself: idle)
-            if (on) {
-                int w = 2 * round - lane;                // in (-(m-1), 2(m-1)): reduce mod m-1 without a division
-                if (w < 0) w += m - 1;
-                if (w >= m - 1) w -= m - 1;
-                pl = lane == m - 1 ? round : lane == round ? m - 1 : w;
-                if (pl >= r) pl = lane;                  // the bye of an odd rank
-            }
-            double cl = 1.0, sl = 0.0;                   // rotation of the pair this lane's index is in
-            if (pl != lane) {
-                const int p = min(lane, pl), q = max(lane, pl);
-                const double app = Zs[p * rs + p], aqq = Zs[q * rs + q], apq = Zs[p * rs + q];
-                // t = sgn(tau) / (|tau| + sqrt(1 + tau^2)) with tau = (aqq - app) / (2 apq)
-                const double d = aqq - app, b2 = 2.0 * apq;
-                const double h2 = d * d + b2 * b2;
-                if (apq != 0.0 && h2 > 1e-280) {         // (below that the entry is nothing against any diagonal)
-                    const double t = (d >= 0.0 ? b2 : -b2) * fast_rcp(fabs(d) + h2 * fast_rsqrt(h2));
-                    cl = fast_rsqrt(1.0 + t * t);
-                    sl = t * cl;
-                }
-            }
-            // row `lane` (and column `lane`) turns into al row_lane + bl row_partner
-            const double al = cl, bl = lane < pl ? -sl : sl;
-            // One pass: the group of pair k holds rows p and q; lane l rotates the rows (in registers), fetches the
-            // rotated entries of column partner(l) from the lane that holds them and rotates the columns.
-            for (int k = grp; k < half; k += ngrp) {
-                int p, q;
-                if (k == 0) { p = m - 1; q = round; }
-                else {
-                    p = round + k;     if (p >= m - 1) p -= m - 1;
-                    q = round - k;     if (q < 0) q += m - 1;
-                }
-                if (p > q) { const int t = p; p = q; q = t; }
-                const bool two = q < r;                  // else the bye: row and column p stay
-                const int qr = two ? q : p;
-                const double c = two ? __shfl(cl, p, lw) : 1.0, s = two ? __shfl(sl, p, lw) : 0.0;
-                const double zp = on ? Zs[p * rs + lane] : 0.0, zq = (on && two) ? Zs[qr * rs + lane] : 0.0;
-                const double up = on ? Us[p * rs + lane] : 0.0, uq = (on && two) ? Us[qr * rs + lane] : 0.0;
-                const double wp = c * zp - s * zq, wq = s * zp + c * zq;
-                const double wpo = __shfl(wp, pl, lw), wqo = __shfl(wq, pl, lw);
-                if (on) {
-                    Zn[p * rs + lane] = al * wp + bl * wpo;
-                    Un[p * rs + lane] = c * up - s * uq;
-                    if (two) {
-                        Zn[q * rs + lane] = al * wq + bl * wqo;
-                        Un[q * rs + lane] = s * up + c * uq;
-                    }
-                }
-            }
-            __syncthreads();
-            { double* t = Zs; Zs = Zn; Zn = t; t = Us; Us = Un; Un = t; }
+            const int next = round + 1 < m - 1 ? round + 1 : 0;
+            if (cur == 0) rotate(std::integral_constant<int, 0>{}, next);
+            else rotate(std::integral_constant<int, 1>{}, next);
+            cur ^= 1;
         }
     }
+    const double* Zs = smem + cur * MAT;
+    const double* Us = smem + (2 + cur) * MAT;
     // descending order of the eigenvalues (ties by index)
     if (tid < r) {
-        const double ci = Zs[tid * rs + tid];
+        const double ci = Zs[tid * (LD + 1)];
         int pos = 0;
         for (int j = 0; j < r; ++j) {
-            const double cj = Zs[j * rs + j];
+            const double cj = Zs[j * (LD + 1)];
             if (cj > ci || (cj == ci && j < tid)) ++pos;
         }
         order[pos] = tid;
     }
     __syncthreads();
     const StateView v = state_view(tb.state[slot] + (int64_t)b * tb.st_b, dim, rank);
-    if (tid == 0) {
-        const double cmax = Zs[order[0] * rs + order[0]];
-        double sumd = 0.0, sumsq = 0.0;
-        for (int j = 0; j < r; ++j) sumd += v.d[j];
-        const double rho = *v.rho;
-        for (int i = 0; i < r; ++i) {
-            double c = Zs[order[i] * rs + order[i]];
-            c = fmax(c, kCFloor * cmax);
-            const double sq = sqrt(c);
-            Zs[order[i] * rs + order[i]] = sq;          // keep sqrt(c_i) on the diagonal for the other threads
-            sumsq += sq;
-        }
+    if (tid < 64) {                                 // one wavefront, lane i = the i-th largest eigenvalue
+        const bool has = tid < r;
+        const double cmax = Zs[order[0] * (LD + 1)];
+        const double old_d = has ? v.d[tid] : 0.0, rho = *v.rho;
+        const double sq = has ? sqrt(fmax(Zs[order[tid] * (LD + 1)], kCFloor * cmax)) : 0.0;
+        if (has) red[tid] = sq;
+        const double sumd = wave_sum(old_d), sumsq = wave_sum(sq);
         const double trT = (double)eta * tb.scal[slot][b * 2 + 0] / (double)n + (1.0 - (double)eta) * ((double)dim * rho + sumd);
-        double rho_new = (trT - sumsq) / (double)(dim - rank);
-        double dmax = -1e300;
-        for (int i = 0; i < r; ++i) {
-            const double di = Zs[order[i] * rs + order[i]] - rho_new;
-            v.d[i] = di;
-            dmax = fmax(dmax, di);
-        }
-        rho_new = fmax(rho_new, kEps);
+        const double rho_new = (trT - sumsq) / (double)(dim - rank);
+        const double di = has ? sq - rho_new : -1e300;
+        double dmax = di;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o, 64));
         const double floor_d = fmax(kEps, kDelta * dmax);
-        for (int i = 0; i < r; ++i) v.d[i] = fmax(v.d[i], floor_d);
-        *v.rho = rho_new;
-        if (bump_t) *v.t = *v.t + 1;
-        v.info[0] = sweeps_done;
-        if (!converged) v.info[1] += 1;
+        if (has) v.d[tid] = fmax(di, floor_d);
+        if (tid == 0) {
+            *v.rho = fmax(rho_new, kEps);
+            if (bump_t) *v.t = *v.t + 1;
+            v.info[0] = sweeps_done;
+            if (!converged) v.info[1] += 1;
+        }
     }
     __syncthreads();
     double* __restrict__ Wb = Wt + zi * kMaxRank * kMaxRank;
-    for (int w = tid; w < r * r; w += kEigThreads) {
+    for (int w = tid; w < r * r; w += NT) {
         const int i = w / r, k = w - i * r;
-        const int col = order[i];
-        Wb[w] = Us[col * rs + k] / Zs[col * rs + col];
+        Wb[w] = Us[order[i] * LD + k] / red[i];
     }
 }
 
@@ -982,7 +1002,7 @@ struct NgCall {
     } while (0)
 #define NG_LAUNCHED() NG_CHECK(note_hip_error(hipGetLastError()))
 
-int ng_eig_smem_bytes(int rank) { return (4 * rank * ((rank + 1) & ~1) + 16) * 8 + 64 * 4; }
+int ng_eig_smem_bytes(int rank) { return (4 * (rank <= 32 ? kEigMat<32> : kEigMat<64>) + 64) * 8 + 64 * 4; }
 
 // Z = Y Y^T and its eigen-decomposition, new (d, rho, t) and Wt for every (slot, replica) of the table: two launches.
 // Reads Y, the squared norms and the old d, rho; does not touch R.
@@ -1000,7 +1020,9 @@ int ng_finish_zeig(const NgFoldTable& tb, int rank, int n, float eta, bool y64, 
         int dev = -1;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) dev = -1;
         if (dev < 0 || raised[dev] < smem) {
-            NG_CHECK(note_hip_error(hipFuncSetAttribute(reinterpret_cast<const void*>(ng_eig_kernel),
+            NG_CHECK(note_hip_error(hipFuncSetAttribute(reinterpret_cast<const void*>(ng_eig_kernel<32>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem)));
+            NG_CHECK(note_hip_error(hipFuncSetAttribute(reinterpret_cast<const void*>(ng_eig_kernel<64>),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem)));
             if (dev >= 0) raised[dev] = smem;
         }
@@ -1009,7 +1031,8 @@ int ng_finish_zeig(const NgFoldTable& tb, int rank, int n, float eta, bool y64, 
     if (y64) hipLaunchKernelGGL(ng_z_kernel<double>, gz, dim3(256), 0, s, tb, rank, Z);
     else hipLaunchKernelGGL(ng_z_kernel<float>, gz, dim3(256), 0, s, tb, rank, Z);
     NG_LAUNCHED();
-    hipLaunchKernelGGL(ng_eig_kernel, dim3(tb.nslots * tb.batch), dim3(kEigThreads), smem, s, tb, rank, n, eta, Z, Wt, bump);
+    if (rank <= 32) hipLaunchKernelGGL(ng_eig_kernel<32>, dim3(tb.nslots * tb.batch), dim3(kEigThreads<32>), smem, s, tb, rank, n, eta, Z, Wt, bump);
+    else hipLaunchKernelGGL(ng_eig_kernel<64>, dim3(tb.nslots * tb.batch), dim3(kEigThreads<64>), smem, s, tb, rank, n, eta, Z, Wt, bump);
     NG_LAUNCHED();
     return 0;
 }

@@ -90,6 +90,12 @@ def test_precondition_sequence_matches_oracle(n, dim, rank):
     assert np.array_equal(host(st), before)
 
 
+# one index, one pair, the last odd and the full group of 32 lanes, the first rank of the 64-lane groups, an odd one there
+@pytest.mark.parametrize("n,dim,rank", [(64, 41, 1), (64, 41, 2), (64, 100, 31), (64, 100, 32), (128, 200, 63)])
+def test_eigen_solver_at_the_edges_of_its_groups(n, dim, rank):
+    test_precondition_sequence_matches_oracle(n, dim, rank)
+
+
 def test_ngsgd_validation_on_device_side_arguments():
     from paper_1507_01239_amd import binding as B
     A = 1 << 20
