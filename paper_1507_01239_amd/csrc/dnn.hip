@@ -67,6 +67,7 @@ Workspace make_workspace(const Layout& y, int n, int k, uint32_t flags, int ng_r
     Workspace w;
     int64_t g = 0;
     for (int l = 1; l <= y.L; ++l) {
+        if (l > 2 && y.d[l] == y.d[l - 1] && y.d[l - 1] == y.d[l - 2]) continue;      // the same products as layer l - 1
         int64_t f = gemm_ws_floats(n, y.d[l], y.d[l - 1], k);                  // forward
         if (f > g) g = f;
         if (l > 1) { f = gemm_ws_floats(n, y.d[l - 1], y.d[l], k); if (f > g) g = f; }   // back-propagation

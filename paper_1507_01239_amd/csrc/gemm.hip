@@ -217,11 +217,19 @@ int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch) {
 }
 
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg, int force_splits) {
-    int64_t f = plan_floats(gemm_plan(M, N, K, batch, force_cfg, force_splits), M, N, batch);
+    int64_t f = 0;
     auto cover = [&](const GemmPlan& pl) { const int64_t g = plan_floats(pl, M, N, batch); if (g > f) f = g; };
+    const bool forced = force_cfg >= 0 && force_cfg < kNumCfgs;
     // what runs when the operands' alignment rules a plan out
+    cover(gemm_plan_fp32(M, N, K, batch, forced ? CFG_64_REG : CFG_AUTO, force_splits));
+    // (Below 512 steps the split-operand kernels run unsplit when they are chosen, so the fp32 plans are all there is to
+    // cover; callers ask on every call, and the comparison of plans is most of the host time of a small one.)
+    if (!forced && force_splits <= 0 && K < 512) {
+        cover(gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits));
+        return f;
+    }
+    cover(gemm_plan(M, N, K, batch, force_cfg, force_splits));
     cover(gemm_plan(M, N, K, batch, force_cfg, force_splits, true));
-    cover(gemm_plan_fp32(M, N, K, batch, force_cfg < 0 || force_cfg >= kNumCfgs ? CFG_AUTO : CFG_64_REG, force_splits));
     return f;
 }
 
