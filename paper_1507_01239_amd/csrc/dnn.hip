@@ -149,6 +149,9 @@ extern "C" int32_t dnn_forward(const mavg_shape* shape, int32_t k, const float* 
     if (w.total_floats > 0 && (!workspace || workspace_bytes < w.total_floats * 4 + 256)) return MAVG_E_WORKSPACE;
     float* ws = workspace ? ws_base(workspace) : nullptr;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const int act_tanh = shape->hidden_act == MAVG_ACT_TANH;
+    if (narrow_net(y.d, y.L))
+        return narrow_forward_launch(y.d, y.L, act_tanh, k, theta, theta_stride, x, x_stride, n, acts, act_stride, s) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
     for (int l = 1; l <= y.L; ++l) {
         GemmDesc g;
         g.M = n; g.N = y.d[l]; g.K = y.d[l - 1]; g.batch = k;
@@ -158,7 +161,7 @@ extern "C" int32_t dnn_forward(const mavg_shape* shape, int32_t k, const float* 
         g.B = theta + y.w_off[l]; g.ldb = y.d[l - 1]; g.b_bstride = theta_stride; g.b_kc = true;
         g.C = acts + y.a_off[l]; g.ldc = y.d[l]; g.c_bstride = act_stride;
         g.epi.kind = (l < y.L) ? EPI_BIAS_SIGMOID : EPI_BIAS;
-        g.epi.act_tanh = shape->hidden_act == MAVG_ACT_TANH;
+        g.epi.act_tanh = act_tanh;
         g.epi.bias = theta + y.b_off[l]; g.epi.bias_bstride = theta_stride;
         if (gemm_launch(g, ws ? ws + w.off_gemm : nullptr, w.gemm_floats, s) != 0) return MAVG_E_LAUNCH;
     }
@@ -200,6 +203,11 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
     auto delta_of = [&](int l) { return ws + w.off_delta[l]; };
     auto dstride_of = [&](int l) { return (int64_t)n * w.ld_delta[l]; };
 
+    const int act_tanh = shape->hidden_act == MAVG_ACT_TANH;
+    if (!ng && n <= kNarrowRows && narrow_net(y.d, y.L))
+        return narrow_backward_launch(y.d, y.L, act_tanh, k, theta, theta_stride, y.P, x, x_stride, labels, label_stride, n, acts, act_stride,
+                                      y.acts, lr, scale, loss_sum, s) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
+
     if (ce_delta_launch(acts + y.a_off[y.L], y.d[y.L], act_stride, labels, label_stride, delta_of(y.L), w.ld_delta[y.L],
                         dstride_of(y.L), loss_sum, n, y.d[y.L], k, scale, s) != 0) return MAVG_E_LAUNCH;
 
@@ -212,7 +220,7 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
         g.B = theta + y.w_off[l]; g.ldb = y.d[l - 1]; g.b_bstride = theta_stride; g.b_kc = false;
         g.C = delta_of(l - 1); g.ldc = w.ld_delta[l - 1]; g.c_bstride = dstride_of(l - 1);
         g.epi.kind = EPI_MUL_DSIGMOID;
-        g.epi.act_tanh = shape->hidden_act == MAVG_ACT_TANH;
+        g.epi.act_tanh = act_tanh;
         g.epi.aux = acts + y.a_off[l - 1]; g.epi.ldaux = y.d[l - 1]; g.epi.aux_bstride = act_stride;
         if (gemm_launch(g, gws, w.gemm_floats, s) != 0) return MAVG_E_LAUNCH;
     }

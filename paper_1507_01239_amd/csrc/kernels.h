@@ -30,4 +30,16 @@ int copy_bcast_launch(const float* src, int64_t count, float* dst, int64_t dst_b
 int count_correct_launch(const float* p, int64_t ld, int64_t bstride, const int32_t* labels, int64_t label_bstride,
                          int rows, int cols, int batch, int32_t* correct, hipStream_t s);
 
+// Networks of at most kNarrowLayers layers, all (the input among them) at most kNarrowWidth wide: whole passes in one
+// launch (narrow.hip).  The backward pass with plain SGD takes up to kNarrowRows rows; `params` and `act_count` are the
+// parameters and the activations of one replica.
+constexpr int kNarrowWidth = 64, kNarrowRows = 64, kNarrowLayers = 64;
+struct NarrowNet { int L, act_tanh, d[kNarrowLayers + 1]; };
+bool narrow_net(const int* d, int L);
+int narrow_forward_launch(const int* d, int L, int act_tanh, int k, const float* theta, int64_t theta_stride, const float* x,
+                          int64_t x_stride, int n, float* acts, int64_t act_stride, hipStream_t s);
+int narrow_backward_launch(const int* d, int L, int act_tanh, int k, float* theta, int64_t theta_stride, int64_t params, const float* x,
+                           int64_t x_stride, const int32_t* labels, int64_t label_stride, int n, const float* acts, int64_t act_stride,
+                           int64_t act_count, float lr, float scale, float* loss_sum, hipStream_t s);
+
 }  // namespace mavg

@@ -377,3 +377,29 @@ def test_shared_labels_and_inputs_across_replicas():
     for k in range(K):
         check_tensors(th[k], ref, dims, 1e-5, f"replica {k}")
         assert int(host(correct)[k]) == want
+
+
+# The one-launch passes of networks at most 64 wide: one unit and one row, the edges of the 16-wide blocks, of the forward
+# pass's 32 rows and of the backward pass's 64 (65 rows: general backward pass), the full width, one layer, many layers.
+# Sums of at most 64 products in float32: 64 * 2^-24 = 4e-6 of their terms, through a few layers.
+@pytest.mark.parametrize("dims,n,k,hidden,mean", [
+    ([1, 1, 2], 1, 1, "sigmoid", True), ([64, 64, 64], 64, 3, "tanh", True), ([17, 15, 16, 33], 33, 2, "sigmoid", False),
+    ([63, 1, 64, 5], 16, 2, "tanh", False), ([40, 64, 64, 32], 65, 2, "sigmoid", True), ([5, 3], 47, 4, "sigmoid", True),
+    ([64] * 12, 49, 1, "tanh", True), ([64, 65, 64], 64, 2, "sigmoid", True)])
+def test_networks_of_narrow_layers(dims, n, k, hidden, mean):
+    from paper_1507_01239_amd import binding as B
+    theta0 = gen.init_theta(dims, 3, 0.3)
+    g = Gpu(dims, k, n, theta0, flags=B.MEAN_GRAD if mean else 0, hidden_act=B.ACT_TANH if hidden == "tanh" else B.ACT_SIGMOID)
+    g.ws.fill_(255)
+    X = np.zeros((k, (n * dims[0] + 3) // 4 * 4), np.float32)
+    x = np.stack([gen.features_iid(n, dims[0], 3, r, 0) for r in range(k)])
+    X[:, :n * dims[0]] = x.reshape(k, -1)
+    Y = np.stack([gen.labels_uniform(n, dims[-1], 3, r, 0) for r in range(k)])
+    lr = 0.5 if mean else 0.5 / n
+    g.forward(X)
+    g.backward(Y, lr)
+    for r in range(k):
+        ref, loss, acts = dnn.sgd_step(theta0, dims, x[r], Y[r], lr, mean_grad=mean, hidden=hidden)
+        check_acts(g.activations(r), acts, 1e-5, f"replica {r}")
+        check_tensors(g.params()[r], ref, dims, 1e-5, f"replica {r}")
+        assert abs(host(g.loss)[r] - loss) <= 1e-5 * abs(loss) + 1e-6
