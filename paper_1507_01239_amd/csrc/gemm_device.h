@@ -117,6 +117,7 @@ __device__ __forceinline__ const float* at_off(const float* ubase, uint32_t off)
 // are this wavefront's to write (a workgroup whose wavefronts share the epilogue of one accumulator); -1 = all of them.
 // Read-modify-write epilogues request the old values of all blocks back to back before the first store: loads and stores
 // count in one in-order counter, so a load behind a store would wait for that store to reach memory.
+// (C2's old values: block by block, so that a wavefront of four blocks needs 16 registers for them and not 64.)
 template <int KIND, int TM, int TN>
 __device__ __forceinline__ void write_tile(const floatx16 (&acc)[TM][TN], const Epilogue& e, const EpiCtx& c,
                                            int64_t ldc, int M, int N, int mbase, int nbase, int lrow, int lcol, int bands = -1) {
@@ -176,6 +177,16 @@ __device__ __forceinline__ void write_tile(const floatx16 (&acc)[TM][TN], const 
         const bool lastcol = LC && n == e.lastcol;
         float bias_n = 0.f;
         if (kBias && n_ok) bias_n = c.bias[n];
+        float old2[KIND == EPI_AXPBY ? 16 : 1];
+        if constexpr (KIND == EPI_AXPBY) {
+            if (c.C2)
+                static_for<16>([&](auto vc) {
+                    constexpr int v = decltype(vc)::value;
+                    const int mu = mb + i * 32 + 8 * (v >> 2) + (v & 3);
+                    old2[v] = 0.f;
+                    if (((bands >> (v >> 2)) & 1) && (IN || mu + 4 * lrow < M) && n_ok) old2[v] = *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2);
+                });
+        }
         static_for<16>([&](auto vc) {
             constexpr int v = decltype(vc)::value;
             const int mu = mb + i * 32 + 8 * (v >> 2) + (v & 3);
@@ -195,7 +206,7 @@ __device__ __forceinline__ void write_tile(const floatx16 (&acc)[TM][TN], const 
                     const float r = c.alpha * a + e.beta * old[t][v];
                     if (lastcol) c.lastcol_dst[m] = r;
                     else *dst = r;
-                    if (c.C2) *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) += r;
+                    if (c.C2) *at_off(c.C2 + (int64_t)mu * e.ldc2, offC2) = old2[v] + r;
                 } else if constexpr (KIND == EPI_BIAS_SIGMOID_SAMPLE) {
                     const float pr = sigmoidf_dev(a + bias_n);
                     if (c.C) *dst = pr;
