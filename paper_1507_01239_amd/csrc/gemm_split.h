@@ -65,21 +65,26 @@ __device__ __forceinline__ bool block_not_finite(const floatx16& a) {
     return __any(!(t == 0.f));
 }
 
-// The 32x32 block at (mb, nb) over contraction steps [kbeg, kend) on the fp32 matrix cores, operands element by element.
+constexpr int kSplitBK = 16;      // contraction steps per k-tile: one MFMA
+
+// The 32x32 block at (mb, nb) over contraction steps [kbeg, kend), of which those of every `stride`-th k-tile, on the fp32
+// matrix cores, operands element by element.
 template <bool AKC, bool BKC>
 __device__ __forceinline__ floatx16 block_fp32(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N,
-                                                          int mb, int nb, int kbeg, int kend) {
+                                                          int mb, int nb, int kbeg, int kend, int stride) {
     const int lane = threadIdx.x & 63, lrow = lane >> 5, lcol = lane & 31;
     const int m = min(mb + lcol, M - 1), n = min(nb + lcol, N - 1);
     floatx16 acc = floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int k0 = kbeg; k0 < kend; k0 += 2) {
-        const int k = k0 + lrow;
-        const bool ok = k < kend;
-        const float a = ok ? (AKC ? A[(int64_t)m * lda + k] : A[(int64_t)k * lda + m]) : 0.f;
-        const float b = ok ? (BKC ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
-    }
+    for (int kt = kbeg; kt < kend; kt += stride * kSplitBK)
+#pragma unroll 1
+        for (int k0 = kt; k0 < kt + kSplitBK && k0 < kend; k0 += 2) {
+            const int k = k0 + lrow;
+            const bool ok = k < kend;
+            const float a = ok ? (AKC ? A[(int64_t)m * lda + k] : A[(int64_t)k * lda + m]) : 0.f;
+            const float b = ok ? (BKC ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+        }
     return acc;
 }
 
@@ -87,7 +92,6 @@ __device__ __forceinline__ floatx16 block_fp32(const float* A, int64_t lda, cons
 //   k-contiguous operand: W = 4, unit c -> row c / 4, steps 4 (c % 4) ..: four neighbouring lanes read the 64 bytes of one
 //     row with one load (two lanes of 8 steps each, two loads apiece, touch twice the cache lines per load)
 //   m/n-contiguous operand: W = 8, unit c -> row c % BR, steps 8 (c / BR) ..: a wavefront reads 256 bytes of each of 8 k-rows
-constexpr int kSplitBK = 16;      // contraction steps per k-tile: one MFMA
 template <int BR, int NT, bool KC>
 struct SplitOperand {
     static constexpr int BK = kSplitBK, W = KC ? 4 : 8, Q = BK / W, CH = BR * Q / NT;     // units per row, units per thread
@@ -103,7 +107,7 @@ struct SplitOperand {
     GlobalF base;           // (uniform) row r0 (or column), contraction step kfull
     int64_t ld;
 
-    // kfull: where k-tile 0 of the whole ones would begin (before kbeg when a partial tile goes first)
+    // kfull: where the first whole k-tile begins
     __device__ __forceinline__ void init(const float* P, int64_t ld_, int r0, int R, int64_t kfull, int tid) {
         ld = (int64_t)uniform_u64((uint64_t)ld_);
         base = (GlobalF)uniform_u64(reinterpret_cast<uint64_t>(KC ? P + (int64_t)r0 * ld_ + kfull : P + kfull * ld_ + r0));
@@ -184,27 +188,26 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
     int tm_i, tn_i;
     tile_coords(p, tile, tm_i, tn_i);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
-    int kbeg = split * p.kper, kend = min(p.K, kbeg + p.kper);
-    int nloop = 0;                 // every wavefront takes part in this many barriers
-    if constexpr (KG > 1) {        // this k-group's share, in whole k-tiles
-        const int all = (kend - kbeg + BK - 1) / BK, base = all / KG, rem = all % KG;
-        nloop = base + (rem > 0 ? 1 : 0);
-        const int first = kbeg + (kg * base + min(kg, rem)) * BK;
-        kend = min(kend, first + (base + (kg < rem ? 1 : 0)) * BK);
-        kbeg = min(first, kend);
-    }
-    const int nkt = __builtin_amdgcn_readfirstlane((kend - kbeg + BK - 1) / BK);
+    const int kbeg = split * p.kper, kend = min(p.K, kbeg + p.kper);
+    // k-group g takes k-tiles g, g + KG, ...: what the groups of a workgroup read at a time are neighbouring pieces of the
+    // same cache lines (a k-tile is half a line of a k-contiguous operand): 1024 x 2048 x 2048 55.9 against 59.1 us with a
+    // contiguous share per group, 256 x 8000 x 2048 57.0 against 64.8.
+    constexpr int KS = KG * BK;
+    const int all = (kend - kbeg + BK - 1) / BK, first = kbeg + kg * BK;
+    const int nloop = (all + KG - 1) / KG;                     // every wavefront takes part in this many barriers
+    const int nkt = __builtin_amdgcn_readfirstlane(all > kg ? (all - kg + KG - 1) / KG : 0);
     const float* A = p.A + (int64_t)b * p.a_bstride;
     const float* B = p.B + (int64_t)b * p.b_bstride;
     OpA oa;
     OpB ob;
     // A partial k-tile (contraction not a multiple of 16) goes first, so that the loop's loads are all whole ones and
-    // their number in flight is known: tile 0 is the last `left` steps then, tile t > 0 begins at step (t - 1) BK.
-    // (The host sends contractions of at least 16 steps.  A range that is a partial tile alone, or empty, is not the first
-    // one, so 16 steps lie before it, and those are what its unused loads of whole tiles read.)
-    const int left = (kend - kbeg) % BK, shift = left > 0 ? BK : 0, kpart = kend - left - kbeg + shift;
-    oa.init(A, p.lda, m0, p.M, (int64_t)kbeg - shift, tid);
-    ob.init(B, p.ldb, n0, p.N, (int64_t)kbeg - shift, tid);
+    // their number in flight is known: tile 0 is the last `left` steps then, tile t > 0 the (t - 1)-th whole one.
+    // (The host sends contractions of at least 16 steps.  A group without a whole tile reads, and never uses, the first
+    // whole one of the range, or the one before a range that is a partial tile alone, which is not the first range.)
+    const int left = nkt > 0 && (all - 1) % KG == kg ? (kend - kbeg) % BK : 0, part = left > 0 ? 1 : 0;
+    const int kwhole = nkt > part ? first : kend - kbeg >= BK ? kbeg : kbeg - BK;
+    oa.init(A, p.lda, m0, p.M, kwhole, tid);
+    ob.init(B, p.ldb, n0, p.N, kwhole, tid);
 
     floatx16 acc[TM][TN];
     static_for<TM * TN>([&](auto tc) {
@@ -224,9 +227,9 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
 
     float xa[2][OpA::CH][OpA::W], xb[2][OpB::CH][OpB::W];       // two k-tiles on their way, tile t in set t & 1
     auto load = [&](int tl, auto setc) {
-        const int t = min(tl, nkt - 1);
-        oa.template load<true>(t * BK, BK, xa[decltype(setc)::value], tid);
-        ob.template load<true>(t * BK, BK, xb[decltype(setc)::value], tid);
+        const int k = max(min(tl, nkt - 1) - part, 0) * KS;
+        oa.template load<true>(k, BK, xa[decltype(setc)::value], tid);
+        ob.template load<true>(k, BK, xb[decltype(setc)::value], tid);
     };
     auto row_sums = [&](int t, auto setc) {
         constexpr int set = decltype(setc)::value;
@@ -237,7 +240,7 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
                 const int q = rs_grp + i * RS_G;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const int k = (t == 0 && shift > 0 ? kpart : t * BK) - shift + 8 * q + j;
+                    const int k = (t < part ? kend - left - kbeg : (t - part) * KS) + 8 * q + j;      // (one k-group: from kbeg on)
                     if (rw) { if (k < kend - kbeg) rowsum += xa[set][i][j] * rw[k]; }
                     else rowsum += xa[set][i][j];
                 }
@@ -300,8 +303,8 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
     typedef std::integral_constant<int, 0> C0;
     typedef std::integral_constant<int, 1> C1;
     if (left > 0) {
-        oa.template load<false>(kpart, left, xa[0], tid);
-        ob.template load<false>(kpart, left, xb[0], tid);
+        oa.template load<false>(kend - left - kwhole, left, xa[0], tid);
+        ob.template load<false>(kend - left - kwhole, left, xb[0], tid);
     } else {
         load(0, C0{});
     }
@@ -338,7 +341,7 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
     static_for<TM * TN>([&](auto tc) {
         constexpr int i = decltype(tc)::value / TN, j = decltype(tc)::value % TN;
         if (block_not_finite(acc[i][j]))
-            acc[i][j] = block_fp32<AKC, BKC>(A, p.lda, B, p.ldb, p.M, p.N, m0 + wm + 32 * i, n0 + wn + 32 * j, kbeg, kend);
+            acc[i][j] = block_fp32<AKC, BKC>(A, p.lda, B, p.ldb, p.M, p.N, m0 + wm + 32 * i, n0 + wn + 32 * j, first, kend, KG);
     });
 
     int bands = -1;
