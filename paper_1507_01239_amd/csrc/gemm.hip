@@ -167,15 +167,20 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
     const double ks = (double)((K + pl.splits - 1) / pl.splits);
     double c;
     switch (pl.cfg) {
-    case CFG_S128: c = 3 + rounds * (9 + ks * (0.0318 + 0.0100 * full)); break;
-    case CFG_S64x128: c = 3 + rounds * (5 + ks * (0.0185 + 0.0066 * full)); break;
-    case CFG_S64: c = 5 + rounds * (2 + ks * 0.0151); break;      // (up to three workgroups per compute unit)
-    case CFG_S32x64: c = 3 + rounds * (4 + ks * (0.0062 + 0.0022 * full)); break;
+    case CFG_S128: c = 3 + rounds * (9 + ks * (0.0284 + 0.0131 * full * full)); break;
+    case CFG_S64x128: c = 3 + rounds * (5 + ks * (0.0180 + 0.0055 * full * full)); break;
+    case CFG_S64: c = 5 + rounds * (2 + ks * 0.0132) + (rounds == 1 ? ks * 0.005 : 0.0); break;      // (up to three workgroups per compute unit)
+    case CFG_S32x64: c = 2.3 + rounds * (5.7 + ks * 0.0077); break;
     case CFG_KG_32x64: c = 5 + rounds * ks * 0.0075; break;
-    case CFG_KG_32x32: c = 5 + rounds * ks * 0.0049; break;
+    case CFG_KG_32x32: c = 5 + (w < kNumCU ? 1.0 : (double)w / kNumCU) * ks * 0.0049; break;      // (two workgroups per compute unit)
     default: c = 5 + rounds * ks * 0.0158 * (rounds == 1 ? 1.2 : 1.0) * (ragged ? 2.2 : 1.0); break;
     }
-    if (pl.splits > 1) c += 4 + 8.0 * pl.splits * M * N * batch / 6e6;
+    if (pl.splits > 1) {
+        // the reducer and the partial sums; next to the split-operand kernels less of it shows, as their own epilogue is then
+        // a plain store
+        const double bytes = 8.0 * pl.splits * M * N * batch;
+        c += cfg_split(pl.cfg) ? 3.5 + bytes / 20e6 + (bytes > 32e6 ? (bytes - 32e6) / 8e6 : 0.0) : 4 + bytes / 6e6;
+    }
     return c;
 }
 
@@ -184,6 +189,7 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
 //   4096 x 8000 x 2048: 976 / 753 (128x128)       1999 x 2048 x 2048: 138 / 99 (128x128)     1024 x 8000 x 2048: 261 / 191 (128x128)
 //   256 x 8000 x 2048: 67 / 60 (64x128)           1024 x 2048 x 8000: 244 / 206 (64x128)     512 x 2048 x 8000: 135 / 100 (128x128, 4 splits)
 //   768 x 2048 x 2048: 57 / 51 (64x128)           384 x 8000 x 2048: 96 / 82 (128x128)
+//   512 x 2048 x 2048: 39 / 36 (64x128, 2 splits; 64x64 unsplit 44)
 //   256 x 2048 x 2048: 21.7 / 24.9 (not taken)    128 x 2048 x 8000: 38 / 43 (not taken)     2048 x 2048 x 256: 22.5 / 24.5 (not taken)
 // and with rows that are not 16-byte aligned:
 //   200 x 1021 x 1021: 27 / 16 (32x64)            1000 x 3003 x 1021: 126 / 50 (128x128)     200 x 3003 x 1021: 55 / 26 (64x64)
@@ -195,7 +201,7 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
     GemmPlan best = gemm_plan_fp32(M, N, K, batch, force_cfg, force_splits);
     if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < 16) return best;
     if (ragged && best.cfg != CFG_64) best = gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits);
-    double least = plan_cost(best, M, N, K, batch, ragged) * 0.97;
+    double least = plan_cost(best, M, N, K, batch, ragged) * 0.97 - 0.5;
     const int sums = best.splits * (cfg_kg(best.cfg) ? 4 : 1);
     static const struct { int cfg, kgroups; } kSplitCfgs[] = {{CFG_S128, 2}, {CFG_S64x128, 4}, {CFG_S64, 2}, {CFG_S32x64, 8}};
     for (const auto& sc : kSplitCfgs)
@@ -361,17 +367,19 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
     if (thin) return gemm_launch_grouped_thin(d, count, stream);
     // Three passes over the problems: those for the split-operand kernel (128x128 tiles; m- and n-contiguous operands), those
     // the direct-to-LDS kernel accepts, and the rest (register-staged kernel).
-    // The split-operand kernel takes the launch when its tiles come to at least half the compute units and the contraction is
-    // long enough for its faster multiplies to matter next to the read-modify-write of C: the seven weight updates of
+    // The split-operand kernel takes the launch when its tiles come to at least four per compute unit, two from 512 steps on
+    // (with fewer the read-modify-write of C has nothing to hide behind: 140 tiles, two replicas of 1696 x 528 and 64 x 1696 at 270
+    // rows, made the step 88 us, 73 with 64x64 tiles of fp32 MFMAs) and the contraction is long enough for its faster
+    // multiplies to matter next to that: the seven weight updates of
     // 440-6x2048-8000 take 116 us either way at minibatch 128 (memory), 134 against 145 us at 192, 152 against 177 at 256,
-    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from 16 steps on (the alternative
+    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from half a tile per compute unit and 16 steps on (the alternative
     // there is the register-staged kernel, 28 against 21 us at 3003 x 1021 x 200).
     int64_t tiles128 = 0;
     for (int i = 0; i < count; ++i) tiles128 += tiles_of(CFG_S128, d[i].M > 0 ? d[i].M : 0, d[i].N > 0 ? d[i].N : 0, d[i].batch);
     auto family = [&](const GemmDesc& di, const GemmKParams& q) {
         const bool dma = dma_eligible(di, q);
         const bool split = split_eligible(di) && !di.a_kc && !di.b_kc && di.epi.side_sum_src == nullptr &&
-                           tiles128 >= kNumCU / 2 && di.K >= (dma ? 192 : 16);
+                           tiles128 >= (!dma ? kNumCU / 2 : di.K >= 512 ? 2 * kNumCU : 4 * kNumCU) && di.K >= (dma ? 192 : 16);
         return split ? 0 : dma ? 1 : 2;
     };
     for (int pass = 0; pass < 3; ++pass) {
