@@ -5,7 +5,7 @@
 // eight launches of about 5 us per minibatch, each a handful of dependent loads.  A layer of 32 rows is eight 16x16 blocks
 // here, of 64 rows sixteen, one per wavefront (v_mfma_f32_16x16x4_f32, fp32 throughout); activations and errors stay in
 // LDS between layers, and the weights of the next layer are requested before the current one is finished.
-// Four replicas of 40-64-64-32, two minibatches of 32 rows and the averaging: 49 us with 5 launches, was 79 with 17.
+// Four replicas of 40-64-64-32, two minibatches of 32 rows and the averaging: 51 us with 5 launches, was 79 with 17.
 // The limits are the tile: one block per wavefront needs no loop over blocks, and the backward pass keeps all rows of a
 // replica in one workgroup (more rows take the general kernels, as do networks with one wider layer).
 #include <hip/hip_runtime.h>
@@ -62,14 +62,15 @@ __global__ __launch_bounds__(512) void narrow_forward_kernel(NarrowNet t, const 
     for (int l = 1; l <= t.L; ++l) {
         const int cur = (l - 1) & 1, N = t.d[l];
         __syncthreads();
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        floatx4 part[2] = {};       // (even and odd chunks: half as many roundings in a row)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (16 * j < t.d[l - 1]) {
                 const floatx4 a = *reinterpret_cast<const floatx4*>(&S[cur][16 * rb + c16][16 * j + 4 * q]);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc = mfma16(a[c], w[j][c], acc);
+                for (int c = 0; c < 4; ++c) part[j & 1] = mfma16(a[c], w[j][c], part[j & 1]);
             }
+        const floatx4 acc = part[0] + part[1];
         const float bias_l = bias;
         if (l < t.L) {
             theta += layer_params(t, l);
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(1024) void narrow_backward_kernel(NarrowNet t, floa
         }
         __syncthreads();
         if (l > 1) {       // rows mb .. of the errors of layer l - 1
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            floatx4 part[2] = {};
             float a_in[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -173,8 +174,9 @@ __global__ __launch_bounds__(1024) void narrow_backward_kernel(NarrowNet t, floa
                 if (16 * j < N) {
                     const floatx4 a = *reinterpret_cast<const floatx4*>(&D[cur][mb + c16][16 * j + 4 * q]);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) acc = mfma16(a[c], b[j][c], acc);
+                    for (int c = 0; c < 4; ++c) part[j & 1] = mfma16(a[c], b[j][c], part[j & 1]);
                 }
+            const floatx4 acc = part[0] + part[1];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int r = mb + 4 * q + v;
@@ -198,16 +200,22 @@ __global__ __launch_bounds__(1024) void narrow_backward_kernel(NarrowNet t, floa
         }
         float* bias = theta + (int64_t)N * K;
         if (tid < N) old_b = bias[tid];
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        floatx4 part[2] = {};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (16 * j < n) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc = mfma16(D[cur][16 * j + 4 * q + c][mb + c16], g[j][c], acc);
+                for (int c = 0; c < 4; ++c) part[j & 1] = mfma16(D[cur][16 * j + 4 * q + c][mb + c16], g[j][c], part[j & 1]);
             }
+        const floatx4 acc = part[0] + part[1];
         float sum = 0.f;
-        if (tid < N)
-            for (int r = 0; r < n; ++r) sum += D[cur][r][tid];
+        if (tid < N) {
+            float rows[4] = {};
+            for (int r = 0; r < kNarrowRows; r += 4)      // (rows past the minibatch are zero)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rows[i] += D[cur][r + i][tid];
+            sum = (rows[0] + rows[1]) + (rows[2] + rows[3]);
+        }
         __syncthreads();       // every wavefront has read the weights
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
