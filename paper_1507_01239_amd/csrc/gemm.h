@@ -96,7 +96,8 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
                    int64_t ws_floats = INT64_MAX);
 // float32 elements of scratch the plan for this problem needs (0 when it is not split), whatever the operands' alignment
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg = -1, int force_splits = 0);
-// ... when only the fp32-MFMA kernels are considered: the least that gemm_launch accepts (it then plans with that much)
+// ... when only the fp32-MFMA kernels are considered, whatever the operands' alignment and strides: the least that
+// gemm_launch accepts for all of them (it then plans with that much)
 int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch);
 // enqueue; returns hipError_t as int (0 = ok).  ws must hold gemm_ws_floats_fp32() floats when that is > 0;
 // with less than gemm_ws_floats() the plan makes do with fewer splits.

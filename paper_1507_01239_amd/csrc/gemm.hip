@@ -218,22 +218,24 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
 
 static int64_t plan_floats(const GemmPlan& pl, int M, int N, int batch) { return pl.splits > 1 ? (int64_t)pl.splits * batch * M * N : 0; }
 
-int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch) {
-    return plan_floats(gemm_plan_fp32(M, N, K, batch, CFG_AUTO, 0), M, N, batch);
+// The fp32 MFMA plans for one problem: the automatic one, and the register-staged one that takes its place where operands
+// are not 16-byte aligned or their strides are too long for the others (an in-workgroup-split plan has no partial sums, the
+// register-staged one for the same sizes up to sixteen splits of them).
+static int64_t plan_floats_fp32(int M, int N, int K, int batch, int cfg, int force_splits) {
+    const int64_t f = plan_floats(gemm_plan_fp32(M, N, K, batch, cfg, force_splits), M, N, batch);
+    const int64_t g = plan_floats(gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits), M, N, batch);
+    return f > g ? f : g;
 }
 
+int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch) { return plan_floats_fp32(M, N, K, batch, CFG_AUTO, 0); }
+
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg, int force_splits) {
-    int64_t f = 0;
-    auto cover = [&](const GemmPlan& pl) { const int64_t g = plan_floats(pl, M, N, batch); if (g > f) f = g; };
     const bool forced = force_cfg >= 0 && force_cfg < kNumCfgs;
-    // what runs when the operands' alignment rules a plan out
-    cover(gemm_plan_fp32(M, N, K, batch, forced ? CFG_64_REG : CFG_AUTO, force_splits));
+    int64_t f = plan_floats_fp32(M, N, K, batch, forced ? CFG_64_REG : CFG_AUTO, force_splits);
     // (Below 512 steps the split-operand kernels run unsplit when they are chosen, so the fp32 plans are all there is to
     // cover; callers ask on every call, and the comparison of plans is most of the host time of a small one.)
-    if (!forced && force_splits <= 0 && K < 512) {
-        cover(gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits));
-        return f;
-    }
+    if (!forced && force_splits <= 0 && K < 512) return f;
+    auto cover = [&](const GemmPlan& pl) { const int64_t g = plan_floats(pl, M, N, batch); if (g > f) f = g; };
     cover(gemm_plan(M, N, K, batch, force_cfg, force_splits));
     cover(gemm_plan(M, N, K, batch, force_cfg, force_splits, true));
     return f;

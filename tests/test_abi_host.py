@@ -5,6 +5,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import gen
 from paper_1507_01239_amd import binding as B
@@ -135,3 +136,30 @@ def test_rbm_and_gemm_validation():
     assert gg([pr(lda=4)]) == B.E_ALIGN
     assert gg([pr(epi=7)]) == B.E_FLAG
     assert gg([pr(epi=1)]) == B.E_NULL                   # bias epilogue without a bias
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="calls the library with addresses that are never dereferenced: only where nothing can be launched")
+def test_every_plan_fits_the_scratch_that_the_size_queries_report():
+    # Without a GPU a call that passes every host check fails at its launch ("no ROCm-capable device"); a plan whose partial
+    # sums do not fit the scratch fails before that, with "invalid argument".  Ragged rows, where the register-staged kernels
+    # replace plans without partial sums, from a few rows and hundreds of steps to several rounds of tiles.
+    A = 1 << 20
+
+    def reaches_the_launch(fn, *a, **kw):
+        with pytest.raises(B.MavgError) as e:
+            fn(*a, stream=0, **kw)
+        assert e.value.code == B.E_LAUNCH and "device" in str(e.value), (a, str(e.value))
+
+    rng = np.random.default_rng(0)
+    shapes = [(3846, 3128, 36), (3791, 3061, 40), (3125, 3044, 33), (3925, 3200, 48), (3201, 3480, 34), (1593, 4084, 103)]
+    shapes += [(int(rng.integers(3125, 4096)), int(rng.integers(2000, 4200)), int(rng.integers(33, 163))) for _ in range(4000)]
+    shapes += [tuple(int(np.exp(rng.uniform(np.log(lo), np.log(hi)))) for lo, hi in ((16, 9000), (16, 9000), (1, 4096))) for _ in range(4000)]
+    for V, H, n in shapes:
+        # (the reconstruction contracts over n_hid: the same product with the two widths exchanged)
+        for v, h in ((V, H), (H, V)):
+            reaches_the_launch(B.rbm_hidden_prob, v, h, A, A, A, n, A, A, workspace_bytes=B.rbm_workspace_bytes(v, h, n))
+        for lda, ldb in ((V, V), ((V + 3) // 4 * 4,) * 2, (1 << 22, V)):
+            reaches_the_launch(B.mavg_gemm, A, lda, 1, A, ldb, 1, A, H, n, H, V, 0, None, None, 0, 1.0, 0.0, -1, 0, A,
+                               workspace_bytes=B.mavg_gemm_workspace_bytes(n, H, V, -1, 0))
+    reaches_the_launch(B.mavg_gemm, A, 1 << 22, 1, A, 2048, 1, A, 2048, 256, 2048, 2048, 0, None, None, 0, 1.0, 0.0, -1, 0, A,
+                       workspace_bytes=B.mavg_gemm_workspace_bytes(256, 2048, 2048, -1, 0))

@@ -143,6 +143,23 @@ def test_config4_gaussian_then_bernoulli_full_size():
         st2 = {k: v.astype(np.float32) for k, v in _one_step(2048, 2048, n, B.VIS_BERNOULLI, B.SAMPLE_V1, 0.4, 0.9, seed, step, 1, st2, V0).items()}
 
 
+# Ragged rows and few of them over a long contraction, n_vis or n_hid steps: products whose register-staged plan has up to
+# sixteen contraction splits, in exactly the scratch that the size query reports.
+@pytest.mark.parametrize("V,H,n", [(3125, 3044, 33), (1593, 4084, 103)])
+def test_ragged_rbm_with_a_long_contraction(V, H, n):
+    import torch
+    from paper_1507_01239_amd import binding as B
+    W, a, c = gen.rbm_params(V, H, 5, 0)
+    V0 = np.random.default_rng(6).random((n, V), dtype=np.float32)
+    state = dict(W=W, a=a, c=c, MW=np.zeros_like(W), Ma=np.zeros_like(a), Mc=np.zeros_like(c))
+    _one_step(V, H, n, 0, 0, 0.05, 0.5, 11, 0, 0, state, V0)
+    need = B.rbm_workspace_bytes(V, H, n)
+    out, ws = torch.empty(n, H, device="cuda"), workspace(need)
+    B.rbm_hidden_prob(V, H, dev(W), dev(c), dev(V0), n, out, ws, workspace_bytes=need)
+    torch.cuda.synchronize()
+    assert rel_err(host(out), 1 / (1 + np.exp(-(V0.astype(np.float64) @ W.astype(np.float64).T + c)))) < 2e-6
+
+
 def test_zero_lr_and_momentum_leave_parameters_bit_identical():
     import torch
     from paper_1507_01239_amd import binding as B
