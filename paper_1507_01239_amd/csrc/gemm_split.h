@@ -273,8 +273,17 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
         if constexpr (r < TM) fa[fs][pl][r] = *reinterpret_cast<const bf16x8*>(fa_base + buf * STAGE + pl * OpA::PS + r * 512);
         else fb[fs][pl][r - TM] = *reinterpret_cast<const bf16x8*>(fb_base + buf * STAGE + pl * OpB::PS + (r - TM) * 512);
     };
-    // A wavefront that is a k-group by itself needs no barrier: its LDS instructions are carried out in order.
-    auto group_barrier = [&]() { if constexpr (NT > 64) __syncthreads(); };
+    // A wavefront that is a k-group by itself needs no s_barrier: its LDS instructions are carried out in order.  The fences
+    // keep the compiler from moving an LDS access across, which another lane's data may depend on.
+    auto group_barrier = [&]() {
+        if constexpr (NT > 64) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    };
     // One k-tile t.  Behind each of its MFMAs goes a share of the other work, which issues while the matrix pipe works:
     //   PRE: the operand reads of tile t+1 (LDS buffer (t+1) & 1) and the split of tile t+2 into LDS buffer t & 1, whose
     //        reads every wavefront had finished before the last barrier;
