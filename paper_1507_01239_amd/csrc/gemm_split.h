@@ -9,11 +9,13 @@
 // MFMAs, 149.  On fewer tiles than fill the chip: LDS, which takes the three parts at 64 bytes per cycle (ds_write of any
 // width; reads run at 240), beside the reads and the matrix pipe: 1024 x 2048 x 2048 60 us, was 66 - 80.
 //
-// What it computes.  x = h + m + l with h = bf16(x) rounded to nearest, m = the next 8 bits of x - h (truncated),
-// l = the rest; the split is exact for |x| >= 2^-110 and off by at most 2^-133 below that.  Products of bf16 values are
-// exact in fp32, and the matrix cores add eight of them to the accumulator with one rounding to nearest (measured;
-// denormals are kept).  h h', h m', m h', m m', h l', l h' are accumulated; m l', l m' and l l' are left out: together at
-// most 2^-24 of |x x'|, in the mean 2^-27 with either sign, below the rounding of a single fp32 product (2^-25 in the mean).
+// What it computes.  x = h + m + l with h = bf16(x) and m = bf16(x - h), rounded to nearest, and l = the rest; the split is
+// exact for |x| >= 2^-110 and off by at most 2^-133 below that.  Products of bf16 values are exact in fp32, and the matrix
+// cores add eight of them to the accumulator with one rounding to nearest (measured; denormals are kept).  h h', h m', m h',
+// m m', h l', l h' are accumulated; m l', l m' and l l' are left out: for |x| in [1, 2), |m| <= 2^-8 and |l| <= 2^-17, so
+// together at most 2^-24 of |x x'| (1 + 2^-9), the largest rounding of an fp32 product, and 2^-28.2 in the mean with either
+// sign (2^-25.5 for the rounding of an fp32 product).  A truncated m would leave |l| up to 2^-16 and twice to three times
+// that: 2^-23 at most, 2^-26.7 in the mean.
 // Against float64 the results are as close as those of the fp32 matrix cores (12 roundings of the accumulator per 16
 // contraction steps here, 16 there).
 //
@@ -43,17 +45,18 @@ __device__ __forceinline__ GlobalF g_off(GlobalF ubase, uint32_t off) {      // 
 template <int STEP>
 __device__ __forceinline__ void split_step(float& x0, float& x1, uint32_t& h, uint32_t& m, uint32_t& l, const uint32_t kHigh) {
     constexpr uint32_t kPackHigh = 0x07060302u;
+    // (an instruction of its own: from the C conversions the compiler makes a second one for the low half)
+    auto round_pair = [&](uint32_t& d) { asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(x0), "v"(x1)); };
     if constexpr (STEP == 0) {
-        // (as an instruction of its own: from the C conversions the compiler makes a second one for the low half)
-        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(h) : "v"(x0), "v"(x1));
+        round_pair(h);
         x0 -= __builtin_bit_cast(float, h << 16);
         l = h & kHigh;
     } else if constexpr (STEP == 1) {
         x1 -= __builtin_bit_cast(float, l);
-        m = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x1), __builtin_bit_cast(uint32_t, x0), kPackHigh);
-        x0 -= __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x0) & kHigh);
+        round_pair(m);
+        x0 -= __builtin_bit_cast(float, m << 16);
     } else {
-        x1 -= __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x1) & kHigh);
+        x1 -= __builtin_bit_cast(float, m & kHigh);
         l = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x1), __builtin_bit_cast(uint32_t, x0), kPackHigh);
     }
 }

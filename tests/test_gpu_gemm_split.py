@@ -34,6 +34,25 @@ def test_epilogues(epi, cfg):
 
 
 @pytest.mark.parametrize("cfg", SPLIT_CFGS)
+def test_single_products_where_the_second_part_rounds_up(cfg):
+    # One term per sum, of factors 1 + 2^-8 - j 2^-23: h = 1, m = 2^-8, l = -j 2^-23, and the six products that are kept add
+    # up without rounding.  What is left out is (i + j) 2^-31 + i j 2^-46, below 2^-24 for i, j <= 60; with a second part cut
+    # off instead of rounded it would be 2^-23.
+    import torch
+    from paper_1507_01239_amd import binding as B
+    m, n, k = 60, 60, 16
+    x = (1 + 2.0 ** -8 - np.arange(1, 61) * 2.0 ** -23).astype(np.float32)
+    A = np.zeros((m, k), np.float32)
+    A[np.arange(m), np.arange(m) % k] = x
+    c = torch.zeros(m, n, device="cuda")
+    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, cfg, 1))
+    B.mavg_gemm(dev(A), k, 1, dev(np.repeat(x[:, None], k, 1)), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, cfg, 1, ws)
+    torch.cuda.synchronize()
+    ref = x[:, None].astype(np.float64) * x[None]
+    assert (np.abs(host(c) - ref) <= 2.0 ** -24 * ref).all()
+
+
+@pytest.mark.parametrize("cfg", SPLIT_CFGS)
 def test_values_that_do_not_survive_the_split(cfg):
     # infinities, NaNs and floats that round to infinity in bf16 give what float32 arithmetic gives; rows and columns
     # without them are untouched
