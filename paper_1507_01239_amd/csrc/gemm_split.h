@@ -22,7 +22,9 @@
 // Infinities, NaNs and values that round to infinity in bf16 (above 3.39e38) do not survive the split (inf - inf, and
 // inf * 0 where a part of the other factor is zero).  They always leave a NaN or an infinity in the accumulators they
 // reach, so a wavefront that finds a non-finite accumulator recomputes that 32x32 block with the fp32 matrix cores:
-// what is returned is then what fp32 arithmetic gives.
+// what is returned is then what fp32 arithmetic gives.  Microseconds for ordinary values, one infinity and nothing but NaNs:
+// 1024 x 2048 x 2048 60 / 94 / 174 (fp32 kernels alone 68; with single loads in the recomputation 60 / 151 / 488),
+// 4096 x 8000 x 2048 712 / 816 / 2385 (fp32 920; with single loads 758 / 991 / 7654).
 #pragma once
 #include "gemm_device.h"
 
@@ -71,23 +73,52 @@ __device__ __forceinline__ bool block_not_finite(const floatx16& a) {
 constexpr int kSplitBK = 16;      // contraction steps per k-tile: one MFMA
 
 // The 32x32 block at (mb, nb) over contraction steps [kbeg, kend), of which those of every `stride`-th k-tile, on the fp32
-// matrix cores, operands element by element.
+// matrix cores.  Lane half `lrow` multiplies steps 8 lrow .. 8 lrow + 7 of a k-tile, which it reads from a k-contiguous
+// operand with two 16-byte loads (single floats touch four times the cache lines, and those are what bounds this); a k-tile
+// is on its way while the one before is multiplied.
 template <bool AKC, bool BKC>
 __device__ __forceinline__ floatx16 block_fp32(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N,
-                                                          int mb, int nb, int kbeg, int kend, int stride) {
-    const int lane = threadIdx.x & 63, lrow = lane >> 5, lcol = lane & 31;
-    const int m = min(mb + lcol, M - 1), n = min(nb + lcol, N - 1);
-    floatx16 acc = floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int kt = kbeg; kt < kend; kt += stride * kSplitBK)
-#pragma unroll 1
-        for (int k0 = kt; k0 < kt + kSplitBK && k0 < kend; k0 += 2) {
-            const int k = k0 + lrow;
-            const bool ok = k < kend;
-            const float a = ok ? (AKC ? A[(int64_t)m * lda + k] : A[(int64_t)k * lda + m]) : 0.f;
-            const float b = ok ? (BKC ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n]) : 0.f;
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+                                               int mb, int nb, int kbeg, int kend, int stride) {
+    const int lane = threadIdx.x & 63, lrow = lane >> 5, lcol = lane & 31, hop = stride * kSplitBK;
+    const GlobalF ra = (GlobalF)(A + (int64_t)min(mb + lcol, M - 1) * (AKC ? lda : 1));      // this lane's row (or column)
+    const GlobalF rb = (GlobalF)(B + (int64_t)min(nb + lcol, N - 1) * (BKC ? ldb : 1));
+    auto fetch = [&](GlobalF p, int64_t ld, auto kcc, int kt, float (&x)[8]) {
+        constexpr bool KC = decltype(kcc)::value;
+        const int k = kt + 8 * lrow;
+        if (kt + kSplitBK <= kend) {      // (uniform)
+            if constexpr (KC) {
+                const floatx4u u = *(GlobalF4)(p + k), v = *(GlobalF4)(p + k + 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { x[i] = u[i]; x[4 + i] = v[i]; }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[i] = p[(int64_t)(k + i) * ld];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                x[i] = 0.f;
+                if (k + i < kend) x[i] = p[KC ? (int64_t)(k + i) : (int64_t)(k + i) * ld];
+            }
         }
+    };
+    floatx16 acc = floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float a[8], b[8], an[8] = {}, bn[8] = {};
+    if (kbeg < kend) {
+        fetch(ra, lda, std::integral_constant<bool, AKC>{}, kbeg, a);
+        fetch(rb, ldb, std::integral_constant<bool, BKC>{}, kbeg, b);
+    }
+#pragma unroll 1
+    for (int kt = kbeg; kt < kend; kt += hop) {
+        if (kt + hop < kend) {
+            fetch(ra, lda, std::integral_constant<bool, AKC>{}, kt + hop, an);
+            fetch(rb, ldb, std::integral_constant<bool, BKC>{}, kt + hop, bn);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { a[i] = an[i]; b[i] = bn[i]; }
+    }
     return acc;
 }
 
