@@ -25,6 +25,12 @@
 // what is returned is then what fp32 arithmetic gives.  Microseconds for ordinary values, one infinity and nothing but NaNs:
 // 1024 x 2048 x 2048 60 / 94 / 174 (fp32 kernels alone 68; with single loads in the recomputation 60 / 151 / 488),
 // 4096 x 8000 x 2048 712 / 816 / 2385 (fp32 920; with single loads 758 / 991 / 7654).
+//
+// Small values.  An element below 2^-110 loses up to 2^-133 in the split, so a sum over terms x x' may be off by
+// 2^-133 times the sum of the other factors' magnitudes.  Where that could matter the sum itself is small: a block with an
+// accumulator below 2^-80 other than zero, or with nothing but zeros, is recomputed as well.  What is left is 2^-53 of a
+// result times the sum of the other factors' magnitudes: below 2^-24 unless those come to 2^29.  (Scaling every element by
+// 2^16 before its split would keep them all, at 6 - 9 % of every product; this takes 0 - 1 %.)
 #pragma once
 #include "gemm_device.h"
 
@@ -63,11 +69,25 @@ __device__ __forceinline__ void split_step(float& x0, float& x1, uint32_t& h, ui
     }
 }
 
-// Is any accumulator of the wavefront's 32x32 block infinite or NaN?  (x * 0 is NaN exactly then.)
-__device__ __forceinline__ bool block_not_finite(const floatx16& a) {
-    float t = 0.f;
-    static_for<16>([&](auto vc) { t = __builtin_fmaf(a[decltype(vc)::value], 0.f, t); });
-    return __any(!(t == 0.f));
+// Does the wavefront's 32x32 block hold an infinity or a NaN (x * 0 is NaN exactly then), a value below 2^-80 other than zero,
+// or nothing but zeros?  (First the least magnitude with the zeros among it: one and a half instructions per element.)
+__device__ __forceinline__ bool block_suspect(const floatx16& a) {
+    constexpr float kTiny = 0x1p-80f;
+    float t = 0.f, least = 1.f;
+    static_for<16>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        t = __builtin_fmaf(a[v], 0.f, t);
+        least = fminf(least, fabsf(a[v]));
+    });
+    asm("" : "+v"(least));      // (a minimum, not a comparison per element)
+    if (!__any(!(t == 0.f) || least < kTiny)) return false;
+    bool odd = !(t == 0.f), zeros = true;
+    static_for<16>([&](auto vc) {
+        const float x = fabsf(a[decltype(vc)::value]);
+        odd |= x < kTiny && x != 0.f;
+        zeros &= x == 0.f;
+    });
+    return __any(odd) || __all(zeros);
 }
 
 constexpr int kSplitBK = 16;      // contraction steps per k-tile: one MFMA
@@ -383,7 +403,7 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
 
     static_for<TM * TN>([&](auto tc) {
         constexpr int i = decltype(tc)::value / TN, j = decltype(tc)::value % TN;
-        if (block_not_finite(acc[i][j]))
+        if (block_suspect(acc[i][j]))
             acc[i][j] = block_fp32<AKC, BKC>(A, p.lda, B, p.ldb, p.M, p.N, m0 + wm + 32 * i, n0 + wn + 32 * j, first, kend, KG);
     });
 

@@ -130,19 +130,22 @@ def test_a_product_of_nothing_but_nans_takes_no_multiple_of_its_time():
     assert best_ms(torch.full((m, k), float("nan"), device="cuda")) < 5 * ordinary
 
 
-@pytest.mark.parametrize("scale", [1e-30, 1e-36])
-def test_small_magnitudes(scale):
-    # parts below 2^-126 are kept as denormals down to 2^-133: at 1e-36 that is 13 bits below the smallest element here
+# Elements whose parts bf16 cannot hold (below 2^-110 the third one, below 2^-134 all three): float32 products all the same.
+# The second scale keeps the results above the float32 denormals, whose rounding the tolerance does not cover.
+@pytest.mark.parametrize("scale,other", [(1e-30, 1.0), (1e-34, 1.0), (1e-36, 1.0), (1e-38, 1e6), (1e-41, 1e10)])
+@pytest.mark.parametrize("cfg", SPLIT_CFGS)
+def test_small_magnitudes(cfg, scale, other):
     rng = np.random.default_rng(8)
     m, n, k = 70, 90, 64
-    A, Bt = (rng.uniform(1, 2, (m, k)) * scale).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    A = (rng.uniform(1, 2, (m, k)) * scale).astype(np.float32)
+    Bt = (rng.standard_normal((n, k)) * other).astype(np.float32)
     import torch
     from paper_1507_01239_amd import binding as B
     c = torch.zeros(m, n, device="cuda")
-    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, 3, 1))
-    B.mavg_gemm(dev(A), k, 1, dev(Bt), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, 3, 1, ws)
+    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, cfg, 1))
+    B.mavg_gemm(dev(A), k, 1, dev(Bt), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, cfg, 1, ws)
     torch.cuda.synchronize()
-    assert rel_err(host(c), A.astype(np.float64) @ Bt.astype(np.float64).T) < (2e-6 if scale == 1e-30 else 2.0 ** -13)
+    assert rel_err(host(c), A.astype(np.float64) @ Bt.astype(np.float64).T) < 2e-6
 
 
 @pytest.mark.parametrize("aligned", [True, False])
