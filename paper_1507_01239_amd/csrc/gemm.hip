@@ -10,7 +10,7 @@
 //  - gemm_dma_kernel / gemm_dma_kg_kernel: v_mfma_f32_32x32x2_f32 on operands that go from global memory straight into
 //    an LDS ring (global_load_lds_dwordx4): problems that do not fill the chip with large tiles, 16-byte aligned rows;
 //  - gemm_kernel: register-staged 64x64 tiles of the same MFMA with guarded loads, for what is left (contractions of fewer
-//    than 16 steps, fused row sums of ragged operands).
+//    than 32 steps, fused row sums of ragged operands).
 #include "gemm_device.h"
 #include "gemm_launchers.h"
 
@@ -184,6 +184,13 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
     return c;
 }
 
+// The automatic plans take the split-operand kernels from this many contraction steps on: where they sum shorter ones their
+// errors are larger than those of the fp32 MFMAs.  Relative errors against float64, split / fp32, of terms of either sign and
+// of positive terms: 16 steps 83 / 74 and 85 / 62 (e-9), 24 steps 80 / 90 and 67 / 74, 32 steps 87 / 103 and 68 / 84.
+// The grouped kernel has no k-groups, whose separate sums round less: 32 steps 104 / 103 and 100 / 84, 64 steps 136 / 145 and
+// 120 / 115, 80 steps 148 / 161 and 134 / 138.
+constexpr int kSplitMinK = 32, kSplitGroupedMinK = 80;
+
 // Which kernel family: the cheapest by plan_cost among the fp32 MFMA plan and the split-operand kernels, unsplit or with 2,
 // 4 or 8 contraction splits of at least 256 steps.  Measured (us; fp32 MFMA kernels against the split-operand kernel taken):
 //   4096 x 8000 x 2048: 976 / 753 (128x128)       1999 x 2048 x 2048: 138 / 99 (128x128)     1024 x 8000 x 2048: 261 / 191 (128x128)
@@ -199,7 +206,7 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
 GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged, int64_t ws_floats) {
     if (force_cfg == CFG_S128_ALIAS) force_cfg = CFG_S128;
     GemmPlan best = gemm_plan_fp32(M, N, K, batch, force_cfg, force_splits);
-    if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < 16) return best;
+    if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < kSplitMinK) return best;
     if (ragged && best.cfg != CFG_64) best = gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits);
     double least = plan_cost(best, M, N, K, batch, ragged) * 0.97 - 0.5;
     const int sums = best.splits * (cfg_kg(best.cfg) ? 4 : 1);
@@ -374,14 +381,14 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
     // rows, made the step 88 us, 73 with 64x64 tiles of fp32 MFMAs) and the contraction is long enough for its faster
     // multiplies to matter next to that: the seven weight updates of
     // 440-6x2048-8000 take 116 us either way at minibatch 128 (memory), 134 against 145 us at 192, 152 against 177 at 256,
-    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from half a tile per compute unit and 16 steps on (the alternative
+    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from half a tile per compute unit and kSplitGroupedMinK steps on (the alternative
     // there is the register-staged kernel, 28 against 21 us at 3003 x 1021 x 200).
     int64_t tiles128 = 0;
     for (int i = 0; i < count; ++i) tiles128 += tiles_of(CFG_S128, d[i].M > 0 ? d[i].M : 0, d[i].N > 0 ? d[i].N : 0, d[i].batch);
     auto family = [&](const GemmDesc& di, const GemmKParams& q) {
         const bool dma = dma_eligible(di, q);
         const bool split = split_eligible(di) && !di.a_kc && !di.b_kc && di.epi.side_sum_src == nullptr &&
-                           tiles128 >= (!dma ? kNumCU / 2 : di.K >= 512 ? 2 * kNumCU : 4 * kNumCU) && di.K >= (dma ? 192 : 16);
+                           tiles128 >= (!dma ? kNumCU / 2 : di.K >= 512 ? 2 * kNumCU : 4 * kNumCU) && di.K >= (dma ? 192 : kSplitGroupedMinK);
         return split ? 0 : dma ? 1 : 2;
     };
     for (int pass = 0; pass < 3; ++pass) {

@@ -148,6 +148,32 @@ def test_small_magnitudes(cfg, scale, other):
     assert rel_err(host(c), A.astype(np.float64) @ Bt.astype(np.float64).T) < 2e-6
 
 
+@pytest.mark.parametrize("k", [16, 24, 31, 32, 48, 79, 80, 96])
+def test_short_contractions_are_no_less_exact_than_with_fp32_products(k):
+    # positive terms, ragged rows, a problem large enough for the split-operand kernels: their sums of one k-tile are off by up
+    # to 1.4 times as much as those of the float32 kernel (cfg 1), the grouped launch's up to 1.4 times at 16 and 1.2 times at
+    # 32 steps, so the float32 kernels run there (2 %: the order of their sums)
+    import torch
+    from paper_1507_01239_amd import binding as B
+    rng = np.random.default_rng(90 + k)
+    m, n = 1003, 2001
+    A, Bt = rng.random((m, k), dtype=np.float32), rng.random((n, k), dtype=np.float32)
+    ref = A.astype(np.float64) @ Bt.astype(np.float64).T
+    err = []
+    for cfg in (-1, 1):
+        c = torch.zeros(m, n, device="cuda")
+        ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, cfg, 0))
+        B.mavg_gemm(dev(A), k, 1, dev(Bt), k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, cfg, 0, ws)
+        torch.cuda.synchronize()
+        err.append(rel_err(host(c), ref))
+    # the same product as a grouped update of zeros
+    c = torch.zeros(m, n, device="cuda")
+    B.mavg_gemm_grouped([B.gemm_problem(dev(A.T.copy()), m, dev(Bt.T.copy()), n, c, n, m, n, k, epi=4, alpha=1.0, beta=1.0)], 0, 0)
+    torch.cuda.synchronize()
+    err.append(rel_err(host(c), ref))
+    assert err[0] <= 1.02 * err[1] and err[2] <= 1.02 * err[1], err
+
+
 @pytest.mark.parametrize("aligned", [True, False])
 @pytest.mark.parametrize("n", [16, 200, 263])
 def test_grouped_weight_updates(n, aligned):
