@@ -148,6 +148,27 @@ def test_small_magnitudes(cfg, scale, other):
     assert rel_err(host(c), A.astype(np.float64) @ Bt.astype(np.float64).T) < 2e-6
 
 
+# Few rows over a long contraction, few columns, about one tile per compute unit: where the split-operand kernels lose.
+@pytest.mark.parametrize("m,n,k,a_kc,b_kc", [(64, 2048, 8000, 1, 0), (96, 624, 6064, 0, 0), (3329, 175, 1036, 1, 1), (32, 3200, 1728, 1, 0)])
+def test_automatic_plans_are_not_slower_than_the_fp32_kernels(m, n, k, a_kc, b_kc):
+    # up to 1.3 times the time of cfg 0 when they went to a split-operand kernel; 1.1 leaves room for the clock
+    import torch
+    from paper_1507_01239_amd import binding as B
+    a, b, c = torch.rand(m * k, device="cuda"), torch.randn(n * k, device="cuda"), torch.empty(m, n, device="cuda")
+    ws = workspace(max(B.mavg_gemm_workspace_bytes(m, n, k, cfg, 0) for cfg in (-1, 0)))
+    best = {-1: 1e9, 0: 1e9}
+    for rep in range(12):
+        for cfg in best:
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(20):
+                B.mavg_gemm(a, k if a_kc else m, a_kc, b, k if b_kc else n, b_kc, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, cfg, 0, ws)
+            e1.record()
+            torch.cuda.synchronize()
+            best[cfg] = min(best[cfg], e0.elapsed_time(e1))
+    assert best[-1] < 1.1 * best[0], best
+
+
 @pytest.mark.parametrize("k", [16, 24, 31, 32, 48, 79, 80, 96])
 def test_short_contractions_are_no_less_exact_than_with_fp32_products(k):
     # positive terms, ragged rows, a problem large enough for the split-operand kernels: their sums of one k-tile are off by up
