@@ -283,9 +283,10 @@ int32_t ngsgd_precondition(void* state, int32_t dim, int32_t rank,
 /*
  * C(m,n) = epilogue( sum_{kk<k} A(m,kk) B(kk,n) ), float32 operands, float32 accumulation.  Either float32 MFMAs, or every
  * operand element split into three bf16 parts (exactly, from 2^-110 up) and the six products of parts that float32 can tell
- * apart accumulated by bf16 MFMAs.  32x32 blocks in which a sum is infinite, NaN or below 2^-80, or in which all are zero, are
- * computed by float32 MFMAs with both, so that smaller elements count in full too; beside larger sums, from other factors
- * that come to more than 2^29, an element below 2^-110 may be off by 2^-133.
+ * apart accumulated by bf16 MFMAs.  32x32 blocks in which a sum is infinite, NaN or below 2^-80 without being zero are
+ * computed by float32 MFMAs with both, so that smaller elements count in full too.  What is left: beside larger sums, from
+ * other factors that come to more than 2^29, an element below 2^-110 may be off by 2^-133, and products of elements that are
+ * all below 2^-134 may come out as zero.
  *   a_kc != 0: A(m,kk) = a[m*lda + kk], else a[kk*lda + m];   b_kc != 0: B(kk,n) = b[n*ldb + kk], else b[kk*ldb + n]
  *   C(m,n) = c[m*ldc + n]
  *   epi: 0  C = v            1  C = v + bias[n]          2  C = alpha*sigmoid(v + bias[n])
