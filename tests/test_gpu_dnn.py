@@ -403,3 +403,34 @@ def test_networks_of_narrow_layers(dims, n, k, hidden, mean):
         check_acts(g.activations(r), acts, 1e-5, f"replica {r}")
         check_tensors(g.params()[r], ref, dims, 1e-5, f"replica {r}")
         assert abs(host(g.loss)[r] - loss) <= 1e-5 * abs(loss) + 1e-6
+
+
+# Inputs and labels shared by all replicas (strides of 0), and labels that name no class: such a row has no target and no
+# loss.  33 and 64 rows: the one-launch backward pass, 65: the general one.
+@pytest.mark.parametrize("n", [33, 64, 65])
+def test_networks_of_narrow_layers_with_shared_inputs_and_labels_outside_the_classes(n, monkeypatch):
+    import torch
+    from paper_1507_01239_amd import binding as B
+    dims, K, seed = [17, 15, 64, 33], 3, 61
+    theta0 = gen.init_theta(dims, seed, 0.3)
+    X = gen.features_iid(n, dims[0], seed, 0, 0)
+    y = gen.labels_uniform(n, dims[-1], seed, 0, 0).astype(np.int32)
+    y[[0, 7, n - 1]] = [-1, dims[-1], 2 ** 31 - 1]
+    known = (y >= 0) & (y < dims[-1])
+
+    def output_delta(p, labels, mean_grad):
+        d = p.copy()
+        d[np.flatnonzero(known), labels[known]] -= 1.0
+        return d / p.shape[0] if mean_grad else d
+    monkeypatch.setattr(dnn, "output_delta", output_delta)
+    monkeypatch.setattr(dnn, "cross_entropy_sum", lambda p, labels: float(-np.log(p[np.flatnonzero(known), labels[known]]).sum()))
+    g = Gpu(dims, K, n, theta0)
+    x_d, y_d = dev(X), dev(y)
+    B.dnn_forward(g.shape, K, g.theta, g.stride, x_d, 0, n, g.acts, g.act_stride, g.ws)
+    B.dnn_backward_update(g.shape, K, g.theta, g.stride, x_d, 0, y_d, 0, n, g.acts, g.act_stride, 0.5, B.MEAN_GRAD, g.loss, g.ws)
+    ref, loss, acts = dnn.sgd_step(theta0, dims, X, y, 0.5)
+    for r in range(K):
+        check_acts(g.activations(r), acts, 1e-5, f"replica {r}")
+        check_tensors(g.params()[r], ref, dims, 1e-5, f"replica {r}")
+        assert abs(host(g.loss)[r] - loss) <= 1e-5 * abs(loss)
+    torch.cuda.synchronize()
