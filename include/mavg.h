@@ -312,8 +312,9 @@ int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const float* b, int
 
 /*
  * Several independent contractions C_i = epilogue(A_i B_i) of the same operand layouts in ONE launch (unsplit
- * contraction; problems that need different kernels go into up to three launches): the form in which dnn_backward_update issues the weight gradients and SGD updates of all
- * layers of a step (eq. 3).  Exported for tests and for timing that launch by itself.
+ * contraction; problems that need different kernels go into up to three launches): the form in which
+ * dnn_backward_update issues the weight gradients and SGD updates of all layers of a step (eq. 3).  Exported for tests
+ * and for timing that launch by itself.
  *   problems  host array of `count` records (1 <= count <= 8), read during the call; all pointers inside device
  *   a_kc, b_kc  as in mavg_gemm, shared by all problems
  *   epi, alpha, beta, bias, aux, ldaux per problem as in mavg_gemm
@@ -333,6 +334,12 @@ typedef struct {
     int32_t a_pad4, b_pad4;
 } mavg_gemm_problem;
 int32_t mavg_gemm_grouped(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc, void* stream);
+/*
+ * Which kernel that call runs problem `which` with: 0 = split-operand (bf16 parts), 1 = direct-to-LDS, 2 = register-staged
+ * float32 MFMAs; or an error as above (MAVG_E_DIM also for `which` outside 0 .. count - 1).  Host only; for tests.
+ */
+int32_t mavg_gemm_grouped_kernel(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc,
+                                 int32_t which);
 
 #ifdef __cplusplus
 }

@@ -88,6 +88,7 @@ _SIG = {
                          _i32, _i32, _p, _i64, _p]),
     "mavg_gemm_workspace_bytes": (_i64, [_i32, _i32, _i32, _i32, _i32]),
     "mavg_gemm_grouped": (_i32, [_p, _i32, _i32, _i32, _p]),
+    "mavg_gemm_grouped_kernel": (_i32, [_p, _i32, _i32, _i32, _i32]),
 }
 EXPORTS = tuple(_SIG)
 for _name, (_res, _args) in _SIG.items():
@@ -262,3 +263,9 @@ def mavg_gemm_grouped(problems, a_kc, b_kc, stream=None):
     arr = (GemmProblem * len(problems))(*problems)
     return _check(lib.mavg_gemm_grouped(C.cast(arr, C.c_void_p), len(problems), int(a_kc), int(b_kc), _stream(stream)),
                   "mavg_gemm_grouped")
+
+
+def mavg_gemm_grouped_kernel(problems, a_kc, b_kc, which) -> int:
+    arr = (GemmProblem * len(problems))(*problems)
+    return _check(lib.mavg_gemm_grouped_kernel(C.cast(arr, C.c_void_p), len(problems), int(a_kc), int(b_kc), which),
+                  "mavg_gemm_grouped_kernel")

@@ -47,7 +47,7 @@ struct Epilogue {
     //   alpha_dev0[b] * alpha_dev1[b] of alpha apply to rowsum_alpha as well
     const float* rowsum_w = nullptr; int64_t rowsum_w_bstride = 0;
     // optional, a short vector summed on the side of the launch (forces an unsplit contraction, not taken by the
-    // in-workgroup-split kernels): side_sum_dst[0] = sum_{i < side_sum_n} side_sum_src[i], by workgroup 0 of batch
+    // in-workgroup-split and the split-operand kernels): side_sum_dst[0] = sum_{i < side_sum_n} side_sum_src[i], by workgroup 0 of batch
     // element 0 behind its own tile, in the order of a 256-thread fixed-order segment sum (thread-strided partial
     // sums, then the four wavefronts' sums pairwise) - e.g. the per-block squared errors a preceding launch left
     const float* side_sum_src = nullptr; float* side_sum_dst = nullptr; int side_sum_n = 0;
@@ -103,10 +103,12 @@ int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch);
 // with less than gemm_ws_floats() the plan makes do with fewer splits.
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream);
 
-// Several independent GEMMs of the same operand layouts and batch count in ONE launch (64x64 tiles, unsplit
+// Several independent GEMMs of the same operand layouts and batch count in one launch per kernel that they need (unsplit
 // contraction, no scratch).  `thin`: products with few output columns and a long contraction, both operands
 // k-contiguous (32x32 tiles, the contraction split four ways inside each workgroup).  Returns hipError_t as int.
 constexpr int kThinMaxProblems = 40;    // thin problems one launch takes (more are launched in further launches)
 int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool thin = false);
+// which of its kernels takes problem `which` (not thin): 0 = split-operand, 1 = direct-to-LDS, 2 = register-staged
+int gemm_grouped_kernel(const GemmDesc* d, int count, int which);
 
 }  // namespace mavg

@@ -378,25 +378,37 @@ static int gemm_launch_grouped_thin(const GemmDesc* d, int count, hipStream_t st
     return flush();
 }
 
+static int64_t grouped_tiles128(const GemmDesc* d, int count) {
+    int64_t t = 0;
+    for (int i = 0; i < count; ++i) t += tiles_of(CFG_S128, d[i].M > 0 ? d[i].M : 0, d[i].N > 0 ? d[i].N : 0, d[i].batch);
+    return t;
+}
+
+// Which kernel of the grouped launch takes problem d (q: its parameters for 64x64 tiles) among problems of tiles128 tiles in
+// all: 0 = split-operand (128x128 tiles; m- and n-contiguous operands), 1 = direct-to-LDS, 2 = register-staged.
+// The split-operand kernel takes it when the tiles come to at least four per compute unit, two from 512 steps on (with
+// fewer the read-modify-write of C has nothing to hide behind: 140 tiles, two replicas of 1696 x 528 and 64 x 1696 at 270 rows,
+// made the step 88 us, 73 with 64x64 tiles of fp32 MFMAs), and the contraction is long enough for its faster multiplies to
+// matter next to that: the seven weight updates of 440-6x2048-8000 take 116 us either way at minibatch 128 (memory), 134
+// against 145 us at 192, 152 against 177 at 256, 253 against 318 at 512, 473 against 616 at 1024.
+// Rows that are not 16-byte aligned: from half a tile per compute unit and kSplitGroupedMinK steps on (the alternative there
+// is the register-staged kernel, 28 against 21 us at 3003 x 1021 x 200).
+static int grouped_kernel(const GemmDesc& d, const GemmKParams& q, int64_t tiles128) {
+    const bool dma = dma_eligible(d, q);
+    const bool split = split_eligible(d) && !d.a_kc && !d.b_kc && d.epi.side_sum_src == nullptr &&
+                       tiles128 >= (!dma ? kNumCU / 2 : d.K >= 512 ? 2 * kNumCU : 4 * kNumCU) && d.K >= (dma ? 192 : kSplitGroupedMinK);
+    return split ? 0 : dma ? 1 : 2;
+}
+
+int gemm_grouped_kernel(const GemmDesc* d, int count, int which) {
+    return grouped_kernel(d[which], fill_params(d[which], gemm_plan_fp32(d[which].M, d[which].N, d[which].K, d[which].batch, CFG_64, 1), nullptr),
+                          grouped_tiles128(d, count));
+}
+
 int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool thin) {
     if (thin) return gemm_launch_grouped_thin(d, count, stream);
-    // Three passes over the problems: those for the split-operand kernel (128x128 tiles; m- and n-contiguous operands), those
-    // the direct-to-LDS kernel accepts, and the rest (register-staged kernel).
-    // The split-operand kernel takes the launch when its tiles come to at least four per compute unit, two from 512 steps on
-    // (with fewer the read-modify-write of C has nothing to hide behind: 140 tiles, two replicas of 1696 x 528 and 64 x 1696 at 270
-    // rows, made the step 88 us, 73 with 64x64 tiles of fp32 MFMAs) and the contraction is long enough for its faster
-    // multiplies to matter next to that: the seven weight updates of
-    // 440-6x2048-8000 take 116 us either way at minibatch 128 (memory), 134 against 145 us at 192, 152 against 177 at 256,
-    // 253 against 318 at 512, 473 against 616 at 1024.  Rows that are not 16-byte aligned: from half a tile per compute unit and kSplitGroupedMinK steps on (the alternative
-    // there is the register-staged kernel, 28 against 21 us at 3003 x 1021 x 200).
-    int64_t tiles128 = 0;
-    for (int i = 0; i < count; ++i) tiles128 += tiles_of(CFG_S128, d[i].M > 0 ? d[i].M : 0, d[i].N > 0 ? d[i].N : 0, d[i].batch);
-    auto family = [&](const GemmDesc& di, const GemmKParams& q) {
-        const bool dma = dma_eligible(di, q);
-        const bool split = split_eligible(di) && !di.a_kc && !di.b_kc && di.epi.side_sum_src == nullptr &&
-                           tiles128 >= (!dma ? kNumCU / 2 : di.K >= 512 ? 2 * kNumCU : 4 * kNumCU) && di.K >= (dma ? 192 : kSplitGroupedMinK);
-        return split ? 0 : dma ? 1 : 2;
-    };
+    // Three passes over the problems, one for each kernel.
+    const int64_t tiles128 = grouped_tiles128(d, count);
     for (int pass = 0; pass < 3; ++pass) {
         GemmGroupParams gp;
         gp.ngroups = 0;
@@ -421,7 +433,7 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (di.epi.rowsum_dst != nullptr && di.a_kc) return note_hip_error(hipErrorInvalidValue);
             // unsplit, 64x64 tiles (128x128 for the split-operand kernel)
             GemmKParams q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_64, 1), nullptr);
-            if (family(di, q) != pass) continue;
+            if (grouped_kernel(di, q, tiles128) != pass) continue;
             if (pass == 0) q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_S128, 1), nullptr);
             a_kc = di.a_kc; b_kc = di.b_kc; batch = di.batch;
             gp.g[gp.ngroups] = q;
@@ -478,10 +490,10 @@ extern "C" int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const fl
     return gemm_launch(g, ws, need, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
 }
 
-extern "C" int32_t mavg_gemm_grouped(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, void* stream) {
+// Checks the problems of mavg_gemm_grouped and writes their descriptions (as many as kMaxGroups).
+static int32_t grouped_descs(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, GemmDesc* g) {
     if (!pr) return MAVG_E_NULL;
     if (count < 1 || count > kMaxGroups) return MAVG_E_DIM;
-    GemmDesc g[kMaxGroups];
     for (int i = 0; i < count; ++i) {
         const mavg_gemm_problem& q = pr[i];
         if (!q.a || !q.b || !q.c) return MAVG_E_NULL;
@@ -501,5 +513,20 @@ extern "C" int32_t mavg_gemm_grouped(const mavg_gemm_problem* pr, int32_t count,
         d.epi.kind = q.epi; d.epi.bias = q.bias; d.epi.aux = q.aux; d.epi.ldaux = q.ldaux; d.epi.alpha = q.alpha; d.epi.beta = q.beta;
         d.epi.rowsum_dst = q.rowsum_dst; d.epi.rowsum_alpha = q.rowsum_alpha; d.epi.rowsum_beta = q.rowsum_beta;
     }
+    return MAVG_OK;
+}
+
+extern "C" int32_t mavg_gemm_grouped(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, void* stream) {
+    GemmDesc g[kMaxGroups];
+    const int32_t rc = grouped_descs(pr, count, a_kc, b_kc, g);
+    if (rc) return rc;
     return gemm_launch_grouped(g, count, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
+}
+
+extern "C" int32_t mavg_gemm_grouped_kernel(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, int32_t which) {
+    GemmDesc g[kMaxGroups];
+    const int32_t rc = grouped_descs(pr, count, a_kc, b_kc, g);
+    if (rc) return rc;
+    if (which < 0 || which >= count) return MAVG_E_DIM;
+    return gemm_grouped_kernel(g, count, which);
 }

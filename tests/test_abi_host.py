@@ -136,6 +136,9 @@ def test_rbm_and_gemm_validation():
     assert gg([pr(lda=4)]) == B.E_ALIGN
     assert gg([pr(epi=7)]) == B.E_FLAG
     assert gg([pr(epi=1)]) == B.E_NULL                   # bias epilogue without a bias
+    assert B.mavg_gemm_grouped_kernel([pr()], 1, 1, 0) == 1
+    assert _rc(B.mavg_gemm_grouped_kernel, [pr()], 1, 1, 1) == B.E_DIM
+    assert _rc(B.mavg_gemm_grouped_kernel, [pr(a=None)], 1, 1, 0) == B.E_NULL
 
 
 @pytest.mark.skipif(torch.cuda.is_available(), reason="calls the library with addresses that are never dereferenced: only where nothing can be launched")

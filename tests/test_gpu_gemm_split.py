@@ -195,16 +195,24 @@ def test_short_contractions_are_no_less_exact_than_with_fp32_products(k):
     assert err[0] <= 1.02 * err[1] and err[2] <= 1.02 * err[1], err
 
 
-@pytest.mark.parametrize("aligned", [True, False])
-@pytest.mark.parametrize("n", [16, 200, 263])
-def test_grouped_weight_updates(n, aligned):
-    # enough 128x128 tiles for the split-operand kernel of the grouped launch (rows of the second operand aligned to 16
-    # bytes or not; below 192 contraction steps the aligned ones run on another kernel): ragged tile edges, row sums, and
-    # a small problem next to a large one
+# Weight updates C <- C - 0.25 D^T A with row sums, several in one launch: (rows n, shapes, kernel of each problem: 0 =
+# split-operand, 1 = direct-to-LDS, 2 = register-staged).  Ragged tile edges, whole and partial k-tiles, small problems
+# next to a large one; aligned problems need 1024 tiles of 128x128 (512 from 520 rows on), ragged ones 128, and both enough rows.
+# Tolerance: a product of n terms of random sign is off by about 2^-24 sqrt(n / 2) where every addition rounds: 1e-6 at 520.
+BIG, HALF, SMALL, RAGGED = (4100, 4100), (2052, 4100), [(130, 68), (514, 260)], [(1027, 1537), (130, 65), (514, 259)]
+
+
+@pytest.mark.parametrize("n,shapes,kernels", [
+    (16, [(1027, 1540)] + SMALL, [1, 1, 1]), (200, [BIG] + SMALL, [0, 0, 0]), (263, [BIG] + SMALL, [0, 0, 0]),
+    (263, [(1027, 1540)] + SMALL, [1, 1, 1]), (520, [HALF] + SMALL, [0, 0, 0]),
+    (16, RAGGED, [2, 2, 2]), (79, RAGGED, [2, 2, 2]), (80, RAGGED, [0, 0, 0]), (200, RAGGED, [0, 0, 0]), (263, RAGGED, [0, 0, 0]),
+    # aligned and ragged problems in one call: on one kernel, on two
+    (263, [BIG, (514, 259), (130, 68)], [0, 0, 0]), (100, [(1027, 1540), (514, 259), (130, 68)], [1, 0, 1]),
+    (30, [(514, 260), (514, 259)], [1, 2])])
+def test_grouped_weight_updates(n, shapes, kernels):
     import torch
     from paper_1507_01239_amd import binding as B
     rng = np.random.default_rng(50 + n)
-    shapes = [(1027, 1537 if not aligned else 1540), (130, 65 if not aligned else 68), (514, 259 if not aligned else 260)]
     probs, refs, outs, keep = [], [], [], []
     for (m, nc) in shapes:
         ldd = (m + 3) // 4 * 4
@@ -217,7 +225,32 @@ def test_grouped_weight_updates(n, aligned):
         refs.append((W - 0.25 * D[:, :m].astype(np.float64).T @ A.astype(np.float64), bv - 0.25 * D[:, :m].astype(np.float64).sum(axis=0)))
         outs.append((w_d, b_d))
         keep.append((d_d, a_d))
+    assert [B.mavg_gemm_grouped_kernel(probs, 0, 0, i) for i in range(len(probs))] == kernels
     B.mavg_gemm_grouped(probs, 0, 0)
     torch.cuda.synchronize()
     for (w_d, b_d), (Wr, br) in zip(outs, refs):
         assert rel_err(host(w_d), Wr) < 2e-6 and rel_err(host(b_d), br) < 2e-6
+
+
+@pytest.mark.parametrize("kind", ["infinity", "small"])
+def test_grouped_updates_with_an_infinity_and_with_small_values(kind):
+    # the grouped kernel recomputes blocks as the others do: one infinite error makes one row of the update infinite, errors
+    # of 1e-36 count in full (C is zero before)
+    import torch
+    from paper_1507_01239_amd import binding as B
+    rng = np.random.default_rng(81)
+    n, m, nc = 101, 1027, 1537
+    D, A = rng.standard_normal((n, 1028)).astype(np.float32), (1 + rng.random((n, nc))).astype(np.float32)
+    if kind == "small": D *= np.float32(1e-36)
+    else: D[n - 1, 700] = np.inf
+    c, b, d_d, a_d = torch.zeros(m, nc, device="cuda"), torch.zeros(m, device="cuda"), dev(D), dev(A)
+    prob = [B.gemm_problem(d_d, 1028, a_d, nc, c, nc, m, nc, n, epi=4, alpha=1.0, beta=1.0, rowsum_dst=b, rowsum_alpha=1.0, rowsum_beta=1.0, a_pad4=True)]
+    assert B.mavg_gemm_grouped_kernel(prob, 0, 0, 0) == 0
+    B.mavg_gemm_grouped(prob, 0, 0)
+    torch.cuda.synchronize()
+    got, sums, rows = host(c), host(b), np.arange(m)
+    if kind == "infinity":
+        assert np.isposinf(got[700]).all() and np.isposinf(sums[700])
+        rows = np.delete(rows, 700)
+    Dr = D[:, rows].astype(np.float64)
+    assert rel_err(got[rows], Dr.T @ A.astype(np.float64)) < 2e-6 and rel_err(sums[rows], Dr.sum(axis=0)) < 2e-6

@@ -297,6 +297,17 @@ def test_ng_training_step_ragged_row_tiles_rank_above_32():
     _run_small_ng_case([52, 100, 44], 1, 45, 0.05, 34, 0.2, 27, [True] * 2)
 
 
+def test_ng_training_step_on_the_split_operand_update():
+    # 263 rows (a partial k-tile) and layers wide enough for the split-operand kernel of the grouped update, whose row sums
+    # are then weighted by the preconditioned "ones" column: the biases of the second step
+    from paper_1507_01239_amd import binding as B
+    dims, n = [520, 4100, 4100], 263
+    A = 1 << 20
+    probs = [B.gemm_problem(A, dims[l], A, (dims[l - 1] + 32) // 32 * 32, A, dims[l - 1], dims[l], dims[l - 1], n, epi=4) for l in (1, 2)]
+    assert [B.mavg_gemm_grouped_kernel(probs, 0, 0, i) for i in (0, 1)] == [0, 0]
+    _run_small_ng_case(dims, 1, n, 0.05, 8, 0.2, 31, [True] * 2)
+
+
 def test_ng_training_step_many_row_blocks():
     # 1100 rows: more blocks of rows than a backward pass keeps partial products H^T X for, so Y is formed by the
     # pass of its own over X (and its last tile of rows is ragged)
