@@ -239,12 +239,12 @@ def test_grouped_updates_with_an_infinity_and_with_small_values(kind):
     import torch
     from paper_1507_01239_amd import binding as B
     rng = np.random.default_rng(81)
-    n, m, nc = 101, 1027, 1537
-    D, A = rng.standard_normal((n, 1028)).astype(np.float32), (1 + rng.random((n, nc))).astype(np.float32)
+    n, m, nc, ld = 101, 1155, 1537, 1156
+    D, A = rng.standard_normal((n, ld)).astype(np.float32), (1 + rng.random((n, nc))).astype(np.float32)
     if kind == "small": D *= np.float32(1e-36)
     else: D[n - 1, 700] = np.inf
     c, b, d_d, a_d = torch.zeros(m, nc, device="cuda"), torch.zeros(m, device="cuda"), dev(D), dev(A)
-    prob = [B.gemm_problem(d_d, 1028, a_d, nc, c, nc, m, nc, n, epi=4, alpha=1.0, beta=1.0, rowsum_dst=b, rowsum_alpha=1.0, rowsum_beta=1.0, a_pad4=True)]
+    prob = [B.gemm_problem(d_d, ld, a_d, nc, c, nc, m, nc, n, epi=4, alpha=1.0, beta=1.0, rowsum_dst=b, rowsum_alpha=1.0, rowsum_beta=1.0, a_pad4=True)]
     assert B.mavg_gemm_grouped_kernel(prob, 0, 0, 0) == 0
     B.mavg_gemm_grouped(prob, 0, 0)
     torch.cuda.synchronize()
