@@ -92,7 +92,7 @@ Workspace make_workspace(const Layout& y, int n, int k, uint32_t flags, int ng_r
 
 }  // namespace
 
-extern "C" const char* mavg_version(void) { return "mavg 0.1 (gfx950, fp32 MFMA)"; }
+extern "C" const char* mavg_version(void) { return "mavg 0.1 (gfx950, fp32 and split bf16 MFMA)"; }
 
 extern "C" int64_t mavg_param_count(const mavg_shape* shape) {
     const int rc = check_shape(shape);

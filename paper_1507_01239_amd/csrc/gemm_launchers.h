@@ -11,7 +11,7 @@ void launch_grouped_legacy(const GemmGroupParams& gp, bool a_kc, bool b_kc, dim3
 // direct-to-LDS kernels: 64x64 tiles with a ring of 4 (CFG_64) or 3 (CFG_64_RING3) stages
 void launch_dma64(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 void launch_grouped_dma(const GemmGroupParams& gp, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
-// contraction split inside the workgroup: 32x64 tiles (cfg 13) or 32x32 tiles (cfg 14); thin grouped problems
+// contraction split inside the workgroup: 32x64 tiles (CFG_KG_32x64) or 32x32 tiles (CFG_KG_32x32); thin grouped problems
 void launch_kg(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 // split-operand kernels (bf16 matrix cores, three parts per fp32 element); grouped: m- and n-contiguous operands only
 void launch_split128(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);

@@ -464,7 +464,6 @@ __device__ __forceinline__ void gemm_split_body(const GemmKParams& p, const int 
         const EpiCtx c = epi_ctx(p.epi, p.C, p.c_bstride, b);
         MAVG_EPI_DISPATCH(p.epi.kind, (write_tile<KIND, TM, TN>(acc, p.epi, c, p.ldc, p.M, p.N, m0 + wm, n0 + wn, lrow, lcol, bands)))
     }
-    if (KG == 1 && p.epi.side_sum_src != nullptr && tile == 0 && bz == 0) side_sum(p.epi, reinterpret_cast<float*>(S));
 }
 
 template <int BM, int BN, int WM, int WN, int KG, int OCC, bool AKC, bool BKC>

@@ -62,8 +62,8 @@ def test_epilogues_with_and_without_split(epi, splits):
 @pytest.mark.parametrize("cfg", [0, 1, 3, 4, 5, 6, 7, 8])
 def test_direct_to_lds_variant_and_its_register_staged_twin(a_kc, b_kc, cfg):
     # shapes the direct-to-LDS kernels accept (16-byte aligned rows, contraction a multiple of 16); cfg 0 runs the
-    # 64x64 one, cfg 1 forces the register-staged kernel on the same problem, 3 / 4 / 5 are the 128x64, 64x128
-    # and 128x128 direct-to-LDS tiles, 6 the 64x64 one with a ring of three LDS stages, 7 the 32x64 tile whose
+    # 64x64 one, cfg 1 forces the register-staged kernel on the same problem, 3 / 4 / 5 are the split-operand kernels
+    # with 64x64, 64x128 and 128x128 tiles, 6 the 64x64 one with a ring of three LDS stages, 7 the 32x64 tile whose
     # contraction is split four ways inside the workgroup (falls back to 1 below four k-tiles), 8 its 32x32 variant
     # with one wavefront per k-group and no barrier in the loop.  Ragged tile edges in m and n (clamped loads), one
     # to many k-tiles (ring start-up and tail), padded leading dimensions, splits.
