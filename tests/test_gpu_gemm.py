@@ -157,3 +157,22 @@ def test_grouped_launch_of_weight_gradient_shaped_problems():
     torch.cuda.synchronize()
     for (w_d, b_d), (Wr, br) in zip(outs, refs):
         assert rel_err(host(w_d), Wr) < 3e-6 and rel_err(host(b_d), br) < 3e-6
+
+
+def test_row_strides_beyond_what_the_fast_kernels_address():
+    # a row stride of 2^22 floats (the split-operand kernels' limit) over 256 rows (2^30 floats: beyond the direct loads'
+    # offsets too): the register-staged kernel, whose plan splits this contraction, in the scratch that the query reports
+    import torch
+    from paper_1507_01239_amd import binding as B
+    m, n, k, lda = 256, 2048, 2048, 1 << 22
+    g = torch.Generator(device="cuda").manual_seed(1)
+    A = torch.randn(m, k, device="cuda", generator=g)
+    Bt = torch.randn(n, k, device="cuda", generator=g)
+    big = torch.empty(m * lda, device="cuda")
+    big.view(m, lda)[:, :k] = A
+    c = torch.empty(m, n, device="cuda")
+    need = B.mavg_gemm_workspace_bytes(m, n, k, -1, 0)
+    B.mavg_gemm(big, lda, 1, Bt, k, 1, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, -1, 0, workspace(need), workspace_bytes=need)
+    torch.cuda.synchronize()
+    ref = host(A).astype(np.float64) @ host(Bt).astype(np.float64).T
+    assert rel_err(host(c), ref) < 3e-6
