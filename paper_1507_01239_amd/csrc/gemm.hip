@@ -175,7 +175,7 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
     case CFG_KG_32x32: c = 5 + (w < kNumCU ? 1.0 : (double)w / kNumCU) * ks * 0.0049; break;      // (two workgroups per compute unit)
     default:      // (64x64 tiles; measured at 1200 shapes: within 6 % of this, one standard deviation)
         if (ragged) c = 5 + rounds * ks * 0.0348 * (rounds == 1 ? 1.2 : 1.0);
-        else c = pl.splits > 1 ? 3 + rounds * ks * 0.0145 : 5 + rounds * ks * 0.0154;
+        else c = pl.splits > 1 ? 3 + rounds * ks * 0.0145 : 5 + rounds * ks * 0.0157;
         break;
     }
     if (pl.splits > 1) {
@@ -203,8 +203,8 @@ constexpr int kSplitMinK = 32, kSplitGroupedMinK = 80;
 //   256 x 2048 x 2048: 20.6 / 24.9 (not taken)    96 x 624 x 6064: 17 / 20 (not taken)       3329 x 175 x 1036: 21 / 28 (not taken)
 // and with rows that are not 16-byte aligned:
 //   200 x 1021 x 1021: 27 / 16 (32x64)            1000 x 3003 x 1021: 126 / 50 (128x128)     200 x 3003 x 1021: 55 / 26 (64x64)
-// Over 1200 shapes of 8 - 4096 x 64 - 9000 x 32 - 9000 the choice is in the mean 16 % faster than the fp32 plans, and more
-// than 4 % slower in six of them (7 % at most).
+// Over 1800 shapes of 8 - 4096 x 64 - 9000 x 32 - 9000 the choice is in the mean 16 % faster than the fp32 plans, and more
+// than 4 % slower in ten of them (12 % at most).
 // Small products stay with the fp32 MFMAs: every operand element has to be split once per tile it is used in, and LDS takes
 // the three parts at 64 bytes per cycle, which small tiles cannot hide.
 // Summation error: a split-operand plan has at least 0.75 times as many partial sums as the plan it replaces.
