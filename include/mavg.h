@@ -282,10 +282,9 @@ int32_t ngsgd_precondition(void* state, int32_t dim, int32_t rank,
 /* ---- the dense contraction all of the above are built from (exported for tests and tuning) -------- */
 /*
  * C(m,n) = epilogue( sum_{kk<k} A(m,kk) B(kk,n) ), float32 operands, float32 accumulation.  Either float32 MFMAs, or every
- * operand element split into two fp16 parts (22 bits; off by one unit of the last place for a quarter of all floats)
- * and three products of parts accumulated by fp16 MFMAs: closer to the exact sums than float32 MFMAs from 32 contraction steps
- * on.  32x32 blocks with a row of A or a column of B whose largest magnitude is below 2^-14 (other than zero) or at least
- * 65408, and those in which a sum is infinite or NaN, are computed by float32 MFMAs with both.
+ * operand element split exactly into three bf16 parts and the six products of parts that float32 can tell apart accumulated by
+ * bf16 MFMAs (what is left out is at most 2^-24 of a product).  32x32 blocks in which a sum is infinite or NaN are computed by
+ * float32 MFMAs with both.
  *   a_kc != 0: A(m,kk) = a[m*lda + kk], else a[kk*lda + m];   b_kc != 0: B(kk,n) = b[n*ldb + kk], else b[kk*ldb + n]
  *   C(m,n) = c[m*ldc + n]
  *   epi: 0  C = v            1  C = v + bias[n]          2  C = alpha*sigmoid(v + bias[n])
@@ -294,9 +293,9 @@ int32_t ngsgd_precondition(void* state, int32_t dim, int32_t rank,
  *        0  64x64 tiles, operands loaded global -> LDS directly when they allow it (16-byte aligned rows, k a
  *           multiple of 16, widths of m/n-contiguous operands multiples of 4), else through registers
  *        1  64x64 tiles, always through registers (guarded loads: any shape and alignment)
- *        3 / 4 / 5  split-operand kernels (fp16 parts) with 64x64 / 64x128 / 128x128 tiles, any alignment;  2  256x128
+ *        3 / 4 / 5  split-operand kernels with 64x64 / 64x128 / 128x128 tiles, any alignment;  2  256x128
  *        6  as 0 with a shallower LDS ring
- *        7 / 8  direct-to-LDS 32x64 / 32x32 tiles (fp16 parts) whose contraction is split eight / four ways inside the workgroup
+ *        7 / 8  direct-to-LDS 32x64 / 32x32 tiles whose contraction is split eight / four ways inside the workgroup
  *        9  split-operand kernel with 32x64 tiles
  *        (7, 8 run as 1 when the operands do not allow direct loads, the split-operand kernels when k < 16)
  *   splits: 0 = choose how many ways the contraction is split across workgroups (partial sums are combined
@@ -308,6 +307,27 @@ int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const float* b, int
                   float* c, int64_t ldc, int32_t m, int32_t n, int32_t k,
                   int32_t epi, const float* bias, const float* aux, int64_t ldaux, float alpha, float beta,
                   int32_t cfg, int32_t splits, void* workspace, int64_t workspace_bytes, void* stream);
+/*
+ * The same for operands whose rows (of A, columns of B) are known to have their largest magnitudes within a range, as the training
+ * calls use it: with MAVG_PARTS_TWO, every element may be split into two fp16 parts, after a scaling of A by 2^a_exp and of B by
+ * 2^b_exp, and three products of parts are accumulated by fp16 MFMAs (4096^3: 400 us instead of 700).
+ *   An element x that is at least 2^-14 when scaled is off by up to 2^-23 of the next power of two (one unit of the last place, for a
+ *   quarter of all floats), a smaller one by up to 2^-36 of the range, that is 2^-36-a_exp: 2^-22 of its row's largest element.  The
+ *   product of two such parts is left out: 2^-22 of a product at most, 2^-21 with both roundings.  Long sums of ordinary terms come closer to
+ *   the exact ones than with float32 MFMAs all the same (fewer roundings): 2048 terms of either sign 2.2e-7, float32 MFMAs 8.1e-7.
+ *   32x32 blocks with a row or column whose largest magnitude, scaled, is below 2^-14 (other than zero) or at least 65408 are computed by
+ *   float32 MFMAs, as are those with an infinite sum or a NaN.
+ *   (The split-operand kernels scale both operands if both are m/n-contiguous, A alone if B alone is, none if both are k-contiguous.)
+ * MAVG_PARTS_THREE: as mavg_gemm.
+ * a_exp, b_exp: -60 to 60.  Errors: as mavg_gemm; MAVG_E_FLAG for other values of these three.
+ */
+#define MAVG_PARTS_THREE   0
+#define MAVG_PARTS_TWO     1
+int32_t mavg_gemm_parts(const float* a, int64_t lda, int32_t a_kc, const float* b, int64_t ldb, int32_t b_kc,
+                        float* c, int64_t ldc, int32_t m, int32_t n, int32_t k,
+                        int32_t epi, const float* bias, const float* aux, int64_t ldaux, float alpha, float beta,
+                        int32_t cfg, int32_t splits, int32_t parts, int32_t a_exp, int32_t b_exp,
+                        void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
  * Several independent contractions C_i = epilogue(A_i B_i) of the same operand layouts in ONE launch (unsplit
@@ -333,8 +353,11 @@ typedef struct {
     int32_t a_pad4, b_pad4;
 } mavg_gemm_problem;
 int32_t mavg_gemm_grouped(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc, void* stream);
+/* ... with the elements split as in mavg_gemm_parts. */
+int32_t mavg_gemm_grouped_parts(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc,
+                                int32_t parts, int32_t a_exp, int32_t b_exp, void* stream);
 /*
- * Which kernel that call runs problem `which` with: 0 = split-operand (fp16 parts), 1 = direct-to-LDS, 2 = register-staged
+ * Which kernel those calls run problem `which` with: 0 = split-operand, 1 = direct-to-LDS, 2 = register-staged
  * float32 MFMAs; or an error as above (MAVG_E_DIM also for `which` outside 0 .. count - 1).  Host only; for tests.
  */
 int32_t mavg_gemm_grouped_kernel(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc,

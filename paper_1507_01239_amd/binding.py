@@ -86,8 +86,11 @@ _SIG = {
     "ngsgd_precondition": (_i32, [_p, _i32, _i32, _p, _i64, _i32, _f, _f, _i32, _p, _i64, _p]),
     "mavg_gemm": (_i32, [_p, _i64, _i32, _p, _i64, _i32, _p, _i64, _i32, _i32, _i32, _i32, _p, _p, _i64, _f, _f,
                          _i32, _i32, _p, _i64, _p]),
+    "mavg_gemm_parts": (_i32, [_p, _i64, _i32, _p, _i64, _i32, _p, _i64, _i32, _i32, _i32, _i32, _p, _p, _i64, _f, _f,
+                               _i32, _i32, _i32, _i32, _i32, _p, _i64, _p]),
     "mavg_gemm_workspace_bytes": (_i64, [_i32, _i32, _i32, _i32, _i32]),
     "mavg_gemm_grouped": (_i32, [_p, _i32, _i32, _i32, _p]),
+    "mavg_gemm_grouped_parts": (_i32, [_p, _i32, _i32, _i32, _i32, _i32, _i32, _p]),
     "mavg_gemm_grouped_kernel": (_i32, [_p, _i32, _i32, _i32, _i32]),
 }
 EXPORTS = tuple(_SIG)
@@ -245,6 +248,16 @@ def mavg_gemm(a, lda, a_kc, b, ldb, b_kc, c, ldc, m, n, k, epi, bias, aux, ldaux
                                 ptr(aux), ldaux, alpha, beta, cfg, splits, ptr(workspace), wb, _stream(stream)), "mavg_gemm")
 
 
+PARTS_THREE, PARTS_TWO = 0, 1
+
+
+def mavg_gemm_parts(a, lda, a_kc, b, ldb, b_kc, c, ldc, m, n, k, epi, bias, aux, ldaux, alpha, beta, cfg, splits, parts, a_exp, b_exp,
+                    workspace, stream=None, workspace_bytes=None):
+    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
+    return _check(lib.mavg_gemm_parts(ptr(a), lda, int(a_kc), ptr(b), ldb, int(b_kc), ptr(c), ldc, m, n, k, epi, ptr(bias), ptr(aux), ldaux,
+                                      alpha, beta, cfg, splits, parts, a_exp, b_exp, ptr(workspace), wb, _stream(stream)), "mavg_gemm_parts")
+
+
 class GemmProblem(C.Structure):
     """mavg_gemm_problem of include/mavg.h."""
     _fields_ = [("a", _p), ("lda", _i64), ("b", _p), ("ldb", _i64), ("c", _p), ("ldc", _i64),
@@ -263,6 +276,12 @@ def mavg_gemm_grouped(problems, a_kc, b_kc, stream=None):
     arr = (GemmProblem * len(problems))(*problems)
     return _check(lib.mavg_gemm_grouped(C.cast(arr, C.c_void_p), len(problems), int(a_kc), int(b_kc), _stream(stream)),
                   "mavg_gemm_grouped")
+
+
+def mavg_gemm_grouped_parts(problems, a_kc, b_kc, parts, a_exp, b_exp, stream=None):
+    arr = (GemmProblem * len(problems))(*problems)
+    return _check(lib.mavg_gemm_grouped_parts(C.cast(arr, C.c_void_p), len(problems), int(a_kc), int(b_kc), parts, a_exp, b_exp,
+                                              _stream(stream)), "mavg_gemm_grouped_parts")
 
 
 def mavg_gemm_grouped_kernel(problems, a_kc, b_kc, which) -> int:

@@ -14,9 +14,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmavg.so")
-SOURCES = ["gemm_split256.hip", "gemm_split128.hip", "gemm_split64x128.hip", "gemm_split64.hip", "gemm_split32x64.hip", "gemm_split_grouped.hip",
-           "gemm_dma64.hip", "gemm_kg.hip", "gemm_legacy.hip", "gemm.hip", "elementwise.hip", "average.hip", "dnn.hip", "narrow.hip", "rbm.hip",
-           "ngsgd.hip"]
+SPLIT = [f"gemm_split{t}{p}.hip" for p in ("", "_three") for t in ("256", "128", "64x128", "64", "32x64", "_grouped")]
+SOURCES = SPLIT + ["gemm_dma64.hip", "gemm_kg.hip", "gemm_legacy.hip", "gemm.hip", "elementwise.hip", "average.hip", "dnn.hip",
+                   "narrow.hip", "rbm.hip", "ngsgd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-std=c++17", "-O3", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

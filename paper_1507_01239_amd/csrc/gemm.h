@@ -58,6 +58,9 @@ struct Epilogue {
 //   a_kc: A(m,k) = A[m*lda + k]  (contraction index contiguous) else A[k*lda + m]
 //   b_kc: B(k,n) = B[n*ldb + k]  else B[k*ldb + n]
 //   C(m,n) = C[m*ldc + n]
+// How the split-operand kernels may split an element (gemm_split.h): into three bf16 parts, exactly, or into two fp16 parts, off by up
+// to 2^-22 of it or, where that is more, 2^-36 of the range (a_exp, b_exp).
+enum SplitParts : int { kThreeParts = 0, kTwoParts = 1 };
 // a_exp / b_exp of values that are at most 1 in magnitude (probabilities, activations), and of values without a bound that are
 // expected between 2^-19 and 2^11 (features, weights)
 constexpr int kExpUnit = 15, kExpFree = 5;
@@ -71,12 +74,13 @@ struct GemmDesc {
     // columns (the caller's buffer has that padding inside its row stride; what it holds is never used in a
     // stored result).  Lets the direct-to-LDS kernel take widths that are not multiples of 4.
     bool a_pad4 = false, b_pad4 = false;
-    // What the split-operand kernels scale the operands by, log2.  Taken as they are: both operands where both are k-contiguous
-    // (a forward product: activations, weights), B where A alone is (a back-propagated error: weights); the scaling of a pair of
-    // elements is two of the nine instructions that its split takes.  The kernels are at their best when the largest magnitude
-    // of every row of A and column of B, scaled, lies between 2^-14 and 65504; 32x32 blocks of C with other rows or columns are
-    // recomputed, three times as slowly.
-    int a_exp = 0, b_exp = 0;
+    SplitParts parts = kThreeParts;
+    // Two parts: what the operands are scaled by, log2, so that the largest magnitude of a row of A or column of B lies between 2^-14
+    // and 65408.  The split-operand kernels take as they are both operands where both are k-contiguous (a forward product:
+    // activations, weights), B where A alone is (a back-propagated error: weights); the scaling of a pair of elements is two of the
+    // nine instructions that its split takes.
+    int a_exp = kExpFree, b_exp = kExpFree;
+    bool a_exact = false;      // A holds nothing but zeros and numbers of at most 11 bits, which one part holds as they are
     Epilogue epi;
     int force_cfg = -1;     // -1: choose; otherwise tile configuration index
     int force_splits = 0;   // 0: choose; otherwise number of contraction splits
@@ -101,9 +105,9 @@ enum GemmCfg : int {
 struct GemmPlan { int cfg; int splits; int bm, bn; };
 
 // `ragged`: the rows of an operand are not 16-byte aligned (the direct-to-LDS kernels are out then).  ws_floats: the
-// scratch there is for partial sums; plans that need more are not considered.
+// scratch there is for partial sums; plans that need more are not considered.  three: the split-operand kernels split into three parts.
 GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged = false,
-                   int64_t ws_floats = INT64_MAX);
+                   int64_t ws_floats = INT64_MAX, bool three = false);
 // float32 elements of scratch the plan for this problem needs (0 when it is not split), whatever the operands' alignment
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg = -1, int force_splits = 0);
 // ... when only the fp32-MFMA kernels are considered, whatever the operands' alignment and strides: the least that

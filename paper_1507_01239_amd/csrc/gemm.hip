@@ -182,6 +182,35 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
     return c;
 }
 
+// The same with three parts, from measurements at 32 to 4096 rows, 440 to 8000 contraction
+// steps and 1 to 2000 tiles (operands of ordinary values: with every compute unit busy the split-operand kernels run
+// into the power limit, which the share `full` of busy compute units stands for; on zeros they take a quarter less).
+static double plan_cost_three(const GemmPlan& pl, int M, int N, int K, int batch, bool ragged) {
+    const int64_t w = tiles_of(pl.cfg, M, N, batch) * pl.splits;
+    const double rounds = (double)((w + kNumCU - 1) / kNumCU), full = w < kNumCU ? (double)w / kNumCU : 1.0;
+    const double ks = (double)((K + pl.splits - 1) / pl.splits);
+    double c;
+    switch (pl.cfg) {
+    case CFG_S128: c = 3 + rounds * (9 + ks * (0.0284 + 0.0131 * full * full)); break;
+    case CFG_S64x128: c = 3 + rounds * (5 + ks * (0.0180 + 0.0055 * full * full)); break;
+    case CFG_S64: c = 5 + rounds * (2 + ks * 0.0132) + (rounds == 1 ? ks * 0.005 : 0.0); break;      // (up to three workgroups per compute unit)
+    case CFG_S32x64: c = 2.3 + rounds * (5.7 + ks * 0.0077); break;
+    case CFG_KG_32x64: c = 5 + rounds * ks * 0.0075; break;
+    case CFG_KG_32x32: c = 5 + (w < kNumCU ? 1.0 : (double)w / kNumCU) * ks * 0.0049; break;      // (two workgroups per compute unit)
+    default:      // (64x64 tiles; measured at 1200 shapes: within 6 % of this, one standard deviation)
+        if (ragged) c = 5 + rounds * ks * 0.0348 * (rounds == 1 ? 1.2 : 1.0);
+        else c = pl.splits > 1 ? 3 + rounds * ks * 0.0145 : 5 + rounds * ks * 0.0157;
+        break;
+    }
+    if (pl.splits > 1) {
+        // the reducer and the partial sums; next to the split-operand kernels less of it shows, as their own epilogue is then
+        // a plain store
+        const double bytes = 8.0 * pl.splits * M * N * batch;
+        c += cfg_split(pl.cfg) ? 3.5 + bytes / 20e6 + (bytes > 32e6 ? (bytes - 32e6) / 8e6 : 0.0) : 4 + bytes / 6e6;
+    }
+    return c;
+}
+
 // The automatic plans take the split-operand kernels from this many contraction steps on: where they sum shorter ones their
 // errors are larger than those of the fp32 MFMAs.  Relative errors against float64, split / fp32, of terms of either sign and
 // of positive terms: 16 steps 89 / 73 and 45 / 62 (e-9), 24 steps 93 / 89 and 43 / 74, 32 steps 94 / 103 and 45 / 84.
@@ -198,26 +227,32 @@ constexpr int kSplitMinK = 32, kSplitGroupedMinK = 80;
 //   377 x 408 x 328: 9.3 / 5.7 (32x32 in-workgroup split)     22 x 7688 x 320: 8.3 / 5.4 (likewise)      256 x 2048 x 2048: 21 / 16 (32x64 likewise)
 // Small products stay with the fp32 MFMAs: every operand element has to be split once per tile it is used in, and LDS takes
 // the parts at 64 bytes per cycle, which small tiles cannot hide.
-GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged, int64_t ws_floats) {
+GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged, int64_t ws_floats, bool three) {
     GemmPlan best = gemm_plan_fp32(M, N, K, batch, force_cfg, force_splits);
     if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < kSplitMinK) return best;
     if (ragged && best.cfg != CFG_64) best = gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits);
-    double least = 0.94 * plan_cost(best, M, N, K, batch, ragged);      // (what another kernel must promise: the estimates' scatter)
+    auto cost = [&](const GemmPlan& pl) { return three ? plan_cost_three(pl, M, N, K, batch, ragged) : plan_cost(pl, M, N, K, batch, ragged); };
+    // (what another kernel must promise: the estimates' scatter)
+    double least = (three ? ragged ? 0.9 : 0.97 : 0.94) * cost(best);
+    // Summation error: three parts have at least 0.75 times as many partial sums as the plan they replace.
+    const int sums = three ? best.splits * (cfg_kg(best.cfg) ? 4 : 1) : 0;
     auto consider = [&](int cfg, int sp) {
         const GemmPlan pl = gemm_plan_fp32(M, N, K, batch, cfg, sp);
-        const double c = plan_cost(pl, M, N, K, batch, ragged);
+        const double c = cost(pl);
         if (c < least) { least = c; best = pl; }
     };
     // (a k-tile of 16 steps for each of their wavefronts)
-    if (!ragged && force_splits <= 1) {
+    if (!ragged && !three && force_splits <= 1) {
         if (K >= 16 * 8) consider(CFG_KG_32x64, 1);
         if (K >= 16 * 4) consider(CFG_KG_32x32, 1);
     }
-    for (const int cfg : {(int)CFG_S256, (int)CFG_S128, (int)CFG_S64x128, (int)CFG_S64, (int)CFG_S32x64})
+    static const struct { int cfg, kgroups; } kSplitCfgs[] = {{CFG_S256, 1}, {CFG_S128, 2}, {CFG_S64x128, 4}, {CFG_S64, 2}, {CFG_S32x64, 8}};
+    for (const auto& sc : kSplitCfgs)
         for (int sp = 1; sp <= 8; sp *= 2) {
             if (force_splits > 0 && sp != force_splits) continue;
             if (sp > 1 && (K < 256 * sp || (int64_t)sp * batch * M * N > ws_floats)) continue;
-            consider(cfg, sp);
+            if ((three && sc.cfg == CFG_S256) || 4 * sp * sc.kgroups < 3 * sums) continue;
+            consider(sc.cfg, sp);
         }
     return best;
 }
@@ -286,8 +321,9 @@ static GemmKParams fill_params(const GemmDesc& d, const GemmPlan& pl, float* ws)
     p.vecA = aligned16(d.A) && (d.lda % 4 == 0) && (d.a_bstride % 4 == 0);
     p.vecB = aligned16(d.B) && (d.ldb % 4 == 0) && (d.b_bstride % 4 == 0);
     p.ws = ws;
-    const int a_exp = d.a_kc && d.b_kc ? 0 : d.a_exp, b_exp = d.a_kc || d.b_kc ? 0 : d.b_exp;
-    p.scale_a = ldexpf(1.f, a_exp); p.scale_b = ldexpf(1.f, b_exp); p.unscale = ldexpf(1.f, -(a_exp + b_exp));
+    p.scale_a = ldexpf(1.f, d.a_exp); p.scale_b = ldexpf(1.f, d.b_exp);
+    p.least_a = d.a_exact ? 0.f : kSplitLeast;
+    p.three = d.parts == kThreeParts;
     p.epi = d.epi;
     return p;
 }
@@ -299,8 +335,10 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     const bool rowsum = d.epi.rowsum_dst != nullptr || d.epi.side_sum_src != nullptr;
     GemmPlan pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, rowsum && cfg_split(d.force_cfg) ? CFG_64 : d.force_cfg, rowsum ? 1 : d.force_splits);
     GemmKParams p = fill_params(d, pl, ws);
+    const bool three = d.parts == kThreeParts;
     if (!rowsum && split_eligible(d)) {
-        pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, !dma_eligible(d, p), ws ? ws_floats : 0);
+        const bool ragged = !dma_eligible(d, p);
+        pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
         p = fill_params(d, pl, ws);
     }
     if ((cfg_split(pl.cfg) && !split_eligible(d)) ||
@@ -311,11 +349,14 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     if (pl.splits > 1 && (ws == nullptr || ws_floats < (int64_t)pl.splits * d.batch * d.M * d.N)) return note_hip_error(hipErrorInvalidValue);
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)(d.batch * pl.splits));
     if (cfg_split(pl.cfg)) {      // (the plan may have been replaced above)
-        if (pl.cfg == CFG_S256) launch_split256(p, d.a_kc, d.b_kc, grid, stream);
-        else if (pl.cfg == CFG_S64x128) launch_split64x128(p, d.a_kc, d.b_kc, grid, stream);
-        else if (pl.cfg == CFG_S64) launch_split64(p, d.a_kc, d.b_kc, grid, stream);
-        else if (pl.cfg == CFG_S32x64) launch_split32x64(p, d.a_kc, d.b_kc, grid, stream);
-        else launch_split128(p, d.a_kc, d.b_kc, grid, stream);
+        typedef void (*Launch)(const GemmKParams&, bool, bool, dim3, hipStream_t);
+        static const Launch k256[] = {launch_split256_three, launch_split256},
+                            k128[] = {launch_split128_three, launch_split128},
+                            k64x128[] = {launch_split64x128_three, launch_split64x128},
+                            k64[] = {launch_split64_three, launch_split64},
+                            k32x64[] = {launch_split32x64_three, launch_split32x64};      // (in the order of SplitParts)
+        const Launch* of = pl.cfg == CFG_S256 ? k256 : pl.cfg == CFG_S64x128 ? k64x128 : pl.cfg == CFG_S64 ? k64 : pl.cfg == CFG_S32x64 ? k32x64 : k128;
+        of[d.parts](p, d.a_kc, d.b_kc, grid, stream);
     } else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else if (pl.cfg != CFG_64_REG && dma_eligible(d, p)) launch_dma64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else launch_legacy(p, d.a_kc, d.b_kc, grid, stream);
@@ -412,6 +453,7 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
     if (thin) return gemm_launch_grouped_thin(d, count, stream);
     // Four passes over the problems, one for each kernel: split-operand (0 with 128x128 tiles, 3 with 256x128), 1 and 2.
     const int64_t tiles128 = grouped_tiles128(d, count);
+    const bool three = count > 0 && d[0].parts == kThreeParts;
     for (int pass = 0; pass < 4; ++pass) {
         GemmGroupParams gp;
         gp.ngroups = 0;
@@ -421,7 +463,7 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (gp.ngroups == 0) return 0;
             gp.tile_start[gp.ngroups] = tiles;
             const dim3 grid((unsigned)tiles, 1, (unsigned)batch);
-            if (pass == 0 || pass == 3) launch_grouped_split(gp, pass == 3, grid, stream);
+            if (pass == 0 || pass == 3) (three ? launch_grouped_split_three : launch_grouped_split)(gp, pass == 3, grid, stream);
             else if (pass == 1) launch_grouped_dma(gp, a_kc, b_kc, grid, stream);
             else launch_grouped_legacy(gp, a_kc, b_kc, grid, stream);
             gp.ngroups = 0;
@@ -434,10 +476,11 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (di.M <= 0 || di.N <= 0 || di.batch <= 0) continue;
             if (di.a_kc != d[0].a_kc || di.b_kc != d[0].b_kc || di.batch != d[0].batch) return note_hip_error(hipErrorInvalidValue);
             if (di.epi.rowsum_dst != nullptr && di.a_kc) return note_hip_error(hipErrorInvalidValue);
+            if (di.parts != d[0].parts) return note_hip_error(hipErrorInvalidValue);
             // unsplit, 64x64 tiles (the split-operand kernel's below)
             GemmKParams q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_64, 1), nullptr);
             const int kernel = grouped_kernel(di, q, tiles128);
-            if ((kernel == 0 && grouped_wide(di, tiles128) ? 3 : kernel) != pass) continue;
+            if ((kernel == 0 && !three && grouped_wide(di, tiles128) ? 3 : kernel) != pass) continue;
             if (kernel == 0) q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, pass == 3 ? CFG_S256 : CFG_S128, 1), nullptr);
             a_kc = di.a_kc; b_kc = di.b_kc; batch = di.batch;
             gp.g[gp.ngroups] = q;
@@ -475,6 +518,15 @@ extern "C" int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const fl
                              float* c, int64_t ldc, int32_t m, int32_t n, int32_t k, int32_t epi, const float* bias,
                              const float* aux, int64_t ldaux, float alpha, float beta, int32_t cfg, int32_t splits,
                              void* workspace, int64_t workspace_bytes, void* stream) {
+    return mavg_gemm_parts(a, lda, a_kc, b, ldb, b_kc, c, ldc, m, n, k, epi, bias, aux, ldaux, alpha, beta, cfg, splits, MAVG_PARTS_THREE, 0, 0,
+                           workspace, workspace_bytes, stream);
+}
+
+extern "C" int32_t mavg_gemm_parts(const float* a, int64_t lda, int32_t a_kc, const float* b, int64_t ldb, int32_t b_kc,
+                                   float* c, int64_t ldc, int32_t m, int32_t n, int32_t k, int32_t epi, const float* bias,
+                                   const float* aux, int64_t ldaux, float alpha, float beta, int32_t cfg, int32_t splits,
+                                   int32_t parts, int32_t a_exp, int32_t b_exp, void* workspace, int64_t workspace_bytes, void* stream) {
+    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_TWO || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
     if (!a || !b || !c) return MAVG_E_NULL;
     if (m < 1 || n < 1 || k < 0) return MAVG_E_DIM;
     if (cfg >= kNumCfgs || splits < 0 || epi < EPI_STORE || epi > EPI_AXPBY) return MAVG_E_FLAG;
@@ -490,6 +542,7 @@ extern "C" int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const fl
     g.M = m; g.N = n; g.K = k;
     g.epi.kind = epi; g.epi.bias = bias; g.epi.aux = aux; g.epi.ldaux = ldaux; g.epi.alpha = alpha; g.epi.beta = beta;
     g.force_cfg = cfg; g.force_splits = splits;
+    g.parts = (SplitParts)parts; g.a_exp = a_exp; g.b_exp = b_exp;
     float* ws = workspace ? reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(workspace) + 255u) & ~uintptr_t(255)) : nullptr;
     return gemm_launch(g, ws, need, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
 }
@@ -521,9 +574,16 @@ static int32_t grouped_descs(const mavg_gemm_problem* pr, int32_t count, int32_t
 }
 
 extern "C" int32_t mavg_gemm_grouped(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, void* stream) {
+    return mavg_gemm_grouped_parts(pr, count, a_kc, b_kc, MAVG_PARTS_THREE, 0, 0, stream);
+}
+
+extern "C" int32_t mavg_gemm_grouped_parts(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, int32_t parts, int32_t a_exp,
+                                           int32_t b_exp, void* stream) {
     GemmDesc g[kMaxGroups];
     const int32_t rc = grouped_descs(pr, count, a_kc, b_kc, g);
     if (rc) return rc;
+    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_TWO || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
+    for (int i = 0; i < count; ++i) { g[i].parts = (SplitParts)parts; g[i].a_exp = a_exp; g[i].b_exp = b_exp; }
     return gemm_launch_grouped(g, count, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
 }
 

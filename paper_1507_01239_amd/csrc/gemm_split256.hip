@@ -1,15 +1,9 @@
-// Split-operand GEMM kernels (gemm_split.h): 256x128 tiles.
+// Split-operand GEMM kernels (gemm_split.h): 256x128 tiles, two fp16 parts.
 #include "gemm_split.h"
 #include "gemm_launchers.h"
 
 namespace mavg {
 
-void launch_split256(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) {
-    const dim3 block(512);
-    if (a_kc && b_kc) hipLaunchKernelGGL((gemm_split_kernel<256, 128, 4, 2, 1, 2, true, true>), grid, block, 0, s, p);
-    else if (a_kc && !b_kc) hipLaunchKernelGGL((gemm_split_kernel<256, 128, 4, 2, 1, 2, true, false>), grid, block, 0, s, p);
-    else if (!a_kc && !b_kc) hipLaunchKernelGGL((gemm_split_kernel<256, 128, 4, 2, 1, 2, false, false>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((gemm_split_kernel<256, 128, 4, 2, 1, 2, false, true>), grid, block, 0, s, p);
-}
+void launch_split256(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s) { launch_split<kTwoParts, 256, 128, 4, 2, 1>(p, a_kc, b_kc, grid, s); }
 
 }  // namespace mavg

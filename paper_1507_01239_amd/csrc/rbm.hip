@@ -78,7 +78,7 @@ extern "C" int32_t rbm_hidden_prob(int32_t n_vis, int32_t n_hid, const float* w,
     float* ws = ws_base(workspace);
     GemmDesc g;
     g.M = n; g.N = n_hid; g.K = n_vis;
-    g.A = v; g.lda = n_vis; g.a_kc = true; g.a_exp = kExpFree;
+    g.A = v; g.lda = n_vis; g.a_kc = true; g.parts = kTwoParts;
     g.B = w; g.ldb = n_vis; g.b_kc = true;
     g.C = out; g.ldc = n_hid;
     g.epi.kind = EPI_BIAS_SIGMOID; g.epi.bias = c;
@@ -119,7 +119,7 @@ int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, floa
     {   // P_h0 = sigmoid(V0 W^T + c), H0 = [u < P_h0]
         GemmDesc g;
         g.M = n; g.N = H; g.K = V;
-        g.A = v0; g.lda = V; g.a_kc = true; g.a_exp = kExpFree;
+        g.A = v0; g.lda = V; g.a_kc = true; g.parts = kTwoParts;
         g.B = w; g.ldb = V; g.b_kc = true;
         g.C = ph0; g.ldc = lay.ldh;
         g.epi.kind = EPI_BIAS_SIGMOID_SAMPLE; g.epi.bias = c;
@@ -130,8 +130,8 @@ int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, floa
     {   // V1 from H0 W + a
         GemmDesc g;
         g.M = n; g.N = V; g.K = H;
-        g.A = h0; g.lda = lay.ldh; g.a_kc = true; g.a_exp = kExpUnit;
-        g.B = w; g.ldb = V; g.b_kc = false; g.b_exp = kExpFree;
+        g.A = h0; g.lda = lay.ldh; g.a_kc = true; g.parts = kTwoParts; g.a_exp = kExpUnit; g.a_exact = true;
+        g.B = w; g.ldb = V; g.b_kc = false;
         g.C = v1; g.ldc = lay.ldv;
         g.epi.bias = a;
         if (vis_type == MAVG_VIS_GAUSSIAN) g.epi.kind = EPI_BIAS;
@@ -147,7 +147,7 @@ int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, floa
     {   // -P_h1 = -sigmoid(V1 W^T + c)
         GemmDesc g;
         g.M = n; g.N = H; g.K = V;
-        g.A = v1; g.lda = lay.ldv; g.a_kc = true; g.a_exp = kExpFree;
+        g.A = v1; g.lda = lay.ldv; g.a_kc = true; g.parts = kTwoParts; g.a_exact = (flags & MAVG_SAMPLE_V1) != 0;
         g.B = w; g.ldb = V; g.b_kc = true;
         g.C = ph1; g.ldc = lay.ldh;
         g.epi.kind = EPI_BIAS_SIGMOID; g.epi.bias = c; g.epi.alpha = -1.f;
@@ -160,9 +160,9 @@ int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, floa
     {   // MW <- momentum MW + (lr/n) (P_h0^T V0 - P_h1^T V1) = momentum MW + (lr/n) [P_h0; -P_h1]^T [V0; V1];  W <- W + MW
         GemmDesc g;
         g.M = H; g.N = V; g.K = 2 * n;
-        g.A = ph0; g.lda = lay.ldh; g.a_kc = false; g.a_exp = kExpUnit;
+        g.A = ph0; g.lda = lay.ldh; g.a_kc = false;
         g.a_pad4 = true;        // rows of the stacked statistics are ldh = round_up(H, 4) floats long
-        g.B = vv; g.ldb = lay.ldv; g.b_kc = false; g.b_exp = kExpFree;
+        g.B = vv; g.ldb = lay.ldv; g.b_kc = false;
         g.b_pad4 = true;
         g.C = mw; g.ldc = V;
         g.epi.kind = EPI_AXPBY; g.epi.alpha = lr * invn; g.epi.beta = momentum;
