@@ -318,11 +318,13 @@ int32_t mavg_gemm(const float* a, int64_t lda, int32_t a_kc, const float* b, int
  *   32x32 blocks with a row or column whose largest magnitude, scaled, is below 2^-14 (other than zero) or at least 65408 are computed by
  *   float32 MFMAs, as are those with an infinite sum or a NaN.
  *   (The split-operand kernels scale both operands if both are m/n-contiguous, A alone if B alone is, none if both are k-contiguous.)
- * MAVG_PARTS_THREE: as mavg_gemm.
+ * MAVG_PARTS_BY_DATA: tiles in which a row of A or column of B begins with elements below 2^-14 (scaled; zeros among them) are
+ * split into three parts, which takes half as long again, the others into two.  MAVG_PARTS_THREE: as mavg_gemm.
  * a_exp, b_exp: -60 to 60.  Errors: as mavg_gemm; MAVG_E_FLAG for other values of these three.
  */
 #define MAVG_PARTS_THREE   0
 #define MAVG_PARTS_TWO     1
+#define MAVG_PARTS_BY_DATA 2
 int32_t mavg_gemm_parts(const float* a, int64_t lda, int32_t a_kc, const float* b, int64_t ldb, int32_t b_kc,
                         float* c, int64_t ldc, int32_t m, int32_t n, int32_t k,
                         int32_t epi, const float* bias, const float* aux, int64_t ldaux, float alpha, float beta,

@@ -248,7 +248,7 @@ def mavg_gemm(a, lda, a_kc, b, ldb, b_kc, c, ldc, m, n, k, epi, bias, aux, ldaux
                                 ptr(aux), ldaux, alpha, beta, cfg, splits, ptr(workspace), wb, _stream(stream)), "mavg_gemm")
 
 
-PARTS_THREE, PARTS_TWO = 0, 1
+PARTS_THREE, PARTS_TWO, PARTS_BY_DATA = 0, 1, 2
 
 
 def mavg_gemm_parts(a, lda, a_kc, b, ldb, b_kc, c, ldc, m, n, k, epi, bias, aux, ldaux, alpha, beta, cfg, splits, parts, a_exp, b_exp,

@@ -220,7 +220,7 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
         GemmDesc g;
         g.M = n; g.N = y.d[l - 1]; g.K = y.d[l]; g.batch = k;
         g.A = delta_of(l); g.lda = w.ld_delta[l]; g.a_bstride = dstride_of(l); g.a_kc = true;
-        g.parts = kTwoParts; g.a_exp = delta_exp(l);
+        g.parts = kPartsByData; g.a_exp = delta_exp(l);
         g.B = theta + y.w_off[l]; g.ldb = y.d[l - 1]; g.b_bstride = theta_stride; g.b_kc = false;
         g.C = delta_of(l - 1); g.ldc = w.ld_delta[l - 1]; g.c_bstride = dstride_of(l - 1);
         g.epi.kind = EPI_MUL_DSIGMOID;
@@ -239,7 +239,7 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
             q.a_pad4 = true;       // rows of delta_l are ld_delta = round_up(d_l, 4) floats long
             q.B = (l == 1) ? x : acts + y.a_off[l - 1]; q.ldb = y.d[l - 1]; q.b_bstride = (l == 1) ? x_stride : act_stride;
             q.b_kc = false;
-            q.parts = kTwoParts; q.a_exp = delta_exp(l); q.b_exp = l == 1 ? kExpFree : kExpUnit;
+            q.parts = kPartsByData; q.a_exp = delta_exp(l); q.b_exp = l == 1 ? kExpFree : kExpUnit;
             q.C = theta + y.w_off[l]; q.ldc = y.d[l - 1]; q.c_bstride = theta_stride;
             q.epi.kind = EPI_AXPBY; q.epi.alpha = -lr; q.epi.beta = 1.f;
             q.epi.rowsum_dst = theta + y.b_off[l]; q.epi.rowsum_bstride = theta_stride;

@@ -58,9 +58,10 @@ struct Epilogue {
 //   a_kc: A(m,k) = A[m*lda + k]  (contraction index contiguous) else A[k*lda + m]
 //   b_kc: B(k,n) = B[n*ldb + k]  else B[k*ldb + n]
 //   C(m,n) = C[m*ldc + n]
-// How the split-operand kernels may split an element (gemm_split.h): into three bf16 parts, exactly, or into two fp16 parts, off by up
-// to 2^-22 of it or, where that is more, 2^-36 of the range (a_exp, b_exp).
-enum SplitParts : int { kThreeParts = 0, kTwoParts = 1 };
+// How the split-operand kernels may split an element (gemm_split.h): into three bf16 parts, exactly; into two fp16 parts, off by up
+// to 2^-22 of it or, where that is more, 2^-36 of the range (a_exp, b_exp); into three where a row has nothing larger than that
+// leaves exact, else two.
+enum SplitParts : int { kThreeParts = 0, kTwoParts = 1, kPartsByData = 2 };
 // a_exp / b_exp of values that are at most 1 in magnitude (probabilities, activations), and of values without a bound that are
 // expected between 2^-19 and 2^11 (features, weights)
 constexpr int kExpUnit = 15, kExpFree = 5;

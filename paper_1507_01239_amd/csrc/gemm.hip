@@ -350,11 +350,11 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)(d.batch * pl.splits));
     if (cfg_split(pl.cfg)) {      // (the plan may have been replaced above)
         typedef void (*Launch)(const GemmKParams&, bool, bool, dim3, hipStream_t);
-        static const Launch k256[] = {launch_split256_three, launch_split256},
-                            k128[] = {launch_split128_three, launch_split128},
-                            k64x128[] = {launch_split64x128_three, launch_split64x128},
-                            k64[] = {launch_split64_three, launch_split64},
-                            k32x64[] = {launch_split32x64_three, launch_split32x64};      // (in the order of SplitParts)
+        static const Launch k256[] = {launch_split256_three, launch_split256, launch_split256_by_data},
+                            k128[] = {launch_split128_three, launch_split128, launch_split128_by_data},
+                            k64x128[] = {launch_split64x128_three, launch_split64x128, launch_split64x128_by_data},
+                            k64[] = {launch_split64_three, launch_split64, launch_split64_by_data},
+                            k32x64[] = {launch_split32x64_three, launch_split32x64, launch_split32x64_by_data};      // (in the order of SplitParts)
         const Launch* of = pl.cfg == CFG_S256 ? k256 : pl.cfg == CFG_S64x128 ? k64x128 : pl.cfg == CFG_S64 ? k64 : pl.cfg == CFG_S32x64 ? k32x64 : k128;
         of[d.parts](p, d.a_kc, d.b_kc, grid, stream);
     } else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
@@ -463,7 +463,7 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (gp.ngroups == 0) return 0;
             gp.tile_start[gp.ngroups] = tiles;
             const dim3 grid((unsigned)tiles, 1, (unsigned)batch);
-            if (pass == 0 || pass == 3) (three ? launch_grouped_split_three : launch_grouped_split)(gp, pass == 3, grid, stream);
+            if (pass == 0 || pass == 3) (three ? launch_grouped_split_three : d[0].parts == kTwoParts ? launch_grouped_split : launch_grouped_split_by_data)(gp, pass == 3, grid, stream);
             else if (pass == 1) launch_grouped_dma(gp, a_kc, b_kc, grid, stream);
             else launch_grouped_legacy(gp, a_kc, b_kc, grid, stream);
             gp.ngroups = 0;
@@ -526,7 +526,7 @@ extern "C" int32_t mavg_gemm_parts(const float* a, int64_t lda, int32_t a_kc, co
                                    float* c, int64_t ldc, int32_t m, int32_t n, int32_t k, int32_t epi, const float* bias,
                                    const float* aux, int64_t ldaux, float alpha, float beta, int32_t cfg, int32_t splits,
                                    int32_t parts, int32_t a_exp, int32_t b_exp, void* workspace, int64_t workspace_bytes, void* stream) {
-    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_TWO || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
+    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_BY_DATA || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
     if (!a || !b || !c) return MAVG_E_NULL;
     if (m < 1 || n < 1 || k < 0) return MAVG_E_DIM;
     if (cfg >= kNumCfgs || splits < 0 || epi < EPI_STORE || epi > EPI_AXPBY) return MAVG_E_FLAG;
@@ -582,7 +582,7 @@ extern "C" int32_t mavg_gemm_grouped_parts(const mavg_gemm_problem* pr, int32_t 
     GemmDesc g[kMaxGroups];
     const int32_t rc = grouped_descs(pr, count, a_kc, b_kc, g);
     if (rc) return rc;
-    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_TWO || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
+    if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_BY_DATA || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
     for (int i = 0; i < count; ++i) { g[i].parts = (SplitParts)parts; g[i].a_exp = a_exp; g[i].b_exp = b_exp; }
     return gemm_launch_grouped(g, count, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
 }

@@ -13,7 +13,7 @@ void launch_dma64(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid
 void launch_grouped_dma(const GemmGroupParams& gp, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 // contraction split inside the workgroup: 32x64 tiles (CFG_KG_32x64) or 32x32 tiles (CFG_KG_32x32); thin grouped problems
 void launch_kg(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
-// split-operand kernels: two fp16 parts per fp32 element, or three bf16 parts; grouped: m- and n-contiguous
+// split-operand kernels: two fp16 parts per fp32 element, three bf16 parts, or as the data ask for; grouped: m- and n-contiguous
 // operands only, `wide`: 256x128 tiles
 void launch_split256(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 void launch_split128(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
@@ -27,6 +27,12 @@ void launch_split64x128_three(const GemmKParams& p, bool a_kc, bool b_kc, dim3 g
 void launch_split64_three(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 void launch_split32x64_three(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 void launch_grouped_split_three(const GemmGroupParams& gp, bool wide, dim3 grid, hipStream_t s);
+void launch_split256_by_data(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+void launch_split128_by_data(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+void launch_split64x128_by_data(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+void launch_split64_by_data(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+void launch_split32x64_by_data(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+void launch_grouped_split_by_data(const GemmGroupParams& gp, bool wide, dim3 grid, hipStream_t s);
 void launch_thin(const ThinGroupParams& gp, dim3 grid, hipStream_t s);
 
 }  // namespace mavg

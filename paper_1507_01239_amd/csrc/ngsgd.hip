@@ -1165,7 +1165,7 @@ int ng_run(const NgCall& c, hipStream_t s) {
         g.a_pad4 = true;                 // rows of H are ldr = round_up(rank, 4) floats long
         g.B = c.x; g.ldb = c.ldx; g.b_bstride = c.x_b; g.b_kc = false;
         g.b_pad4 = c.ldx >= w.ld;
-        g.parts = kTwoParts; g.a_exp = c.x_exp - 3; g.b_exp = c.x_exp;      // (a row of H is as long as a row of X)
+        g.parts = kPartsByData; g.a_exp = c.x_exp - 3; g.b_exp = c.x_exp;      // (a row of H is as long as a row of X)
         g.C = Y; g.ldc = w.ld; g.c_bstride = w.RY_b;
         g.epi.kind = EPI_ROWSCALE_ADD; g.epi.alpha = c.eta / (float)c.n;
         g.epi.rowvec = t.coef + kMaxRank; g.epi.rowvec_bstride = w.coef_b;
@@ -1376,7 +1376,7 @@ int ng_layer_update(const NgLayerArgs& a, hipStream_t s) {
         g.M = a.d_out; g.N = a.d_in + 1; g.K = a.n; g.batch = a.k;
         g.A = a.delta; g.lda = a.ldd; g.a_bstride = a.d_bstride; g.a_kc = false;
         g.a_pad4 = true;       // rows of delta are round_up(d_out, 4) floats long
-        g.parts = kTwoParts; g.a_exp = a.delta_exp;
+        g.parts = kPartsByData; g.a_exp = a.delta_exp - 3;      // (preconditioning may raise an element)
         g.B = Xaug; g.ldb = ld_in; g.b_bstride = aug_b; g.b_kc = false;
         g.b_pad4 = true;       // rows of Xaug are ld_in = round_up(d_in + 1, 4) floats long
         g.C = a.W; g.ldc = a.d_in; g.c_bstride = a.theta_stride;
@@ -1520,7 +1520,7 @@ int ng_dnn_update(const NgLayerArgs* layers, int L, char* ng_state, int64_t stat
                 q.M = a.d_out; q.N = a.d_in; q.K = n; q.batch = k;
                 q.A = a.delta; q.lda = a.ldd; q.a_bstride = a.d_bstride; q.a_kc = false;
                 q.a_pad4 = true;
-                q.parts = kTwoParts; q.a_exp = a.delta_exp;
+                q.parts = kPartsByData; q.a_exp = a.delta_exp - 3;      // (preconditioning may raise an element)
                 q.B = t.x[2 * i]; q.ldb = t.ldx[2 * i]; q.b_bstride = t.x_b[2 * i]; q.b_kc = false;
                 q.b_pad4 = true;
                 q.C = a.W; q.ldc = a.d_in; q.c_bstride = a.theta_stride;

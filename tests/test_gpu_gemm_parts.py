@@ -1,14 +1,15 @@
 """The split-operand and in-workgroup-split GEMM kernels with two fp16 parts per element, as the training calls use them
-(mavg_gemm_parts): what two parts hold and what they lose, and values that do not survive them."""
+(mavg_gemm_parts): what two parts hold and what they lose, values that do not survive them, and the choice between two and three parts
+by the operands themselves."""
 import numpy as np
 import pytest
 
-from tests.test_gpu_gemm_split_range import EXPONENTS, LAYOUTS, _check, _rows, _wide
+from tests.test_gpu_gemm_split_range import EXPONENTS, LAYOUTS, _check, _pick, _rows, _wide
 from tests.util import dev, host, rel_err, workspace
 
 pytestmark = pytest.mark.gpu
 
-TWO = 1
+TWO, BY_DATA = 1, 2
 CFGS = [2, 3, 4, 5, 7, 8, 9]      # split-operand tiles 256x128, 64x64, 64x128, 128x128, 32x64; in-workgroup split 32x64, 32x32
 
 
@@ -32,7 +33,7 @@ def _ref(A, Bt):
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
 @pytest.mark.parametrize("cfg", CFGS)
-@pytest.mark.parametrize("parts", [TWO])
+@pytest.mark.parametrize("parts", [TWO, BY_DATA])
 def test_tile_edges_and_contraction_remainders(parts, cfg, a_kc, b_kc):
     # m, n at tile edges; one k-tile to many, with and without a partial one, fewer tiles than k-groups; rows aligned to 4 bytes only
     # (the in-workgroup-split kernels: 16, or another kernel runs).  Tolerance: every addition of 1040 rounding by 2^-24 gives 1.4e-6.
@@ -47,7 +48,7 @@ def test_tile_edges_and_contraction_remainders(parts, cfg, a_kc, b_kc):
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
 @pytest.mark.parametrize("cfg", CFGS)
-@pytest.mark.parametrize("parts", [TWO])
+@pytest.mark.parametrize("parts", [TWO, BY_DATA])
 @pytest.mark.parametrize("k", [76, 268])
 def test_rows_of_any_magnitude(parts, cfg, a_kc, b_kc, k):
     # every row within 2^8 of its largest element: as close as float32 products, whatever that element is (and two groups of ordinary rows)
@@ -98,7 +99,7 @@ def test_single_products(cfg):
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
 @pytest.mark.parametrize("cfg", CFGS)
-@pytest.mark.parametrize("parts", [0, TWO])
+@pytest.mark.parametrize("parts", [0, TWO, BY_DATA])
 def test_values_that_do_not_survive_the_parts(parts, cfg, a_kc, b_kc):
     # infinities, NaNs and floats too large for either, in the first k-group's share, in others', and in the rest of the contraction
     rng = np.random.default_rng(340)
@@ -132,7 +133,7 @@ def test_long_sums_of_ordinary_terms_are_closer_than_float32_products(m, n, k):
     assert rel_err(_product(A, Bt, 1, 1, -1, TWO, splits=0), ref) < 0.5 * rel_err(_product(A, Bt, 1, 1, 0, TWO), ref)
 
 
-@pytest.mark.parametrize("parts", [TWO])
+@pytest.mark.parametrize("parts", [TWO, BY_DATA])
 @pytest.mark.parametrize("n,shapes,kernel", [(101, [(1155, 1537), (130, 65)], 0), (263, [(4100, 4100), (130, 68)], 0)])
 def test_grouped_updates(parts, n, shapes, kernel):
     # ordinary values and rows of any magnitude, in one launch with a small problem beside the large one; row sums
@@ -163,7 +164,7 @@ def test_grouped_updates(parts, n, shapes, kernel):
                 _check(-4.0 * host(t[2]).astype(np.float64), D.T, X.T)
 
 
-@pytest.mark.parametrize("parts", [TWO])
+@pytest.mark.parametrize("parts", [TWO, BY_DATA])
 def test_grouped_updates_in_256x128_tiles(parts):
     # from 1024 rows and sixteen tiles of 128x128 per compute unit on; ragged tile edges, a partial k-tile, row sums, a small problem beside.
     # Tolerance: every addition of 1027 rounding by 2^-24 gives 1.4e-6.
@@ -191,10 +192,78 @@ def test_arguments():
     import torch
     from paper_1507_01239_amd import binding as B
     x = torch.zeros(64, 64, device="cuda")
-    for parts, ea, eb in [(-1, 0, 0), (2, 0, 0), (1, 61, 0), (1, 0, -61)]:
+    for parts, ea, eb in [(-1, 0, 0), (3, 0, 0), (1, 61, 0), (1, 0, -61)]:
         with pytest.raises(B.MavgError) as e:
             B.mavg_gemm_parts(x, 64, 1, x, 64, 1, torch.zeros_like(x), 64, 64, 64, 64, 0, None, None, 0, 1.0, 0.0, -1, 1, parts, ea, eb, None)
         assert e.value.code == B.E_FLAG
         with pytest.raises(B.MavgError) as e:
             B.mavg_gemm_grouped_parts([B.gemm_problem(x, 64, x, 64, torch.zeros_like(x), 64, 64, 64, 64)], 0, 0, parts, ea, eb)
         assert e.value.code == B.E_FLAG
+
+
+# ---- two parts or three, as the operands ask for ----------------------------------------------------------------------------------------
+
+
+@pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
+@pytest.mark.parametrize("cfg", CFGS)
+def test_rows_that_begin_small_lose_nothing(cfg, a_kc, b_kc):
+    # nothing but small elements to begin with and large ones later, facing zeros: three parts (in the in-workgroup-split kernels,
+    # float32 products), exact as mavg_gemm is
+    rng = np.random.default_rng(370 + cfg)
+    m, n, k = 300, 152, 268
+    A = _wide(rng, m, k, -80, -40)
+    late = rng.integers(130, k, m)
+    A[np.arange(m), late] = rng.uniform(0.5, 1, m)
+    Bt = np.maximum(_pick(rng, n, k, rng.integers(0, 120, n)), 2.0 ** -12 * (np.arange(k) < 130)).astype(np.float32)
+    _check(_product(A, Bt, a_kc, b_kc, cfg, BY_DATA), A, Bt)
+
+
+@pytest.mark.parametrize("cfg", [2, 3, 4, 5, 9])
+@pytest.mark.parametrize("m,n,k,splits", [(1, 1, 17, 1), (257, 129, 40, 1), (300, 140, 700, 3), (33, 65, 1201, 1)])
+def test_one_small_row_among_many(cfg, m, n, k, splits):
+    # one row far below the others, in the last tile; a contraction of a partial k-tile and one whole one, and in splits
+    rng = np.random.default_rng(380)
+    A, Bt = rng.uniform(0.5, 2, (m, k)).astype(np.float32), rng.uniform(0.5, 2, (n, k)).astype(np.float32)
+    A[m - 1] *= np.float32(2.0 ** -50)
+    for a_kc, b_kc in ((1, 0), (0, 0)):
+        _check(_product(A, Bt, a_kc, b_kc, cfg, BY_DATA, splits), A, Bt)
+        _check(_product(Bt, A, a_kc, b_kc, cfg, BY_DATA, splits), Bt, A)
+
+
+def _graph_us(calls):
+    """Microseconds a call of each of `calls`, captured twenty times over in a graph each and replayed in turn."""
+    import torch
+    graphs = []
+    for f in calls:
+        f()
+        torch.cuda.synchronize()
+        g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(g, stream=s):
+            for _ in range(20):
+                f()
+        graphs.append(g)
+    best = [1e9] * len(calls)
+    for _ in range(12):
+        for i, g in enumerate(graphs):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            g.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], e0.elapsed_time(e1) * 50)
+    return best
+
+
+def test_small_rows_take_no_multiple_of_the_time():
+    # one class in 32 whose errors are all far below the others', as with a trained network and thousands of classes: measured 1.3 times
+    # the time of ordinary errors (4.1 times when their blocks go to the fp32 matrix cores, as with MAVG_PARTS_TWO)
+    import torch
+    from paper_1507_01239_amd import binding as B
+    n, m, nc = 512, 8000, 2048
+    d, x, w = torch.randn(n, m, device="cuda"), torch.rand(n, nc, device="cuda"), torch.zeros(m, nc, device="cuda")
+    small = d.clone()
+    small[:, ::32] *= 2.0 ** -50
+    call = lambda t, parts=BY_DATA: lambda: B.mavg_gemm_grouped_parts([B.gemm_problem(t, m, x, nc, w, nc, m, nc, n, epi=4, alpha=1e-6, beta=1.0)], 0, 0, parts, 0, 0)
+    assert B.mavg_gemm_grouped_kernel([B.gemm_problem(d, m, x, nc, w, nc, m, nc, n, epi=4, alpha=1e-6, beta=1.0)], 0, 0, 0) == 0
+    ordinary, with_small, recomputed = _graph_us([call(d), call(small), call(small, TWO)])
+    assert with_small < 1.5 * ordinary, (ordinary, with_small, recomputed)
