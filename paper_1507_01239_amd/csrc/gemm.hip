@@ -328,6 +328,13 @@ static GemmKParams fill_params(const GemmDesc& d, const GemmPlan& pl, float* ws)
     return p;
 }
 
+// Short contractions in small tiles are split into three parts all the same: what two parts, or the look at the operands, cost once per
+// tile is more than what they save.  Rows that are not 16-byte aligned, us in a captured graph, three parts / two / by data:
+//   145 x 145: 129 steps 7.9 / 8.4 / 8.8, 193 steps 8.7 / 8.7 / 9.5, 385 steps 10.0 / 9.3 / 10.0      501 x 1501: 129 steps 9.4 / 8.9 / 9.3
+static bool short_three(const GemmDesc& d, bool ragged) {
+    return ragged && d.K < (d.parts == kPartsByData ? 384 : 192) && tiles_of(CFG_S32x64, d.M, d.N, d.batch) <= kNumCU;
+}
+
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {
     if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return 0;
     if (d.epi.rowsum_dst != nullptr && d.a_kc) return note_hip_error(hipErrorInvalidValue);
@@ -335,9 +342,10 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     const bool rowsum = d.epi.rowsum_dst != nullptr || d.epi.side_sum_src != nullptr;
     GemmPlan pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, rowsum && cfg_split(d.force_cfg) ? CFG_64 : d.force_cfg, rowsum ? 1 : d.force_splits);
     GemmKParams p = fill_params(d, pl, ws);
-    const bool three = d.parts == kThreeParts;
+    bool three = d.parts == kThreeParts;
     if (!rowsum && split_eligible(d)) {
         const bool ragged = !dma_eligible(d, p);
+        three = three || (d.force_cfg < 0 && short_three(d, ragged));
         pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
         p = fill_params(d, pl, ws);
     }
@@ -356,7 +364,7 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
                             k64[] = {launch_split64_three, launch_split64, launch_split64_by_data},
                             k32x64[] = {launch_split32x64_three, launch_split32x64, launch_split32x64_by_data};      // (in the order of SplitParts)
         const Launch* of = pl.cfg == CFG_S256 ? k256 : pl.cfg == CFG_S64x128 ? k64x128 : pl.cfg == CFG_S64 ? k64 : pl.cfg == CFG_S32x64 ? k32x64 : k128;
-        of[d.parts](p, d.a_kc, d.b_kc, grid, stream);
+        of[three ? kThreeParts : d.parts](p, d.a_kc, d.b_kc, grid, stream);
     } else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else if (pl.cfg != CFG_64_REG && dma_eligible(d, p)) launch_dma64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else launch_legacy(p, d.a_kc, d.b_kc, grid, stream);

@@ -267,3 +267,15 @@ def test_small_rows_take_no_multiple_of_the_time():
     assert B.mavg_gemm_grouped_kernel([B.gemm_problem(d, m, x, nc, w, nc, m, nc, n, epi=4, alpha=1e-6, beta=1.0)], 0, 0, 0) == 0
     ordinary, with_small, recomputed = _graph_us([call(d), call(small), call(small, TWO)])
     assert with_small < 1.5 * ordinary, (ordinary, with_small, recomputed)
+
+
+@pytest.mark.parametrize("m,n,k", [(145, 145, 129), (77, 501, 129), (200, 1021, 150)])
+def test_short_ragged_products_take_no_longer_with_two_parts(m, n, k):
+    # 8.4 against 7.9 us when they went to the kernels with two parts
+    import torch
+    from paper_1507_01239_amd import binding as B
+    a, b, c = torch.rand(m * k, device="cuda"), torch.randn(n * k, device="cuda"), torch.empty(m * n, device="cuda")
+    ws = workspace(B.mavg_gemm_workspace_bytes(m, n, k, -1, 0))
+    call = lambda parts: lambda: B.mavg_gemm_parts(a, k, 1, b, n, 0, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, -1, 0, parts, 5, 5, ws)
+    three, two, by_data = _graph_us([call(0), call(TWO), call(BY_DATA)])
+    assert two < 1.04 * three and by_data < 1.04 * three, (three, two, by_data)
