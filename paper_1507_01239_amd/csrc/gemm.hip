@@ -447,10 +447,10 @@ static int grouped_kernel(const GemmDesc& d, const GemmKParams& q, int64_t tiles
 }
 
 // Which tiles the split-operand kernel takes such a problem in: 256x128 where the contraction is long and the tiles are many (one
-// workgroup per compute unit, whose epilogue nothing hides, but a third fewer elements to split per MFMA): backward passes of
-// 440-6x2048-8000, 128x128 / 256x128: 8 replicas 256 rows 1799 / 1831 us, 512 rows 2801 / 2727, 1024 rows 5067 / 4954; 1 replica
-// 1024 rows 754 / 743.
-static bool grouped_wide(const GemmDesc& d, int64_t tiles128) { return d.K >= 512 && tiles128 >= 4 * kNumCU; }
+// workgroup per compute unit, whose epilogue nothing hides, but a third fewer elements to split per MFMA).  Backward passes of
+// 440-6x2048-8000, us, 128x128 / 256x128 tiles:   512 rows: 1 replica 503 / 513, 2 846 / 880, 4 1493 / 1536, 8 2760 / 2834
+//                                                1024 rows: 1 replica 777 / 780, 2 1347 / 1355, 4 2481 / 2461, 8 4972 / 4912
+static bool grouped_wide(const GemmDesc& d, int64_t tiles128) { return d.K >= 1024 && tiles128 >= 16 * kNumCU; }
 
 int gemm_grouped_kernel(const GemmDesc* d, int count, int which) {
     return grouped_kernel(d[which], fill_params(d[which], gemm_plan_fp32(d[which].M, d[which].N, d[which].K, d[which].batch, CFG_64, 1), nullptr),
