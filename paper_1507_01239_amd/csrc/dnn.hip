@@ -92,7 +92,7 @@ Workspace make_workspace(const Layout& y, int n, int k, uint32_t flags, int ng_r
 
 }  // namespace
 
-extern "C" const char* mavg_version(void) { return "mavg 0.1 (gfx950, fp32 and split fp16 MFMA)"; }
+extern "C" const char* mavg_version(void) { return "mavg 0.1 (gfx950, fp32, split fp16 and split bf16 MFMA)"; }
 
 extern "C" int64_t mavg_param_count(const mavg_shape* shape) {
     const int rc = check_shape(shape);
@@ -157,7 +157,7 @@ extern "C" int32_t dnn_forward(const mavg_shape* shape, int32_t k, const float* 
         g.M = n; g.N = y.d[l]; g.K = y.d[l - 1]; g.batch = k;
         if (l == 1) { g.A = x; g.lda = y.d[0]; g.a_bstride = x_stride; }
         else { g.A = acts + y.a_off[l - 1]; g.lda = y.d[l - 1]; g.a_bstride = act_stride; }
-        g.a_kc = true; g.parts = kTwoParts; g.a_exp = l == 1 ? kExpFree : kExpUnit;
+        g.a_kc = true; g.parts = kTwoParts;
         g.B = theta + y.w_off[l]; g.ldb = y.d[l - 1]; g.b_bstride = theta_stride; g.b_kc = true;
         g.C = acts + y.a_off[l]; g.ldc = y.d[l]; g.c_bstride = act_stride;
         g.epi.kind = (l < y.L) ? EPI_BIAS_SIGMOID : EPI_BIAS;

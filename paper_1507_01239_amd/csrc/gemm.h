@@ -97,7 +97,7 @@ enum GemmCfg : int {
     CFG_S64x128 = 4,     //   64x128 tiles with four,
     CFG_S128 = 5,        //   128x128 tiles with two
     CFG_64_RING3 = 6,    // as CFG_64 with a ring of three LDS stages
-    CFG_KG_32x64 = 7,    // 32x64 tile (fp16 parts), contraction split eight ways inside the workgroup, one wavefront each
+    CFG_KG_32x64 = 7,    // 32x64 tile, contraction split eight ways inside the workgroup, one wavefront each
     CFG_KG_32x32 = 8,    // 32x32 tile, likewise, four ways
     CFG_S32x64 = 9,      // split-operand kernel, 32x64 tiles with eight k-groups of one wavefront
     CFG_COUNT = 10
@@ -111,10 +111,10 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
                    int64_t ws_floats = INT64_MAX, bool three = false);
 // float32 elements of scratch the plan for this problem needs (0 when it is not split), whatever the operands' alignment
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg = -1, int force_splits = 0);
-// ... when only the fp32-MFMA kernels are considered, whatever the operands' alignment and strides: the least that
+// ... when the split-operand kernels are not considered, whatever the operands' alignment and strides: the least that
 // gemm_launch accepts for all of them (it then plans with that much)
-int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch);
-// enqueue; returns hipError_t as int (0 = ok).  ws must hold gemm_ws_floats_fp32() floats when that is > 0;
+int64_t gemm_ws_floats_direct(int M, int N, int K, int batch);
+// enqueue; returns hipError_t as int (0 = ok).  ws must hold gemm_ws_floats_direct() floats when that is > 0;
 // with less than gemm_ws_floats() the plan makes do with fewer splits.
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream);
 

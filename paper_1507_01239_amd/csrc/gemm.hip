@@ -5,9 +5,11 @@
 // reducer and the exported entry points.  The kernels live in gemm_device.h and gemm_split.h and are instantiated per
 // family in gemm_split*.hip, gemm_dma64.hip, gemm_kg.hip and gemm_legacy.hip (separate files so that they compile in
 // parallel).  They share the epilogues, the tile order and the split-contraction reducer:
-//  - gemm_split_kernel: every fp32 element in two fp16 parts, three fp16 MFMAs (v_mfma_f32_32x32x16_f16) per product;
-//    tiles from 32x64 to 256x128, any alignment: everything large, and everything the next two cannot take;
-//  - gemm_dma_kernel (v_mfma_f32_32x32x2_f32) and gemm_dma_kg_kernel (fp16 parts, made when a wavefront reads its operands back):
+//  - gemm_split_kernel: every fp32 element in two fp16 parts, three fp16 MFMAs (v_mfma_f32_32x32x16_f16) per product, or in
+//    three bf16 parts, six bf16 MFMAs; tiles from 32x64 to 256x128, any alignment: everything large, and everything the next two
+//    cannot take;
+//  - gemm_dma_kernel (v_mfma_f32_32x32x2_f32) and gemm_dma_kg_kernel (two fp16 parts, made when a wavefront reads its operands back,
+//    or the same MFMA):
 //    operands go from global memory straight into an LDS ring (global_load_lds_dwordx4): problems that do not fill the chip
 //    with large tiles, 16-byte aligned rows;
 //  - gemm_kernel: register-staged 64x64 tiles of the same MFMA with guarded loads, for what is left (contractions of fewer
@@ -83,8 +85,8 @@ static inline int64_t tiles_of(int cfg, int M, int N, int batch) {
     return (int64_t)((M + kCfgs[cfg].bm - 1) / kCfgs[cfg].bm) * ((N + kCfgs[cfg].bn - 1) / kCfgs[cfg].bn) * batch;
 }
 
-// The plan with the fp32 MFMA kernels alone (or the configuration that is asked for).
-static GemmPlan gemm_plan_fp32(int M, int N, int K, int batch, int force_cfg, int force_splits) {
+// The plan without the split-operand kernels (or the configuration that is asked for).
+static GemmPlan gemm_plan_direct(int M, int N, int K, int batch, int force_cfg, int force_splits) {
     GemmPlan pl;
     // Measured on MI355X (layer shapes at minibatch 256 to 1024, 1 and 8 replicas): the 64x64 direct-to-LDS
     // kernel wins everywhere; many small workgroups per compute unit run out of phase and hide each other's
@@ -98,15 +100,15 @@ static GemmPlan gemm_plan_fp32(int M, int N, int K, int batch, int force_cfg, in
         const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
         cfg = (K <= 1024 && t64 >= 1024) ? CFG_64_RING3 : CFG_64;
         // A skinny problem whose 32x64 tiles come to about one per compute unit (the 256 x 2048 x 2048 hidden
-        // layers of the minibatch-256 step) does its contraction split inside the workgroup: 24.5 against
-        // 26.9 us including the reducer (13.1 against 15.9 us for the 440-wide first layer).  Not at half or
-        // twice that many tiles, nor for K = 8000 (measured).
+        // layers of the minibatch-256 step) does its contraction split inside the workgroup: with fp32 MFMAs in both
+        // 21 to 23 against 26.9 us including the reducer (13.1 against 15.9 us for the 440-wide first layer).  Not at half or
+        // twice that many tiles, nor for K = 8000 (measured).  (With fp16 parts it is a candidate of gemm_plan by its cost.)
         const int64_t t3264 = (int64_t)((M + 31) / 32) * ((N + 63) / 64) * batch;
-        // (One workgroup of it fills a compute unit's LDS: past one tile per compute unit the launch takes two turns,
-        // 39 us at 272 or 288 rows against 29 us for 64x64 tiles split in three.)
+        // (One workgroup of it fills a compute unit's LDS: past one tile per compute unit the launch takes two turns, with fp32
+        // MFMAs 39 us at 272 or 288 rows against 29 us for 64x64 tiles split in three.)
         if (cfg == CFG_64 && t3264 >= 3 * kNumCU / 4 && t3264 <= kNumCU && K >= 256 && K <= 4096) cfg = CFG_KG_32x64;
         // Half as many rows again (128 x 2048 x 2048): 32x32 tiles, one wavefront per k-group, no barrier in the
-        // loop: 18.0 against 19.8 us.  (Two of its workgroups share a compute unit.)
+        // loop, with fp32 MFMAs: 18.0 against 19.8 us.  (Two of its workgroups share a compute unit.)
         const int64_t t3232 = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
         if (cfg == CFG_64 && t3232 >= 3 * kNumCU / 4 && t3232 <= kNumCU + kNumCU / 8 && K >= 1024 && K <= 4096) cfg = CFG_KG_32x32;
     }
@@ -182,8 +184,8 @@ static double plan_cost(const GemmPlan& pl, int M, int N, int K, int batch, bool
     return c;
 }
 
-// The same with three parts, from measurements at 32 to 4096 rows, 440 to 8000 contraction
-// steps and 1 to 2000 tiles (operands of ordinary values: with every compute unit busy the split-operand kernels run
+// The same with three parts (and fp32 MFMAs in the in-workgroup-split kernels), from measurements at 32 to 4096 rows, 440 to 8000
+// contraction steps and 1 to 2000 tiles (operands of ordinary values: with every compute unit busy the split-operand kernels run
 // into the power limit, which the share `full` of busy compute units stands for; on zeros they take a quarter less).
 static double plan_cost_three(const GemmPlan& pl, int M, int N, int K, int batch, bool ragged) {
     const int64_t w = tiles_of(pl.cfg, M, N, batch) * pl.splits;
@@ -217,27 +219,27 @@ static double plan_cost_three(const GemmPlan& pl, int M, int N, int K, int batch
 // The grouped launch's weight updates: from 80 steps on (99 / 161 and 46 / 138), below it they are memory's business anyway.
 constexpr int kSplitMinK = 32, kSplitGroupedMinK = 80;
 
-// Which kernel family: the cheapest by plan_cost among the fp32 MFMA plan, the in-workgroup-split kernels and the split-operand
+// Which kernel family: the cheapest by plan_cost among the plan without the split-operand kernels, the in-workgroup-split and the split-operand
 // kernels, unsplit or with 2, 4 or 8 contraction splits of at least 256 steps.  Over the 1500 shapes the choice is 0.6 % above the
 // fastest that was measured, and 12 % below the plans made for three bf16 parts (more than 10 % above those in twenty, short
 // or small ragged products).  Measured (us; those plans against these):
 //   4096 x 4096 x 4096: 686 / 405 (256x128)            8192 x 2048 x 2048: 349 / 210 (256x128)       2048 x 16384 x 512: 194 / 131 (256x128)
 //   1999 x 8000 x 2048: 345 / 207 (256x128)            1999 x 2048 x 2048: 91 / 63 (128x128)         1024 x 2048 x 2048: 54 / 40 (64x128)
-//   256 x 8000 x 2048: 54 / 40 (64x128)                256 x 2048 x 8000: 56 / 45 (128x128, 8 splits)    200 x 3003 x 1021: 28 / 19 (64x64)
+//   256 x 8000 x 2048: 54 / 43 (256x128, 4 splits; 64x128 42)                256 x 2048 x 8000: 56 / 45 (128x128, 8 splits)    200 x 3003 x 1021: 28 / 19 (64x64)
 //   377 x 408 x 328: 9.3 / 5.7 (32x32 in-workgroup split)     22 x 7688 x 320: 8.3 / 5.4 (likewise)      256 x 2048 x 2048: 21 / 16 (32x64 likewise)
-// Small products stay with the fp32 MFMAs: every operand element has to be split once per tile it is used in, and LDS takes
-// the parts at 64 bytes per cycle, which small tiles cannot hide.
+// (Two parts.  With three, small products stay with the fp32 MFMAs: every operand element has to be split once per tile it is used
+// in, and LDS takes the parts at 64 bytes per cycle, which small tiles cannot hide.)
 GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_splits, bool ragged, int64_t ws_floats, bool three) {
-    GemmPlan best = gemm_plan_fp32(M, N, K, batch, force_cfg, force_splits);
+    GemmPlan best = gemm_plan_direct(M, N, K, batch, force_cfg, force_splits);
     if ((force_cfg >= 0 && force_cfg < kNumCfgs) || K < kSplitMinK) return best;
-    if (ragged && best.cfg != CFG_64) best = gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits);
+    if (ragged && best.cfg != CFG_64) best = gemm_plan_direct(M, N, K, batch, CFG_64_REG, force_splits);
     auto cost = [&](const GemmPlan& pl) { return three ? plan_cost_three(pl, M, N, K, batch, ragged) : plan_cost(pl, M, N, K, batch, ragged); };
     // (what another kernel must promise: the estimates' scatter)
     double least = (three ? ragged ? 0.9 : 0.97 : 0.94) * cost(best);
     // Summation error: three parts have at least 0.75 times as many partial sums as the plan they replace.
     const int sums = three ? best.splits * (cfg_kg(best.cfg) ? 4 : 1) : 0;
     auto consider = [&](int cfg, int sp) {
-        const GemmPlan pl = gemm_plan_fp32(M, N, K, batch, cfg, sp);
+        const GemmPlan pl = gemm_plan_direct(M, N, K, batch, cfg, sp);
         const double c = cost(pl);
         if (c < least) { least = c; best = pl; }
     };
@@ -259,21 +261,21 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, int force_cfg, int force_spli
 
 static int64_t plan_floats(const GemmPlan& pl, int M, int N, int batch) { return pl.splits > 1 ? (int64_t)pl.splits * batch * M * N : 0; }
 
-// The fp32 MFMA plans for one problem: the automatic one, and the register-staged one that takes its place where operands
+// The plans without the split-operand kernels for one problem: the automatic one, and the register-staged one that takes its place where operands
 // are not 16-byte aligned or their strides are too long for the others (an in-workgroup-split plan has no partial sums, the
 // register-staged one for the same sizes up to sixteen splits of them).
-static int64_t plan_floats_fp32(int M, int N, int K, int batch, int cfg, int force_splits) {
-    const int64_t f = plan_floats(gemm_plan_fp32(M, N, K, batch, cfg, force_splits), M, N, batch);
-    const int64_t g = plan_floats(gemm_plan_fp32(M, N, K, batch, CFG_64_REG, force_splits), M, N, batch);
+static int64_t plan_floats_direct(int M, int N, int K, int batch, int cfg, int force_splits) {
+    const int64_t f = plan_floats(gemm_plan_direct(M, N, K, batch, cfg, force_splits), M, N, batch);
+    const int64_t g = plan_floats(gemm_plan_direct(M, N, K, batch, CFG_64_REG, force_splits), M, N, batch);
     return f > g ? f : g;
 }
 
-int64_t gemm_ws_floats_fp32(int M, int N, int K, int batch) { return plan_floats_fp32(M, N, K, batch, CFG_AUTO, 0); }
+int64_t gemm_ws_floats_direct(int M, int N, int K, int batch) { return plan_floats_direct(M, N, K, batch, CFG_AUTO, 0); }
 
 int64_t gemm_ws_floats(int M, int N, int K, int batch, int force_cfg, int force_splits) {
     const bool forced = force_cfg >= 0 && force_cfg < kNumCfgs;
-    int64_t f = plan_floats_fp32(M, N, K, batch, forced ? CFG_64_REG : CFG_AUTO, force_splits);
-    // (Below 512 steps the split-operand kernels run unsplit when they are chosen, so the fp32 plans are all there is to
+    int64_t f = plan_floats_direct(M, N, K, batch, forced ? CFG_64_REG : CFG_AUTO, force_splits);
+    // (Below 512 steps the split-operand kernels run unsplit when they are chosen, so those plans are all there is to
     // cover; callers ask on every call, and the comparison of plans is most of the host time of a small one.)
     if (!forced && force_splits <= 0 && K < 512) return f;
     auto cover = [&](const GemmPlan& pl) { const int64_t g = plan_floats(pl, M, N, batch); if (g > f) f = g; };
@@ -340,7 +342,7 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     if (d.epi.rowsum_dst != nullptr && d.a_kc) return note_hip_error(hipErrorInvalidValue);
     // fused row sums and the side sum are the work of the kernels that own a whole tile: unsplit, no k-groups
     const bool rowsum = d.epi.rowsum_dst != nullptr || d.epi.side_sum_src != nullptr;
-    GemmPlan pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, rowsum && cfg_split(d.force_cfg) ? CFG_64 : d.force_cfg, rowsum ? 1 : d.force_splits);
+    GemmPlan pl = gemm_plan_direct(d.M, d.N, d.K, d.batch, rowsum && cfg_split(d.force_cfg) ? CFG_64 : d.force_cfg, rowsum ? 1 : d.force_splits);
     GemmKParams p = fill_params(d, pl, ws);
     bool three = d.parts == kThreeParts;
     if (!rowsum && split_eligible(d)) {
@@ -351,7 +353,7 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     }
     if ((cfg_split(pl.cfg) && !split_eligible(d)) ||
         (cfg_kg(pl.cfg) && !(dma_eligible(d, p) && !rowsum && d.K / kDmaBK >= (pl.cfg == CFG_KG_32x64 ? 2 : 1) * kKGroups))) {
-        pl = gemm_plan_fp32(d.M, d.N, d.K, d.batch, CFG_64_REG, rowsum ? 1 : d.force_splits);
+        pl = gemm_plan_direct(d.M, d.N, d.K, d.batch, CFG_64_REG, rowsum ? 1 : d.force_splits);
         p = fill_params(d, pl, ws);
     }
     if (pl.splits > 1 && (ws == nullptr || ws_floats < (int64_t)pl.splits * d.batch * d.M * d.N)) return note_hip_error(hipErrorInvalidValue);
@@ -402,7 +404,7 @@ static int gemm_launch_grouped_thin(const GemmDesc* d, int count, hipStream_t st
         if (di.M <= 0 || di.N <= 0 || di.batch <= 0) continue;
         if (!di.a_kc || !di.b_kc || di.batch != d[0].batch || di.epi.kind != EPI_STORE || di.epi.rowsum_dst != nullptr)
             return note_hip_error(hipErrorInvalidValue);
-        const GemmPlan pl = gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_KG_32x32, 1);
+        const GemmPlan pl = gemm_plan_direct(di.M, di.N, di.K, di.batch, CFG_KG_32x32, 1);
         const GemmKParams q = fill_params(di, pl, nullptr);
         if (!dma_eligible(di, q) || di.K / kDmaBK < kThinKGroups) {
             GemmDesc one = di;
@@ -453,7 +455,7 @@ static int grouped_kernel(const GemmDesc& d, const GemmKParams& q, int64_t tiles
 static bool grouped_wide(const GemmDesc& d, int64_t tiles128) { return d.K >= 1024 && tiles128 >= 16 * kNumCU; }
 
 int gemm_grouped_kernel(const GemmDesc* d, int count, int which) {
-    return grouped_kernel(d[which], fill_params(d[which], gemm_plan_fp32(d[which].M, d[which].N, d[which].K, d[which].batch, CFG_64, 1), nullptr),
+    return grouped_kernel(d[which], fill_params(d[which], gemm_plan_direct(d[which].M, d[which].N, d[which].K, d[which].batch, CFG_64, 1), nullptr),
                           grouped_tiles128(d, count));
 }
 
@@ -486,10 +488,10 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
             if (di.epi.rowsum_dst != nullptr && di.a_kc) return note_hip_error(hipErrorInvalidValue);
             if (di.parts != d[0].parts) return note_hip_error(hipErrorInvalidValue);
             // unsplit, 64x64 tiles (the split-operand kernel's below)
-            GemmKParams q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, CFG_64, 1), nullptr);
+            GemmKParams q = fill_params(di, gemm_plan_direct(di.M, di.N, di.K, di.batch, CFG_64, 1), nullptr);
             const int kernel = grouped_kernel(di, q, tiles128);
             if ((kernel == 0 && !three && grouped_wide(di, tiles128) ? 3 : kernel) != pass) continue;
-            if (kernel == 0) q = fill_params(di, gemm_plan_fp32(di.M, di.N, di.K, di.batch, pass == 3 ? CFG_S256 : CFG_S128, 1), nullptr);
+            if (kernel == 0) q = fill_params(di, gemm_plan_direct(di.M, di.N, di.K, di.batch, pass == 3 ? CFG_S256 : CFG_S128, 1), nullptr);
             a_kc = di.a_kc; b_kc = di.b_kc; batch = di.batch;
             gp.g[gp.ngroups] = q;
             gp.tile_start[gp.ngroups] = tiles;
