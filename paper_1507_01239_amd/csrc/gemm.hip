@@ -452,7 +452,8 @@ static int grouped_kernel(const GemmDesc& d, const GemmKParams& q, int64_t tiles
 // workgroup per compute unit, whose epilogue nothing hides, but a third fewer elements to split per MFMA).  Backward passes of
 // 440-6x2048-8000, us, 128x128 / 256x128 tiles:   512 rows: 1 replica 503 / 513, 2 846 / 880, 4 1493 / 1536, 8 2760 / 2834
 //                                                1024 rows: 1 replica 777 / 780, 2 1347 / 1355, 4 2481 / 2461, 8 4972 / 4912
-static bool grouped_wide(const GemmDesc& d, int64_t tiles128) { return d.K >= 1024 && tiles128 >= 16 * kNumCU; }
+// (2352 tiles of 128x128 a replica: the line lies between two replicas and four)
+static bool grouped_wide(const GemmDesc& d, int64_t tiles128) { return d.K >= 1024 && tiles128 >= 32 * kNumCU; }
 
 int gemm_grouped_kernel(const GemmDesc* d, int count, int which) {
     return grouped_kernel(d[which], fill_params(d[which], gemm_plan_direct(d[which].M, d[which].N, d[which].K, d[which].batch, CFG_64, 1), nullptr),
