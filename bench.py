@@ -26,8 +26,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# The two ways to multiply float32 matrices here: float32 MFMAs (256 CU x 4 SIMD x 64 FLOP/cycle x 2.4 GHz), or three fp16 MFMAs
-# per product (dense fp16 peak 2.5 PFLOP/s).  Fractions are of the second, the higher one, unless a record names its peak.
+# The ways to multiply float32 matrices here: float32 MFMAs (256 CU x 4 SIMD x 64 FLOP/cycle x 2.4 GHz), three fp16 MFMAs per
+# product (dense fp16 peak 2.5 PFLOP/s) as training takes them, or six bf16 ones where rows begin too small for fp16.
+# Fractions are of the second, the highest one, unless a record names its peak.
 PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_SPLIT_MFMA_TFLOPS = round(2500.0 / 3, 1)
 PEAK_HBM_GBPS = 8000.0
@@ -35,7 +36,7 @@ ALL_EXTRAS = ("kernels", "stats", "averaging", "cd1", "stack", "sweep", "paper",
 # rocprofv3 counter summary of the roofline kernel: bench.py takes `traffic` from the record this file carries
 ROOFLINE_PROFILE = os.path.join(ROOT, "profiles", "weight_update_grouped_mb256_hbm_counters.md")
 # by what mavg_gemm_grouped_kernel answers for its largest problem: kernel, its form, peak
-ROOFLINE_KERNELS = {0: ("gemm_split_grouped_kernel", "<128,128,2,2,1,2,false,false> fp32 in two fp16 parts", PEAK_SPLIT_MFMA_TFLOPS),
+ROOFLINE_KERNELS = {0: ("gemm_split_grouped_kernel", "<2,128,128,2,2,1,2,false,false> fp32 in two fp16 parts", PEAK_SPLIT_MFMA_TFLOPS),
                     1: ("gemm_dma_grouped_kernel", "<1,1,3,false,false> fp32", PEAK_FP32_MFMA_TFLOPS),
                     2: ("gemm_grouped_kernel", "<64,64,16,2,2,4,false,false> fp32", PEAK_FP32_MFMA_TFLOPS)}
 
@@ -140,7 +141,8 @@ def main():
         t_end = time.perf_counter() + seconds
         while time.perf_counter() < t_end:
             for _ in range(200):
-                B.mavg_gemm(wa, dims[-2], 1, ww, dims[-2], 1, wc, dims[-1], n, dims[-1], dims[-2], 0, None, None, 0, 1.0, 0.0, -1, 0, wws)
+                B.mavg_gemm_parts(wa, dims[-2], 1, ww, dims[-2], 1, wc, dims[-1], n, dims[-1], dims[-2], 0, None, None, 0, 1.0, 0.0, -1, 0,
+                                  B.PARTS_TWO, 5, 5, wws)
             torch.cuda.synchronize()
 
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -214,20 +216,26 @@ def main():
     bl = [None] + [th_s[b_off[l]:b_off[l] + dims[l]] for l in range(1, L + 1)]
     gws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
 
+    # the parts and exponents that training asks for: features and weights below 2^10, activations and errors of mean losses below 1
+    D_EXP, W_EXP = 21, 15
+
+    def a_exp(l):
+        return 5 if l == 0 else 15
+
     def fwd(l):     # A_l = act(A_{l-1} W_l^T + b_l)
-        B.mavg_gemm(A[l - 1], dims[l - 1], 1, Wl[l], dims[l - 1], 1, A[l], dims[l], n, dims[l], dims[l - 1],
-                    2 if l < L else 1, bl[l], None, 0, 1.0, 0.0, -1, 0, gws)
+        B.mavg_gemm_parts(A[l - 1], dims[l - 1], 1, Wl[l], dims[l - 1], 1, A[l], dims[l], n, dims[l], dims[l - 1],
+                          2 if l < L else 1, bl[l], None, 0, 1.0, 0.0, -1, 0, B.PARTS_TWO, a_exp(l - 1), W_EXP, gws)
 
     def bwd(l):     # D_{l-1} = (D_l W_l) * A_{l-1} (1 - A_{l-1})
-        B.mavg_gemm(D[l], ld[l], 1, Wl[l], dims[l - 1], 0, D[l - 1], ld[l - 1], n, dims[l - 1], dims[l], 3, None,
-                    A[l - 1], dims[l - 1], 1.0, 0.0, -1, 0, gws)
+        B.mavg_gemm_parts(D[l], ld[l], 1, Wl[l], dims[l - 1], 0, D[l - 1], ld[l - 1], n, dims[l - 1], dims[l], 3, None,
+                          A[l - 1], dims[l - 1], 1.0, 0.0, -1, 0, B.PARTS_BY_DATA, D_EXP, W_EXP, gws)
 
     update = [B.gemm_problem(D[l], ld[l], A[l - 1], dims[l - 1], Wl[l], dims[l - 1], dims[l], dims[l - 1], n, epi=4,
                              alpha=-1e-6, beta=1.0, rowsum_dst=bl[l], rowsum_alpha=-1e-6, rowsum_beta=1.0, a_pad4=True)
               for l in range(1, L + 1)]
 
     def dw():       # W_l <- W_l - lr D_l^T A_{l-1}, b_l <- b_l - lr colsum(D_l), all layers in one launch
-        B.mavg_gemm_grouped(update, 0, 0)
+        B.mavg_gemm_grouped_parts(update, 0, 0, B.PARTS_BY_DATA, D_EXP, a_exp(0))
 
     # ---- roofline of the dominant kernel of the step: the grouped weight update -------------------------
     dw_flop = 2.0 * n * sum(dims[l] * dims[l - 1] for l in range(1, L + 1))
