@@ -30,7 +30,7 @@ RbmWs rbm_ws(int V, int H, int n) {
     RbmWs w;
     w.ldh = round_up(H, 4);
     w.ldv = round_up(V, 4);
-    // (no more than the fp32 MFMA plans need: rbm_cd1_step_static has a fixed scratch size, and what fits it is documented)
+    // (no more than the plans without the split-operand kernels need: rbm_cd1_step_static has a fixed scratch size, and what fits it is documented)
     int64_t g = gemm_ws_floats_direct(n, H, V, 1), f;
     f = gemm_ws_floats_direct(n, V, H, 1); if (f > g) g = f;
     w.gemm_floats = round_up(g, 64);
