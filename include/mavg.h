@@ -365,6 +365,15 @@ int32_t mavg_gemm_grouped_parts(const mavg_gemm_problem* problems, int32_t count
 int32_t mavg_gemm_grouped_kernel(const mavg_gemm_problem* problems, int32_t count, int32_t a_kc, int32_t b_kc,
                                  int32_t which);
 
+/*
+ * The same problems as mavg_gemm_grouped (m- and n-contiguous operands, epi 4 only) the way that training computes its weight updates
+ * from 80 rows on: a launch that scales every column of both operands by a power of two and splits it into two fp16 parts, then the
+ * products.  tiles: -1 = as training chooses, 0 = 64x64, 1 = 64x128, 2 = 128x128.  Needs mavg_gemm_grouped_packed_bytes() of scratch.
+ */
+int64_t mavg_gemm_grouped_packed_bytes(const mavg_gemm_problem* problems, int32_t count);
+int32_t mavg_gemm_grouped_packed(const mavg_gemm_problem* problems, int32_t count, int32_t tiles, void* workspace,
+                                 int64_t workspace_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

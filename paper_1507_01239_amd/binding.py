@@ -91,6 +91,8 @@ _SIG = {
     "mavg_gemm_workspace_bytes": (_i64, [_i32, _i32, _i32, _i32, _i32]),
     "mavg_gemm_grouped": (_i32, [_p, _i32, _i32, _i32, _p]),
     "mavg_gemm_grouped_parts": (_i32, [_p, _i32, _i32, _i32, _i32, _i32, _i32, _p]),
+    "mavg_gemm_grouped_packed_bytes": (_i64, [_p, _i32]),
+    "mavg_gemm_grouped_packed": (_i32, [_p, _i32, _i32, _p, _i64, _p]),
     "mavg_gemm_grouped_kernel": (_i32, [_p, _i32, _i32, _i32, _i32]),
 }
 EXPORTS = tuple(_SIG)
@@ -282,6 +284,18 @@ def mavg_gemm_grouped_parts(problems, a_kc, b_kc, parts, a_exp, b_exp, stream=No
     arr = (GemmProblem * len(problems))(*problems)
     return _check(lib.mavg_gemm_grouped_parts(C.cast(arr, C.c_void_p), len(problems), int(a_kc), int(b_kc), parts, a_exp, b_exp,
                                               _stream(stream)), "mavg_gemm_grouped_parts")
+
+
+def mavg_gemm_grouped_packed_bytes(problems) -> int:
+    arr = (GemmProblem * len(problems))(*problems)
+    return _check(lib.mavg_gemm_grouped_packed_bytes(C.cast(arr, C.c_void_p), len(problems)), "mavg_gemm_grouped_packed_bytes")
+
+
+def mavg_gemm_grouped_packed(problems, tiles, workspace, stream=None, workspace_bytes=None):
+    arr = (GemmProblem * len(problems))(*problems)
+    wb = _nbytes(workspace) if workspace_bytes is None else workspace_bytes
+    return _check(lib.mavg_gemm_grouped_packed(C.cast(arr, C.c_void_p), len(problems), tiles, ptr(workspace), wb, _stream(stream)),
+                  "mavg_gemm_grouped_packed")
 
 
 def mavg_gemm_grouped_kernel(problems, a_kc, b_kc, which) -> int:

@@ -5,6 +5,7 @@
 
 #include "../../include/mavg.h"
 #include "gemm.h"
+#include "packed.h"
 #include "kernels.h"
 #include "ng_internal.h"
 
@@ -61,6 +62,7 @@ struct Workspace {
     int64_t off_rowloss, off_gemm, gemm_floats;
     int64_t off_ng, ng_floats;                // NG-SGD: preconditioned copies + its own scratch
     int64_t total_floats;
+    int64_t packed_floats;                    // behind all that: the operands of the weight updates, packed (calls with less scratch do without)
 };
 
 Workspace make_workspace(const Layout& y, int n, int k, uint32_t flags, int ng_rank) {
@@ -87,6 +89,8 @@ Workspace make_workspace(const Layout& y, int n, int k, uint32_t flags, int ng_r
     w.ng_floats = (flags & MAVG_USE_NGSGD) ? ng_dnn_ws_floats(y.d, y.L, n, k, ng_rank) : 0;
     off += w.ng_floats;
     w.total_floats = off;
+    w.packed_floats = 0;
+    for (int l = 1; l <= y.L; ++l) w.packed_floats += gemm_packed_floats(y.d[l], y.d[l - 1], n, k);
     return w;
 }
 
@@ -115,7 +119,8 @@ extern "C" int64_t mavg_workspace_bytes(const mavg_shape* shape, int32_t n, int3
     if ((flags & MAVG_NG_FIRST) && (flags & MAVG_NG_APPLY_ONLY)) return MAVG_E_FLAG;
     if ((flags & MAVG_USE_NGSGD) && (ng_rank < 1 || ng_rank > 64)) return MAVG_E_DIM;
     const Layout y = make_layout(shape, n);
-    return make_workspace(y, n, k, flags, ng_rank).total_floats * 4 + 256;
+    const Workspace w = make_workspace(y, n, k, flags, ng_rank);
+    return (w.total_floats + w.packed_floats) * 4 + 256;
 }
 
 static int check_common(const mavg_shape* shape, int32_t k, const void* theta, int64_t theta_stride, const void* x,
@@ -199,6 +204,7 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
     float* ws = ws_base(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
     float* gws = ws + w.off_gemm;
+    float* packed_ws = workspace_bytes >= (w.total_floats + w.packed_floats) * 4 + 256 ? ws + w.total_floats : nullptr;
     const float scale = (flags & MAVG_MEAN_GRAD) ? 1.0f / (float)n : 1.0f;
     auto delta_of = [&](int l) { return ws + w.off_delta[l]; };
     auto dstride_of = [&](int l) { return (int64_t)n * w.ld_delta[l]; };
@@ -245,7 +251,8 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
             q.epi.rowsum_dst = theta + y.b_off[l]; q.epi.rowsum_bstride = theta_stride;
             q.epi.rowsum_alpha = -lr; q.epi.rowsum_beta = 1.f;
         }
-        if (gemm_launch_grouped(g, y.L, s) != 0) return MAVG_E_LAUNCH;
+        const bool packed = packed_ws && gemm_packed_takes(g, y.L);
+        if ((packed ? gemm_launch_packed(g, y.L, packed_ws, w.packed_floats, s) : gemm_launch_grouped(g, y.L, s)) != 0) return MAVG_E_LAUNCH;
     } else {
         // the first minibatch (three folds from the initial state first) layer by layer; afterwards every layer
         // side in the same launches
@@ -265,6 +272,7 @@ extern "C" int32_t dnn_backward_update(const mavg_shape* shape, int32_t k, float
             a.mode = (flags & MAVG_NG_FIRST) ? 2 : (flags & MAVG_NG_APPLY_ONLY) ? 0 : 1;
             a.ws = ws + w.off_ng; a.ws_floats = w.ng_floats;
             a.gemm_ws = gws; a.gemm_ws_floats = w.gemm_floats;
+            a.packed_ws = packed_ws; a.packed_floats = packed_ws ? w.packed_floats : 0;
             if ((flags & MAVG_NG_FIRST) && ng_layer_update(a, s) != 0) return MAVG_E_LAUNCH;
         }
         if (!(flags & MAVG_NG_FIRST)) {

@@ -16,6 +16,8 @@
 //    than 32 steps, fused row sums of ragged operands).
 #include "gemm_device.h"
 #include "gemm_launchers.h"
+#include "gemm_packed.h"
+#include "packed.h"
 
 namespace mavg {
 
@@ -504,6 +506,126 @@ int gemm_launch_grouped(const GemmDesc* d, int count, hipStream_t stream, bool t
     return 0;
 }
 
+// ---- weight updates on packed operands ---------------------------------------------------------------
+
+// Scratch of one operand, in floats: its packed form (an operand that the replicas share is packed once), its columns' exponents.
+struct PackedOperand { int batch; int64_t floats, exps; };
+static PackedOperand packed_operand(int rows, int cols, int batch, int64_t bstride, int pieces) {
+    PackedOperand o;
+    o.batch = batch > 1 && bstride == 0 ? 1 : batch;
+    o.floats = ((int64_t)pieces * ((rows + 15) / 16) * 16 * cols + 63) / 64 * 64;
+    o.exps = (cols + 255) / 256 * 256;
+    return o;
+}
+constexpr int kPackWidthLeast = 16;      // columns per workgroup (see pack_kernel): partial sums of squares have room for that many
+int64_t gemm_packed_floats(int M, int N, int K, int batch, int pieces) {
+    const PackedOperand a = packed_operand(K, M, batch, 1, pieces), b = packed_operand(K, N, batch, 1, pieces);
+    return batch * (a.floats + a.exps + b.floats + b.exps) + (pieces > 1 ? (N / kPackWidthLeast + 64) / 64 * 64 : 0);
+}
+
+// From kSplitGroupedMinK steps on, where fp16 parts sum no less exactly than fp32 MFMAs, and where the launch that packs (5 - 9 us) is worth it:
+// large updates, whose time is the parameters' way through memory, and the products of long enough contractions.  Grouped launch that splits as it
+// goes / packed, us, both launches:
+//   440-6x2048-8000: 128 rows 116 / 82, 256 145 / 100, 512 202 / 175, 1024 338 / 295        640-3x2048-9000 at 80 rows: 61 / 57
+//   2048 x 2048: 128 rows 16.0 / 16.3, 200 21.7 / 19.2, 320 27.5 / 25.1, 512 38.6 / 30.0    1500 x 1500: 128 14.0 / 14.6, 200 18.8 / 17.1, 512 30.6 / 26.7
+//   440-512-512-1000: 200 10.7 / 14.2, 512 16.1 / 20.6, 1000 27.3 / 26.9                    440-6x512-9000: 128 22.5 / 25.9, 200 33.3 / 30.2
+//   429-3x1021-3003: 128 26.2 / 26.5, 200 31.6 / 27.5, 512 50.2 / 43.3                      512 x 4000 and 300 x 512: 512 22.9 / 23.6, 1000 40.0 / 32.9
+// Of two pieces (statistics of an RBM) packing replaces the launch for the visible bias: 440 x 2048 with 2 x 256 rows 22 / 18.
+bool gemm_packed_takes(const GemmDesc* d, int count, int pieces) {
+    double flop = 0;
+    int least = INT32_MAX;
+    for (int i = 0; i < count; ++i) {
+        if (d[i].a_kc || d[i].b_kc || d[i].epi.kind != EPI_AXPBY || !split_eligible(d[i])) return false;
+        if (d[i].K * pieces < least) least = d[i].K * pieces;
+        flop += 2.0 * d[i].M * d[i].N * d[i].K * pieces * d[i].batch;
+    }
+    if (count < 1 || least < kSplitGroupedMinK) return false;
+    return grouped_tiles128(d, count) >= 4 * kNumCU || (least >= 192 && flop >= (pieces > 1 ? 0.7e9 : 1.6e9));
+}
+
+// Tiles: 64x64 below one tile of 128x128 per compute unit (440 x 2048 at 512 rows 11.4 us, 64x128 14.8), 128x128 for long contractions in
+// many tiles (440-6x2048-8000: 512 rows 168 / 157 / 160, 768 270 / 204 / 197, 1000 366 / 252 / 240), 64x128 otherwise (three workgroups per
+// compute unit hide each other's update: 128 rows 77 / 72 / 80, 256 107 / 90 / 98).
+static int packed_shape(int K, int64_t tiles128) { return tiles128 < kNumCU ? 0 : K < 768 || tiles128 < 2 * kNumCU ? 1 : 2; }
+
+int gemm_launch_packed(const GemmDesc* d, int count, float* ws, int64_t ws_floats, hipStream_t stream, int tiles, const PackedPieces* pieces) {
+    const int npieces = pieces ? 2 : 1;
+    int64_t need = 0;
+    for (int i = 0; i < count; ++i) need += gemm_packed_floats(d[i].M, d[i].N, d[i].K, d[i].batch, npieces);
+    if (ws_floats < need || (pieces && (count != 1 || d[0].batch != 1))) return note_hip_error(hipErrorInvalidValue);
+    const int shape = tiles >= 0 ? tiles : packed_shape(d[0].K * npieces, grouped_tiles128(d, count));
+    for (int i0 = 0; i0 < count; i0 += kMaxGroups) {
+        PackedGroupParams gp;
+        PackGroupParams pk;
+        gp.ngroups = pk.ngroups = 0;
+        int ntiles = 0, most_rows = 0;
+        const int batch = d[i0].batch, end = count < i0 + kMaxGroups ? count : i0 + kMaxGroups;
+        // columns per packing workgroup: whole cache lines where that leaves a workgroup per compute unit
+        int64_t blocks64 = 0;
+        for (int i = i0; i < end; ++i) blocks64 += ((int64_t)(d[i].M + 63) / 64 + (d[i].N + 63) / 64) * d[i].batch;
+        const int width = blocks64 >= kNumCU ? 64 : blocks64 >= kNumCU / 2 ? 32 : kPackWidthLeast;
+        int blocks = 0;
+        for (int i = i0; i < end; ++i) {
+            const GemmDesc& di = d[i];
+            if (di.M <= 0 || di.N <= 0 || di.batch <= 0) continue;
+            if (di.a_kc || di.b_kc || di.batch != batch || di.epi.kind != EPI_AXPBY) return note_hip_error(hipErrorInvalidValue);
+            GemmPlan pl = gemm_plan_direct(di.M, di.N, di.K, di.batch, CFG_64, 1);
+            pl.bm = kPackedTiles[shape].bm; pl.bn = kPackedTiles[shape].bn;
+            PackedParams& q = gp.g[gp.ngroups];
+            q.g = fill_params(di, pl, nullptr);
+            q.kt = npieces * ((di.K + 15) / 16);
+            q.A2 = pieces ? pieces->A2 : nullptr; q.B2 = pieces ? pieces->B2 : nullptr;
+            q.lda2 = pieces ? pieces->lda2 : 0; q.ldb2 = pieces ? pieces->ldb2 : 0;
+            auto pack = [&](const float* src, int64_t ld, int64_t bstride, int cols, const char*& packed, int64_t& pstride, const int32_t*& exps, int64_t& estride) -> PackMatrix& {
+                const PackedOperand o = packed_operand(di.K, cols, di.batch, bstride, npieces);
+                PackMatrix& m = pk.g[pk.ngroups];
+                m = PackMatrix();
+                m.src = src; m.ld = ld; m.bstride = bstride;
+                m.dst = reinterpret_cast<char*>(ws); m.dst_bstride = o.floats * 4;
+                m.exps = reinterpret_cast<int32_t*>(ws + o.batch * o.floats); m.e_bstride = o.exps;
+                m.rows = di.K; m.cols = cols; m.batch = o.batch;
+                packed = m.dst; exps = m.exps;
+                pstride = o.batch == di.batch ? m.dst_bstride : 0; estride = o.batch == di.batch ? o.exps : 0;
+                ws += o.batch * (o.floats + o.exps);
+                pk.block_start[pk.ngroups++] = blocks;
+                blocks += (cols + width - 1) / width;
+                return m;
+            };
+            PackMatrix& ma = pack(di.A, di.lda, di.a_bstride, di.M, q.pa, q.pa_bstride, q.ea, q.e_bstride_a);
+            const Epilogue& e = di.epi;
+            if (e.rowsum_dst) {
+                ma.sum_dst = e.rowsum_dst; ma.sum_bstride = e.rowsum_bstride; ma.sum_alpha = e.rowsum_alpha; ma.sum_beta = e.rowsum_beta;
+                ma.sum_dst2 = e.rowsum_dst2; ma.sum2_bstride = e.rowsum2_bstride;
+                ma.sum_w = e.rowsum_w; ma.sum_w_bstride = e.rowsum_w_bstride;
+                ma.alpha_dev0 = e.alpha_dev0; ma.alpha_dev1 = e.alpha_dev1;
+            }
+            PackMatrix& mb = pack(di.B, di.ldb, di.b_bstride, di.N, q.pb, q.pb_bstride, q.eb, q.e_bstride_b);
+            if (pieces) {
+                ma.src2 = pieces->A2; ma.ld2 = pieces->lda2; ma.sum_sign2 = 1.f;
+                mb.src2 = pieces->B2; mb.ld2 = pieces->ldb2; mb.sum_sign2 = -1.f;
+                mb.sum_dst = pieces->diff_dst; mb.sum_alpha = pieces->diff_alpha; mb.sum_beta = pieces->diff_beta; mb.sum_dst2 = pieces->diff_dst2;
+                if (pieces->square_dst) {
+                    mb.sq_partial = ws;
+                    q.g.epi.side_sum_src = ws; q.g.epi.side_sum_dst = pieces->square_dst; q.g.epi.side_sum_n = (di.N + width - 1) / width;
+                }
+            }
+            gp.tile_start[gp.ngroups++] = ntiles;
+            ntiles += q.g.tiles_m * q.g.tiles_n;
+            if (di.K > most_rows) most_rows = di.K;
+        }
+        if (gp.ngroups == 0) continue;
+        gp.tile_start[gp.ngroups] = ntiles;
+        pk.block_start[pk.ngroups] = blocks;
+        launch_pack(pk, width, npieces, most_rows, dim3((unsigned)blocks, (unsigned)batch), stream);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return note_hip_error(e);
+        launch_grouped_packed(gp, shape, dim3((unsigned)ntiles, 1, (unsigned)batch), stream);
+        e = hipGetLastError();
+        if (e != hipSuccess) return note_hip_error(e);
+    }
+    return 0;
+}
+
 }  // namespace mavg
 
 static thread_local hipError_t g_last_error = hipSuccess;
@@ -596,6 +718,28 @@ extern "C" int32_t mavg_gemm_grouped_parts(const mavg_gemm_problem* pr, int32_t 
     if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_BY_DATA || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
     for (int i = 0; i < count; ++i) { g[i].parts = (SplitParts)parts; g[i].a_exp = a_exp; g[i].b_exp = b_exp; }
     return gemm_launch_grouped(g, count, static_cast<hipStream_t>(stream)) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
+}
+
+extern "C" int64_t mavg_gemm_grouped_packed_bytes(const mavg_gemm_problem* pr, int32_t count) {
+    GemmDesc g[kMaxGroups];
+    const int32_t rc = grouped_descs(pr, count, 0, 0, g);
+    if (rc) return rc;
+    int64_t f = 0;
+    for (int i = 0; i < count; ++i) f += gemm_packed_floats(g[i].M, g[i].N, g[i].K, 1);
+    return f * 4 + 256;
+}
+
+extern "C" int32_t mavg_gemm_grouped_packed(const mavg_gemm_problem* pr, int32_t count, int32_t tiles, void* workspace, int64_t workspace_bytes, void* stream) {
+    GemmDesc g[kMaxGroups];
+    const int32_t rc = grouped_descs(pr, count, 0, 0, g);
+    if (rc) return rc;
+    if (tiles < -1 || tiles >= kPackedShapes) return MAVG_E_FLAG;
+    for (int i = 0; i < count; ++i)
+        if (g[i].K < 1 || g[i].epi.kind != EPI_AXPBY) return MAVG_E_FLAG;
+    const int64_t need = mavg_gemm_grouped_packed_bytes(pr, count);
+    if (!workspace || workspace_bytes < need) return MAVG_E_WORKSPACE;
+    float* ws = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(workspace) + 255u) & ~uintptr_t(255));
+    return gemm_launch_packed(g, count, ws, need / 4 - 64, static_cast<hipStream_t>(stream), tiles) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
 }
 
 extern "C" int32_t mavg_gemm_grouped_kernel(const mavg_gemm_problem* pr, int32_t count, int32_t a_kc, int32_t b_kc, int32_t which) {

@@ -18,6 +18,7 @@ struct NgLayerArgs {
     int mode;                                           // 0 apply only, 1 apply + fold, 2 first minibatch (three folds first)
     float* ws; int64_t ws_floats;
     float* gemm_ws; int64_t gemm_ws_floats;
+    float* packed_ws; int64_t packed_floats;            // for the operands of the weight updates of all layers, packed (null: there is no room)
 };
 
 // float32 elements of scratch ng_layer_update needs for the widest layer of the network

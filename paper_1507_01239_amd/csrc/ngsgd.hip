@@ -21,6 +21,7 @@
 #include "../../include/mavg.h"
 #include "device_math.h"
 #include "gemm.h"
+#include "packed.h"
 #include "kernels.h"
 #include "ng_internal.h"
 
@@ -1529,7 +1530,8 @@ int ng_dnn_update(const NgLayerArgs* layers, int L, char* ng_state, int64_t stat
                 q.epi.rowsum_dst = a.b; q.epi.rowsum_bstride = a.theta_stride; q.epi.rowsum_alpha = -a.lr; q.epi.rowsum_beta = 1.f;
                 q.epi.rowsum_w = t.wcol + (int64_t)(2 * i) * k * n; q.epi.rowsum_w_bstride = n;
             }
-            NG_CHECK(gemm_launch_grouped(g, nl, s));
+            if (a0.packed_ws && gemm_packed_takes(g, nl)) NG_CHECK(gemm_launch_packed(g, nl, a0.packed_ws, a0.packed_floats, s));
+            else NG_CHECK(gemm_launch_grouped(g, nl, s));
         }
     }
     if (side) NG_CHECK(note_hip_error(hipStreamWaitEvent(s, side->ev[2], 0)));

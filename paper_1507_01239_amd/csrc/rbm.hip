@@ -11,6 +11,7 @@
 
 #include "../../include/mavg.h"
 #include "gemm.h"
+#include "packed.h"
 #include "kernels.h"
 #include "device_math.h"
 
@@ -24,7 +25,15 @@ inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 struct RbmWs {
     int64_t ldh, ldv;
     int64_t off_ph, off_h0, off_vv, off_part, off_gemm, gemm_floats, total;     // ph: [P_h0; -P_h1], vv: [V0; V1], 2n rows each
+    int64_t packed_floats;      // behind all that: ph and vv packed (calls with less scratch do without)
 };
+
+// Does the statistics product run on packed operands (where there is room for them)?
+bool packed_statistics(int V, int H, int n) {
+    GemmDesc g;
+    g.M = H; g.N = V; g.K = n; g.a_kc = g.b_kc = false; g.lda = H; g.ldb = V; g.epi.kind = EPI_AXPBY;
+    return gemm_packed_takes(&g, 1, 2);
+}
 
 RbmWs rbm_ws(int V, int H, int n) {
     RbmWs w;
@@ -41,6 +50,9 @@ RbmWs rbm_ws(int V, int H, int n) {
     w.off_part = off; off += round_up(colsum_blocks(V), 64);
     w.off_gemm = off; off += w.gemm_floats;
     w.total = off;
+    // (not where it would take a step beyond the static scratch that fits it otherwise: both entry points give the same bits)
+    const int64_t packed = gemm_packed_floats(H, V, n, 1, 2), limit = MAVG_RBM_STATIC_SCRATCH_BYTES / 4;
+    w.packed_floats = packed_statistics(V, H, n) && (off + packed <= limit || off > limit) ? packed : 0;
     return w;
 }
 
@@ -52,7 +64,8 @@ float* ws_base(void* workspace) {
 
 extern "C" int64_t rbm_workspace_bytes(int32_t n_vis, int32_t n_hid, int32_t n) {
     if (n_vis < 1 || n_hid < 1 || n < 1) return MAVG_E_DIM;
-    return rbm_ws(n_vis, n_hid, n).total * 4 + 256;
+    const RbmWs w = rbm_ws(n_vis, n_hid, n);
+    return (w.total + w.packed_floats) * 4 + 256;
 }
 
 // Where rbm_cd1_step leaves its intermediate matrices: byte offsets from the 256-byte aligned workspace base and row
@@ -102,11 +115,11 @@ int cd1_check(int32_t V, int32_t H, int32_t vis_type, const float* w, const floa
     return MAVG_OK;
 }
 
-// The launches of one CD-1 step; ws: 256-byte aligned scratch of rbm_ws(V, H, n).total floats, contents undefined on
+// The launches of one CD-1 step; ws: 256-byte aligned scratch of rbm_ws(V, H, n).total floats (packed: and packed_floats more), contents undefined on
 // entry (every element that a stored result depends on is written before it is read).
 int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, float* c, float* mw, float* ma, float* mc,
                 const float* v0, int32_t n, float lr, float momentum, uint64_t seed, uint32_t step, uint32_t layer,
-                uint32_t flags, float* recon_err, const RbmWs& lay, float* ws, hipStream_t s) {
+                uint32_t flags, float* recon_err, const RbmWs& lay, bool packed, float* ws, hipStream_t s) {
     float* ph0 = ws + lay.off_ph;                       // rows 0..n-1 of the stacked hidden statistics
     float* ph1 = ph0 + (int64_t)n * lay.ldh;            // rows n..2n-1, stored NEGATED
     float* h0 = ws + lay.off_h0;
@@ -153,6 +166,24 @@ int32_t cd1_run(int32_t V, int32_t H, int32_t vis_type, float* w, float* a, floa
         g.epi.kind = EPI_BIAS_SIGMOID; g.epi.bias = c; g.epi.alpha = -1.f;
         if (gemm_launch(g, gws, lay.gemm_floats, s) != 0) return MAVG_E_LAUNCH;
     }
+    if (packed) {
+        // the statistics' updates as below, their operands packed in two pieces each by a launch that does the visible bias and the squared error too
+        GemmDesc g;
+        g.M = H; g.N = V; g.K = n;
+        g.A = ph0; g.lda = lay.ldh; g.a_kc = false;
+        g.B = v0; g.ldb = V; g.b_kc = false;
+        g.C = mw; g.ldc = V;
+        g.epi.kind = EPI_AXPBY; g.epi.alpha = lr * invn; g.epi.beta = momentum;
+        g.epi.C2 = w; g.epi.ldc2 = V;
+        g.epi.rowsum_dst = mc; g.epi.rowsum_alpha = lr * invn; g.epi.rowsum_beta = momentum;
+        g.epi.rowsum_dst2 = c;
+        PackedPieces two;
+        two.A2 = ph1; two.lda2 = lay.ldh;
+        two.B2 = v1; two.ldb2 = lay.ldv;
+        two.diff_dst = ma; two.diff_alpha = lr * invn; two.diff_beta = momentum; two.diff_dst2 = a;
+        two.square_dst = recon_err;
+        return gemm_launch_packed(&g, 1, ws + lay.total, lay.packed_floats, s, -1, &two) == 0 ? MAVG_OK : MAVG_E_LAUNCH;
+    }
     // Ma <- momentum Ma + (lr/n) colsum(V0 - V1); a <- a + Ma;  the same pass copies V0 under V1's rows' stride
     // and leaves the squared reconstruction error of each block of 32 columns (summed in block order by the launch below)
     if (colsum_axpby_launch(v0, V, v1, lay.ldv, ma, a, vv, lay.ldv, recon_err ? ws + lay.off_part : nullptr, n, V, lr * invn,
@@ -188,7 +219,8 @@ extern "C" int32_t rbm_cd1_step(int32_t V, int32_t H, int32_t vis_type, float* w
     if (rc) return rc;
     const RbmWs lay = rbm_ws(V, H, n);
     if (!workspace || workspace_bytes < lay.total * 4 + 256) return MAVG_E_WORKSPACE;
-    return cd1_run(V, H, vis_type, w, a, c, mw, ma, mc, v0, n, lr, momentum, seed, step, layer, flags, recon_err, lay,
+    const bool packed = lay.packed_floats > 0 && workspace_bytes >= (lay.total + lay.packed_floats) * 4 + 256;
+    return cd1_run(V, H, vis_type, w, a, c, mw, ma, mc, v0, n, lr, momentum, seed, step, layer, flags, recon_err, lay, packed,
                    ws_base(workspace), static_cast<hipStream_t>(stream));
 }
 
@@ -230,7 +262,8 @@ extern "C" int32_t rbm_cd1_step_static(int32_t V, int32_t H, int32_t vis_type, f
     if (lay.total * 4 > kStaticScratchBytes) return MAVG_E_WORKSPACE;       // before anything touches the device
     float* ws = static_scratch();
     if (!ws) return MAVG_E_LAUNCH;
-    return cd1_run(V, H, vis_type, w, a, c, mw, ma, mc, v0, n, lr, momentum, seed, step, layer, flags, recon_err, lay, ws,
+    const bool packed = lay.packed_floats > 0 && (lay.total + lay.packed_floats) * 4 <= kStaticScratchBytes;
+    return cd1_run(V, H, vis_type, w, a, c, mw, ma, mc, v0, n, lr, momentum, seed, step, layer, flags, recon_err, lay, packed, ws,
                    static_cast<hipStream_t>(stream));
 }
 
