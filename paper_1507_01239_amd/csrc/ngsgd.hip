@@ -178,27 +178,33 @@ __device__ __forceinline__ double fast_rsqrt(double x) {
     return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
+// The value of the lane that differs in the lowest bit.
+__device__ __forceinline__ double neighbour(double x) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, 0xb1, 0xf, 0xf, true);      // quad_perm [1, 0, 3, 2]
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), 0xb1, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 // Symmetric eigen-decomposition of the rank x rank matrix Z by cyclic Jacobi rotations in a round-robin
 // (tournament) order, so that the rank/2 disjoint rotations of a round are applied in parallel, rows and
-// columns in one pass (the column partner's entries come from a neighbouring lane); then the
-// new d, rho, t and the matrix Wt = diag(c)^-1/2 U^T (rows in descending order of c).
+// columns in one pass; then the new d, rho, t and the matrix Wt = diag(c)^-1/2 U^T (rows in descending order of c).
 //
-// An odd rank gets one more, zero row and column (never rotated: its entries are zero), which makes m indices.  Threads
-// form groups of LW lanes (32; 64 above rank 32), lane l standing for index l of the matrix.  In round `rd` of the
-// tournament index m-1 meets index rd and every other index l meets (2 rd - l) mod (m - 1).  Every lane works out
-// the rotation of its own index's pair from the three entries it depends on (all groups do so redundantly: no
+// An odd rank gets one more, zero row and column (never rotated: its entries are zero), which makes m indices.  In a round the
+// indices at places 2 k and 2 k + 1 meet; what a round writes, it writes where the next one has it: place 0 keeps its index, the other
+// even places' indices move up, the odd ones' down, and after m - 1 rounds every index has met every other one and is back.  So
+// every address is fixed for the whole kernel (both copies at fixed distances: they go into the instructions), and the column partner
+// is the neighbouring lane.  Threads form groups of LW lanes (32; 64 above rank 32), lane l standing for the index at place l.  Every
+// lane works out the rotation of its own index's pair from the three entries it depends on (all groups do so redundantly: no
 // hand-over through LDS, no barrier between computing the rotations and applying them); the group that owns a pair's
-// two rows takes that pair's rotation from its lane p.  Z and U^T are kept twice: a round reads one copy and writes the
-// other (every row belongs to exactly one pair and is written once per round), so a wavefront that is ahead never
-// overwrites what a slower one still has to read, and one barrier per round is enough.
+// two rows takes that pair's rotation from its lane 2 k.  Z and U^T are kept twice: a round reads one copy and writes the
+// other, so a wavefront that is ahead never overwrites what a slower one still has to read, and one barrier per round is enough.
 //
-// What bounds it: one workgroup per matrix and some 120 to 200 rounds, each a chain of LDS reads, the rotation's float64
-// operations, a lane exchange, the products, LDS writes and the barrier.  So everything a round reads from LDS is
-// requested at once, the partner's column entries among it; the next round's addresses are worked out while those reads
-// are on their way (fixed row stride, both copies at fixed distances: they go into the instructions); the rotation needs
-// two reciprocal square roots and nothing else; up to rank 32 one wavefront per SIMD, because the part that every wavefront
-// repeats is half of what it issues (rank 30: 85 against 104 us for 512 threads; above rank 32 the pairs are many enough for
-// 512, rank 40: 260 against 322).  Four sweeps at rank 30: 86 us, was 117; rank 40: 260, was 296; rank 64: 575, was 815.
+// What bounds it: one workgroup per matrix and some 90 to 200 rounds, each a chain of LDS reads, the rotation's float64
+// operations, a lane exchange, the products, LDS writes and the barrier, and the instructions that every wavefront repeats: the rotation
+// needs two reciprocal square roots and nothing else; up to rank 32 one wavefront per SIMD (rank 30: 85 against 104 us for 512
+// threads; above rank 32 the pairs are many enough for 512, rank 40: 260 against 322).  A round took 1640 cycles when the pairs were those of
+// the tournament's indices and a third of its instructions worked out where they are.
 template <int LW> constexpr int kEigLd = LW + 2;       // even: the diagonal (an odd number of doubles apart) spreads over all LDS banks
 template <int LW> constexpr int kEigMat = LW * kEigLd<LW>;
 template <int LW>
@@ -223,88 +229,76 @@ __global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb,
             smem[2 * MAT + i * LD + lane] = i == lane ? 1.0 : 0.0;
         }
     __syncthreads();
-    // Element offsets of what this thread reads in a round.  (Lanes past the matrix stand for its last column and groups
-    // past the last pair for the first one; neither writes.)
-    const int lc = min(lane, m - 1);
-    int pp, qq, pq;                                   // (p, p), (q, q), (p, q) of the pair of this lane's index
-    int lp[KPG], pr[KPG], qr[KPG], partner;           // lane p, rows p and q of the group's pairs; the index met
-    auto pairing = [&](int round) {
-        int w = 2 * round - lc;                       // in (-(m-1), 2(m-1)): reduce mod m-1 without a division
-        if (w < 0) w += m - 1;
-        if (w >= m - 1) w -= m - 1;
-        partner = lc == m - 1 ? round : lc == round ? m - 1 : w;
-        const int p = min(lc, partner), q = max(lc, partner);
-        pp = p * (LD + 1);
-        qq = q * (LD + 1);
-        pq = p * LD + q;
-#pragma unroll
-        for (int i = 0; i < KPG; ++i) {
-            const int k = grp + i * NG;
-            int u = round + k, v = round - k;
-            if (u >= m - 1) u -= m - 1;
-            if (v < 0) v += m - 1;
-            const bool first = k == 0 || k >= half;
-            u = first ? m - 1 : u;
-            v = first ? round : v;
-            lp[i] = min(u, v);
-            pr[i] = lp[i] * LD;
-            qr[i] = max(u, v) * LD;
-        }
+    // Element offsets of what this thread reads and writes in a round.  (Lanes past the matrix stand for its last column and groups
+    // past the last pair for the last one; neither writes.)
+    const int lc = min(lane, m - 1), own = lc & ~1;
+    const int pp = own * (LD + 1), qq = pp + LD + 1, pq = pp + 1;      // of the pair of this lane's index
+    auto moved = [&](int at) {                        // where the tournament's next round has the index at place `at`
+        if (at == 0) return 0;
+        if (at & 1) return at == 1 ? (m > 2 ? 2 : 1) : at - 2;
+        return at == m - 2 ? m - 1 : at + 2;
     };
+    const int col_to = moved(lc);
+    int at_p[KPG], to_p[KPG], to_q[KPG], ut_p[KPG], ut_q[KPG], from[KPG];
+    bool mine[KPG];
+#pragma unroll
+    for (int i = 0; i < KPG; ++i) {
+        const int k = grp + i * NG, p = 2 * min(k, half - 1);
+        mine[i] = on && k < half;
+        from[i] = p;
+        at_p[i] = p * LD + lc;
+        to_p[i] = moved(p) * LD;
+        to_q[i] = moved(p + 1) * LD;
+        ut_p[i] = to_p[i] + lc;
+        ut_q[i] = to_q[i] + lc;
+        to_p[i] += col_to;
+        to_q[i] += col_to;
+    }
     // One round, from copy CUR to the other one: Z <- J^T Z J, U^T <- J^T U^T with, for every pair (p, q), p < q,
-    // row_p <- c row_p - s row_q,  row_q <- s row_p + c row_q  (and the same for the columns of Z)
-    auto rotate = [&](auto curc, int next_round) {
+    // row_p <- c row_p - s row_q,  row_q <- s row_p + c row_q  (and the same for the columns of Z), written to where the next round has them
+    auto rotate = [&](auto curc) {
         constexpr int CUR = decltype(curc)::value;
         const double* Z = smem + CUR * MAT;
         const double* U = smem + (2 + CUR) * MAT;
         double* Zn = smem + (1 - CUR) * MAT;
         double* Un = smem + (3 - CUR) * MAT;
         const double app = Z[pp], aqq = Z[qq], apq = Z[pq];
-        double zp[KPG], zq[KPG], zpo[KPG], zqo[KPG], up[KPG], uq[KPG];
-        int at_p[KPG], at_q[KPG], from[KPG];
-        const bool low = lc < partner;
+        double zp[KPG], zq[KPG], up[KPG], uq[KPG];
 #pragma unroll
         for (int i = 0; i < KPG; ++i) {
-            at_p[i] = pr[i] + lc;
-            at_q[i] = qr[i] + lc;
-            from[i] = lp[i];
-            zp[i] = Z[at_p[i]];            zq[i] = Z[at_q[i]];
-            zpo[i] = Z[pr[i] + partner];   zqo[i] = Z[qr[i] + partner];
-            up[i] = U[at_p[i]];            uq[i] = U[at_q[i]];
+            zp[i] = Z[at_p[i]];   zq[i] = Z[at_p[i] + LD];
+            up[i] = U[at_p[i]];   uq[i] = U[at_p[i] + LD];
         }
         __builtin_amdgcn_sched_barrier(0);
-        pairing(next_round);
         // c^2 = (1 + |d| / h) / 2, s = sgn(d) b2 / (2 h c) with d = aqq - app, b2 = 2 apq, h = sqrt(d^2 + b2^2): the
         // rotation by the smaller angle
-        double cl = 1.0, sl = 0.0;                    // rotation of the pair this lane's index is in
         const double d = aqq - app, b2 = 2.0 * apq;
         const double h2 = d * d + b2 * b2;
-        if (apq != 0.0 && h2 > 1e-280) {              // (below that the entry is nothing against any diagonal)
-            const double ih = fast_rsqrt(h2);
-            const double u = 0.5 + 0.5 * fabs(d) * ih;
-            const double iu = fast_rsqrt(u);
-            cl = u * iu;
-            sl = (d >= 0.0 ? 0.5 : -0.5) * b2 * ih * iu;
-        }
+        const bool turn = apq != 0.0 && h2 > 1e-280;  // (below that the entry is nothing against any diagonal)
+        const double ih = fast_rsqrt(h2);
+        const double u = 0.5 + 0.5 * fabs(d) * ih;
+        const double iu = fast_rsqrt(u);
+        const double cl = turn ? u * iu : 1.0;        // rotation of the pair this lane's index is in
+        const double sl = turn ? (d >= 0.0 ? 0.5 : -0.5) * b2 * ih * iu : 0.0;
         // column `lane` turns into cl column_lane + bl column_partner
-        const double bl = low ? -sl : sl;
-        double c[KPG], s[KPG];
+        const double bl = lc & 1 ? sl : -sl;
+        double c[KPG], sn[KPG];
 #pragma unroll
-        for (int i = 0; i < KPG; ++i) { c[i] = __shfl(cl, from[i], LW); s[i] = __shfl(sl, from[i], LW); }
+        for (int i = 0; i < KPG; ++i) { c[i] = __shfl(cl, from[i], LW); sn[i] = __shfl(sl, from[i], LW); }
 #pragma unroll
         for (int i = 0; i < KPG; ++i) {
-            const double wp = c[i] * zp[i] - s[i] * zq[i], wq = s[i] * zp[i] + c[i] * zq[i];
-            const double wpo = c[i] * zpo[i] - s[i] * zqo[i], wqo = s[i] * zpo[i] + c[i] * zqo[i];
-            if (on && grp + i * NG < half) {
-                Zn[at_p[i]] = cl * wp + bl * wpo;
-                Zn[at_q[i]] = cl * wq + bl * wqo;
-                Un[at_p[i]] = c[i] * up[i] - s[i] * uq[i];
-                Un[at_q[i]] = s[i] * up[i] + c[i] * uq[i];
+            const double wp = c[i] * zp[i] - sn[i] * zq[i], wq = sn[i] * zp[i] + c[i] * zq[i];
+            const double vp = c[i] * up[i] - sn[i] * uq[i], vq = sn[i] * up[i] + c[i] * uq[i];
+            const double np = cl * wp + bl * neighbour(wp), nq = cl * wq + bl * neighbour(wq);
+            if (mine[i]) {
+                Zn[to_p[i]] = np;
+                Zn[to_q[i]] = nq;
+                Un[ut_p[i]] = vp;
+                Un[ut_q[i]] = vq;
             }
         }
         __syncthreads();
     };
-    pairing(0);
     int sweeps_done = 0, cur = 0;
     bool converged = false;
     for (int sweep = 0; sweep <= kJacobiSweeps; ++sweep) {
@@ -331,10 +325,9 @@ __global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb,
         if (off <= 1e-26 * dg) { converged = true; break; }
         if (sweep == kJacobiSweeps) break;          // out of sweeps: the state's info word counts it
         ++sweeps_done;
-        for (int round = 0; round < m - 1; ++round) {
-            const int next = round + 1 < m - 1 ? round + 1 : 0;
-            if (cur == 0) rotate(std::integral_constant<int, 0>{}, next);
-            else rotate(std::integral_constant<int, 1>{}, next);
+        for (int round = 0; round < m - 1; ++round) {      // (after which every index is back at its place)
+            if (cur == 0) rotate(std::integral_constant<int, 0>{});
+            else rotate(std::integral_constant<int, 1>{});
             cur ^= 1;
         }
     }
