@@ -18,6 +18,8 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "../../include/mavg.h"
 #include "device_math.h"
 #include "gemm.h"
@@ -105,8 +107,8 @@ __device__ __forceinline__ double block_sum_d(double v, double* sh) {
     return r;
 }
 
-// the eigen-solver runs 256 threads in groups of 32 lanes, above rank 32 512 threads in groups of 64 lanes
-template <int LW> constexpr int kEigThreads = LW == 32 ? 256 : 512;
+// the eigen-solver runs 512 threads in groups of 32 lanes, above rank 32 1024 threads in groups of 64 lanes
+template <int LW> constexpr int kEigThreads = LW == 32 ? 512 : 1024;
 constexpr int kEigSoloLds = 120 * 1024;      // bytes of LDS a solver workgroup asks for to have its compute unit to itself
 constexpr int kEigSoloMax = 64;              // ... in launches of at most this many workgroups
 // Table of independent folds finished by one launch of each of ng_z_kernel / ng_eig_kernel / ng_newr_kernel:
@@ -148,11 +150,20 @@ __global__ __launch_bounds__(256) void ng_scale_kernel(float* __restrict__ x, in
     }
 }
 
-// Z = Y Y^T in float64; one workgroup per (i <= j)
+// Z = Y Y^T in float64; one workgroup per (i <= j).  With `part` the launch has one more workgroup per state, which sums the `nparts`
+// shares of ||X||^2 of a table of one slot in index order.
 template <typename YT>
-__global__ __launch_bounds__(256) void ng_z_kernel(NgFoldTable tb, int rank, double* __restrict__ Z) {
+__global__ __launch_bounds__(256) void ng_z_kernel(NgFoldTable tb, int rank, double* __restrict__ Z, const double* __restrict__ part, int nparts,
+                                                   double* __restrict__ scal) {
     __shared__ double sh[4];
     const int slot = blockIdx.y, b = blockIdx.z;
+    if (part != nullptr && (int)blockIdx.x == rank * rank) {
+        double s = 0.0;
+        for (int i = threadIdx.x; i < nparts; i += 256) s += part[i];
+        s = block_sum_d(s, sh);
+        if (threadIdx.x == 0) scal[0] = s;
+        return;
+    }
     const int i = blockIdx.x / rank, j = blockIdx.x - i * rank;
     if (i > j) return;
     const int dim = tb.dim[slot];
@@ -201,16 +212,15 @@ __device__ __forceinline__ double neighbour(double x) {
 // other, so a wavefront that is ahead never overwrites what a slower one still has to read, and one barrier per round is enough.
 //
 // What bounds it: one workgroup per matrix and some 90 to 200 rounds, each a chain of LDS reads, the rotation's float64
-// operations, a lane exchange, the products, LDS writes and the barrier, and the instructions that every wavefront repeats: the rotation
-// needs two reciprocal square roots and nothing else; up to rank 32 one wavefront per SIMD (rank 30: 85 against 104 us for 512
-// threads; above rank 32 the pairs are many enough for 512, rank 40: 260 against 322).  A round took 1640 cycles when the pairs were those of
-// the tournament's indices and a third of its instructions worked out where they are.
+// operations (two reciprocal square roots and nothing else), a lane exchange, the products, LDS writes and the barrier; 1000 cycles a
+// round at rank 30 (1640 when the pairs were those of the tournament's indices and a third of a round's instructions worked out where they
+// are).  Five sweeps at rank 30: 72 us (256 threads 78; before 122); preconditioning two minibatches, us, before / now: rank 20 267 / 239,
+// rank 40 792 / 685 (512 threads 693), rank 64 1471 / 1192 (1220).
 template <int LW> constexpr int kEigLd = LW + 2;       // even: the diagonal (an odd number of doubles apart) spreads over all LDS banks
 template <int LW> constexpr int kEigMat = LW * kEigLd<LW>;
-template <int LW>
-__global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb, int rank, int n, float eta, const double* __restrict__ Zg,
-                                                     double* __restrict__ Wt, int bump_t) {
-    extern __shared__ double smem[];
+template <int LW, int NT>
+__device__ __forceinline__ void ng_eig_body(const NgFoldTable& tb, int rank, int n, float eta, const double* __restrict__ Zg,
+                                            double* __restrict__ Wt, int bump_t, double* smem) {
     constexpr int LD = kEigLd<LW>, MAT = kEigMat<LW>;
     const int r = rank, m = (r + 1) & ~1, half = m / 2;
     // Z at 0 and MAT, U^T (row k = eigenvector k, so its update is a row rotation) at 2 MAT and 3 MAT
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb,
     const int dim = tb.dim[slot];
     const int64_t zi = (int64_t)(tb.first + slot) * tb.batch + b;
     const double* __restrict__ Zb = Zg + zi * kMaxRank * kMaxRank;
-    constexpr int NT = kEigThreads<LW>, NG = NT / LW, KPG = LW / 2 / NG;       // groups; pairs of a round per group
+    constexpr int NG = NT / LW, KPG = LW / 2 / NG;       // groups; pairs of a round per group
     const int lane = tid & (LW - 1), grp = tid / LW;
     const bool on = lane < m;
     if (on)
@@ -311,14 +321,12 @@ __global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb,
             }
         off = wave_sum(off);
         dg = wave_sum(dg);
-        if ((tid & 63) == 0) { red[tid >> 6] = off; red[8 + (tid >> 6)] = dg; }
+        constexpr int NW = NT / 64;
+        if ((tid & 63) == 0) { red[tid >> 6] = off; red[NW + (tid >> 6)] = dg; }
         __syncthreads();
-        off = (red[0] + red[1]) + (red[2] + red[3]);
-        dg = (red[8] + red[9]) + (red[10] + red[11]);
-        if constexpr (NT == 512) {
-            off += (red[4] + red[5]) + (red[6] + red[7]);
-            dg += (red[12] + red[13]) + (red[14] + red[15]);
-        }
+        off = dg = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { off += red[w]; dg += red[NW + w]; }
         __syncthreads();
         // off-diagonal norm below 1e-13 of the diagonal: Z spans many orders of magnitude, and a looser stop (1e-10)
         // leaves its small eigenvalues, hence the weak rows of R, outside the parity tolerance
@@ -374,10 +382,16 @@ __global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb,
         Wb[w] = Us[order[i] * LD + k] / red[i];
     }
 }
+template <int LW>
+__global__ __launch_bounds__(kEigThreads<LW>) void ng_eig_kernel(NgFoldTable tb, int rank, int n, float eta, const double* __restrict__ Zg,
+                                                     double* __restrict__ Wt, int bump_t) {
+    extern __shared__ double smem[];
+    ng_eig_body<LW, kEigThreads<LW>>(tb, rank, n, eta, Zg, Wt, bump_t, smem);
+}
 
 // R' = Wt Y (float64 accumulation).  A workgroup owns 32 columns; its 8 thread rows each produce every 8th row of R'.
 template <typename YT>
-__global__ __launch_bounds__(256) void ng_newr_kernel(NgFoldTable tb, int rank, const double* __restrict__ Wt) {
+__device__ __forceinline__ void ng_newr_body(const NgFoldTable& tb, int rank, const double* __restrict__ Wt) {
     __shared__ double Ws[kMaxRank * kMaxRank];
     __shared__ YT ys[kMaxRank][33];
     const int slot = blockIdx.y, b = blockIdx.z;
@@ -398,6 +412,10 @@ __global__ __launch_bounds__(256) void ng_newr_kernel(NgFoldTable tb, int rank, 
         for (int k = 0; k < rank; ++k) acc += Ws[i * rank + k] * (double)ys[k][tx];
         R[(int64_t)i * ld + c] = (c < dim) ? (float)acc : 0.f;
     }
+}
+template <typename YT>
+__global__ __launch_bounds__(256) void ng_newr_kernel(NgFoldTable tb, int rank, const double* __restrict__ Wt) {
+    ng_newr_body<YT>(tb, rank, Wt);
 }
 
 // Float64 versions of H = X R^T and Y = (eta/n) H^T X + (1-eta)(diag(d)+rho I) R for the folds that start from the
@@ -492,7 +510,8 @@ struct NgSlots {
     float* wcol = nullptr;                      // optional, at + q * n: receives the last column of the preconditioned matrix
 };
 
-__global__ __launch_bounds__(256) void ng_sumsq_partial_slots_kernel(NgSlots t, int write_lastcol) {
+// (by workgroup `block` of `nblocks`)
+__device__ __forceinline__ void ng_sumsq_partial(const NgSlots& t, int write_lastcol, int block, int nblocks) {
     __shared__ double sh[4];
     const int slot = blockIdx.y, b = blockIdx.z;
     const int64_t q = (int64_t)slot * t.batch + b;
@@ -501,7 +520,7 @@ __global__ __launch_bounds__(256) void ng_sumsq_partial_slots_kernel(NgSlots t, 
     const int dim = t.dim[slot], n = t.n;
     const bool vec = (ldx & 3) == 0 && (t.x_b[slot] & 3) == 0 && (reinterpret_cast<uintptr_t>(t.x[slot]) & 15u) == 0;
     double s = 0.0;
-    for (int r = blockIdx.x; r < n; r += gridDim.x) {
+    for (int r = block; r < n; r += nblocks) {
         const float* __restrict__ row = xb + (int64_t)r * ldx;
         if (write_lastcol && threadIdx.x == 0) t.wcol[q * n + r] = row[dim - 1];
         float a = 0.f;
@@ -529,7 +548,10 @@ __global__ __launch_bounds__(256) void ng_sumsq_partial_slots_kernel(NgSlots t, 
         s += (double)a;
     }
     s = block_sum_d(s, sh);
-    if (threadIdx.x == 0) t.part[q * kNgParts + blockIdx.x] = s;
+    if (threadIdx.x == 0) t.part[q * kNgParts + block] = s;
+}
+__global__ __launch_bounds__(256) void ng_sumsq_partial_slots_kernel(NgSlots t, int write_lastcol) {
+    ng_sumsq_partial(t, write_lastcol, blockIdx.x, gridDim.x);
 }
 
 // The coefficients of the apply and the fold of (slot, replica b) from its state: e, (1 - eta)(d + rho), 1 - e.
@@ -577,8 +599,8 @@ __global__ __launch_bounds__(256) void ng_sumsq_final_slots_kernel(NgSlots t, in
 struct NgChunkTable { int first[kNgSlots], count[kNgSlots]; };
 // combine != 0 (Hout = t.H2): what is left is H (I - E) - (that sum) in the columns below the rank, the combination
 // the second rank update multiplies by R
-__global__ __launch_bounds__(256) void ng_sum_chunks_slots_kernel(NgSlots t, NgChunkTable ct, const float* __restrict__ P,
-                                                                  float* __restrict__ Hout, int combine) {
+__device__ __forceinline__ void ng_sum_chunks(const NgSlots& t, const NgChunkTable& ct, const float* __restrict__ P, float* __restrict__ Hout,
+                                              int combine, int block, int nblocks) {
     const int slot = blockIdx.y, b = blockIdx.z;
     const int64_t q = (int64_t)slot * t.batch + b;
     const int64_t total4 = (int64_t)t.n * t.ldr / 4;            // ldr is a multiple of 4
@@ -586,7 +608,7 @@ __global__ __launch_bounds__(256) void ng_sum_chunks_slots_kernel(NgSlots t, NgC
     float4* __restrict__ out = reinterpret_cast<float4*>(Hout + q * t.H_b);
     const float* __restrict__ ome = t.coef + q * (3 * kMaxRank) + 2 * kMaxRank;
     const float4* __restrict__ H4 = reinterpret_cast<const float4*>(t.H + q * t.H_b);
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total4; e += (int64_t)gridDim.x * 256) {
+    for (int64_t e = (int64_t)block * 256 + threadIdx.x; e < total4; e += (int64_t)nblocks * 256) {
         float4 a = reinterpret_cast<const float4*>(P + ((int64_t)first * t.batch + b) * t.H_b)[e];
         for (int c = 1; c < count; ++c) {
             const float4 v = reinterpret_cast<const float4*>(P + ((int64_t)(first + c) * t.batch + b) * t.H_b)[e];
@@ -602,6 +624,19 @@ __global__ __launch_bounds__(256) void ng_sum_chunks_slots_kernel(NgSlots t, NgC
         }
         out[e] = a;
     }
+}
+__global__ __launch_bounds__(256) void ng_sum_chunks_slots_kernel(NgSlots t, NgChunkTable ct, const float* __restrict__ P,
+                                                                  float* __restrict__ Hout, int combine) {
+    ng_sum_chunks(t, ct, P, Hout, combine, blockIdx.x, gridDim.x);
+}
+// The same (plain), and beside it, by further workgroups, the shares of ||X||^2 (kHeadShares of them) and the coefficients.
+constexpr int kHeadShares = 256;
+__global__ __launch_bounds__(256) void ng_head_slots_kernel(NgSlots t, NgChunkTable ct, const float* __restrict__ P, float* __restrict__ Hout, int nsum,
+                                                            float alpha, float eta) {
+    const int x = blockIdx.x;
+    if (x < nsum) ng_sum_chunks(t, ct, P, Hout, 0, x, nsum);
+    else if (x < nsum + kHeadShares) ng_sumsq_partial(t, 0, x - nsum, kHeadShares);
+    else ng_coefficients(t, blockIdx.y, blockIdx.z, alpha, eta);
 }
 
 // X <- X + sign * Cm R for every slot (Cm = H or H2 of the slot) on the matrix cores: a wavefront owns 32
@@ -917,6 +952,181 @@ __global__ __launch_bounds__(256) void ng_y_slots_kernel(NgSlots t, NgYTable yt,
         }
 }
 
+// The rest of a preconditioning, from H = X R^T on, of 32 rows of a matrix by one workgroup of eight wavefronts: X1 = X - H R,
+// H2 = X1 R^T, Xh = X1 + (H (I - E) - H2) R and the rows' share of ||Xh||^2.  Nothing of that depends on other rows, so one workgroup per 32
+// rows does it beside the workgroup that decomposes Z, which takes longer (512 x 2049 at rank 30: 72 us), instead of five launches before it
+// (55 us).  Tiles are transposed (lane = row, accumulator element v of half h = column 8 (v / 4) + 4 h + v % 4): the registers that hold X1^T are the
+// B operand of H2^T += R X1^T.  v_mfma_f32_32x32x2_f32 throughout.
+constexpr int kTailParts = 1024;      // the shares of ||Xh||^2 are kept from here on (those of ||X||^2 before)
+constexpr int kTailRowsMost = 32 * (kNgParts - kTailParts);
+template <int KH>
+constexpr int kTailLds = (8 * KH * 1024 + KH * 32 * 33) * 4 + 8 * 8;
+template <int KH>
+__device__ __forceinline__ void ng_tail_body(const NgSlots& t, const int slab, char* smem) {
+    float* red = reinterpret_cast<float*>(smem);                  // [8][KH][16][64]
+    float* m2 = red + 8 * KH * 1024;                              // [32 KH][33]
+    double* sh = reinterpret_cast<double*>(m2 + KH * 32 * 33 + (KH * 32 * 33 & 1));
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, lc = lane & 31;
+    const int dim = t.dim[0], n = t.n, rank = t.rank, row = slab * 32 + lc, nblk = (dim + 31) / 32;
+    const bool row_ok = row < n;
+    const int64_t ldx = t.ldx[0], ldR = ((int64_t)dim + 3) / 4 * 4, ldc = t.ldr;
+    const float* __restrict__ R = reinterpret_cast<const float*>(t.state[0]);
+    float* X = t.x[0] + (int64_t)min(row, n - 1) * ldx;
+    const float* __restrict__ H = t.H + (int64_t)min(row, n - 1) * ldc;
+    const bool vec = (ldx & 3) == 0 && (reinterpret_cast<uintptr_t>(t.x[0]) & 15u) == 0;
+    float af[KH][16];      // the multipliers of R's rows: contraction index 32 kh + 16 h + s in MFMA step s
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = 32 * kh + 16 * h + 4 * j;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < ldc) v = *reinterpret_cast<const float4*>(H + k);      // ldc is a multiple of 4
+            af[kh][4 * j + 0] = k + 0 < rank ? v.x : 0.f;
+            af[kh][4 * j + 1] = k + 1 < rank ? v.y : 0.f;
+            af[kh][4 * j + 2] = k + 2 < rank ? v.z : 0.f;
+            af[kh][4 * j + 3] = k + 3 < rank ? v.w : 0.f;
+        }
+    auto product = [&](int c0) {      // (the multipliers times R)^T for columns c0 ..
+        const int col = min(c0 + lc, dim - 1);
+        float bf[KH][16];
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const int k = 32 * kh + 16 * h + s;
+                bf[kh][s] = k < rank ? R[(int64_t)k * ldR + col] : 0.f;
+            }
+        ng_floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+            for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[kh][s], af[kh][s], acc, 0, 0, 0);
+        return acc;
+    };
+    auto load = [&](int c0, float (&x)[16]) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int c = c0 + 8 * g + 4 * h;
+            if (vec && c + 3 < dim) {
+                const float4 v = *reinterpret_cast<const float4*>(X + c);
+                x[4 * g] = v.x; x[4 * g + 1] = v.y; x[4 * g + 2] = v.z; x[4 * g + 3] = v.w;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) x[4 * g + j] = c + j < dim ? X[c + j] : 0.f;
+            }
+        }
+    };
+    auto store = [&](int c0, const float (&x)[16]) {
+        if (!row_ok) return;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int c = c0 + 8 * g + 4 * h;
+            if (vec && c + 3 < dim) {
+                *reinterpret_cast<float4*>(X + c) = make_float4(x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) if (c + j < dim) X[c + j] = x[4 * g + j];
+            }
+        }
+    };
+    ng_floatx16 h2[KH];
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh) h2[kh] = ng_floatx16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int blk = wave; blk < nblk; blk += 8) {
+        const int c0 = blk * 32;
+        float x[16], ra[KH][16];
+        load(c0, x);
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int c = c0 + 8 * g + 4 * h, i = 32 * kh + lc;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (i < rank && c < dim) v = *reinterpret_cast<const float4*>(R + (int64_t)i * ldR + c);      // (ldR: a multiple of 4)
+                ra[kh][4 * g + 0] = v.x;
+                ra[kh][4 * g + 1] = c + 1 < dim ? v.y : 0.f;
+                ra[kh][4 * g + 2] = c + 2 < dim ? v.z : 0.f;
+                ra[kh][4 * g + 3] = c + 3 < dim ? v.w : 0.f;
+            }
+        const ng_floatx16 acc = product(c0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[v] = c0 + 8 * (v >> 2) + 4 * h + (v & 3) < dim && row_ok ? x[v] - acc[v] : 0.f;
+        store(c0, x);
+#pragma unroll
+        for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) h2[kh] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[kh][v], x[v], h2[kh], 0, 0, 0);
+    }
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[((wave * KH + kh) * 16 + v) * 64 + lane] = h2[kh][v];
+    __syncthreads();
+    const float* __restrict__ ome = t.coef + 2 * kMaxRank;
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {      // wavefront w finishes elements 2 w and 2 w + 1
+            const int v = 2 * wave + u, i = 32 * kh + 8 * (v >> 2) + 4 * h + (v & 3);
+            float s = red[(kh * 16 + v) * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) s += red[((w * KH + kh) * 16 + v) * 64 + lane];
+            m2[i * 33 + lc] = i < rank ? H[i] * ome[i] - s : 0.f;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int kh = 0; kh < KH; ++kh)
+#pragma unroll
+        for (int s = 0; s < 16; ++s) af[kh][s] = m2[(32 * kh + 16 * h + s) * 33 + lc];
+    double ssq = 0.0;
+    for (int blk = wave; blk < nblk; blk += 8) {
+        const int c0 = blk * 32;
+        float x[16], q = 0.f;
+        load(c0, x);      // (what this lane has written)
+        const ng_floatx16 acc = product(c0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            x[v] = c0 + 8 * (v >> 2) + 4 * h + (v & 3) < dim && row_ok ? x[v] + acc[v] : 0.f;
+            q += x[v] * x[v];
+        }
+        store(c0, x);
+        ssq += (double)q;
+    }
+    ssq = wave_sum(ssq);
+    if (lane == 0) sh[wave] = ssq;
+    __syncthreads();
+    if (tid == 0) t.part[kTailParts + slab] = ((sh[0] + sh[1]) + (sh[2] + sh[3])) + ((sh[4] + sh[5]) + (sh[6] + sh[7]));
+}
+
+// Workgroup 0 decomposes the state's Z, the others finish the preconditioning of 32 rows each (a table of one slot, one replica).
+template <int LW>
+__global__ __launch_bounds__(512) void ng_eig_tail_kernel(NgFoldTable tb, NgSlots t, float eta, const double* __restrict__ Zg, double* __restrict__ Wt) {
+    extern __shared__ double smem[];
+    if (blockIdx.x == 0) ng_eig_body<LW, 512>(tb, t.rank, t.n, eta, Zg, Wt, 1, smem);
+    else ng_tail_body<LW / 32>(t, (int)blockIdx.x - 1, reinterpret_cast<char*>(smem));
+}
+
+// R <- Wt Y by the first nnew workgroups; the others sum the `slabs` shares of ||Xh||^2 and multiply X by ||X|| / ||Xh||.
+__global__ __launch_bounds__(256) void ng_newr_scale_kernel(NgFoldTable tb, NgSlots t, const double* __restrict__ Wt, int nnew, int slabs) {
+    if ((int)blockIdx.x < nnew) {
+        ng_newr_body<float>(tb, t.rank, Wt);
+        return;
+    }
+    __shared__ double sh[4];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < slabs; i += 256) s += t.part[kTailParts + i];
+    s = block_sum_d(s, sh);
+    const double nx = t.scal[0];
+    const float g = nx > 0.0 && s > 0.0 ? (float)sqrt(nx / s) : 1.f;
+    const int block = (int)blockIdx.x - nnew, blocks = (int)gridDim.x - nnew, dim = t.dim[0];
+    if (block == 0 && threadIdx.x == 0) { t.scal[1] = s; t.gamma[0] = g; }
+    for (int r = block; r < t.n; r += blocks) {
+        float* row = t.x[0] + (int64_t)r * t.ldx[0];
+        for (int c = threadIdx.x; c < dim; c += 256) row[c] *= g;
+    }
+}
+
 // Xaug_l[b](r, 0..d) = A_l[b](r, :), Xaug_l[b](r, d) = 1, padding columns 0, for up to kNgSlots / 2 layers
 struct NgAugTable {
     const float* A[kNgSlots / 2]; int64_t lda[kNgSlots / 2], a_b[kNgSlots / 2];
@@ -999,6 +1209,21 @@ struct NgCall {
 
 int ng_eig_smem_bytes(int rank) { return (4 * (rank <= 32 ? kEigMat<32> : kEigMat<64>) + 64) * 8 + 64 * 4; }
 
+// Lets the kernels with dynamic LDS ask for `smem` bytes.
+int ng_allow_lds(int smem) {
+    if (smem <= 64 * 1024) return 0;
+    constexpr int kMaxDev = 64;
+    static int raised[kMaxDev] = {};    // per device, the largest size allowed so far (benign if two threads race: the call is idempotent)
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) dev = -1;
+    if (dev >= 0 && raised[dev] >= smem) return 0;
+    for (const void* f : {reinterpret_cast<const void*>(ng_eig_kernel<32>), reinterpret_cast<const void*>(ng_eig_kernel<64>),
+                          reinterpret_cast<const void*>(ng_eig_tail_kernel<32>), reinterpret_cast<const void*>(ng_eig_tail_kernel<64>)})
+        NG_CHECK(note_hip_error(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, smem)));
+    if (dev >= 0) raised[dev] = smem;
+    return 0;
+}
+
 // Z = Y Y^T and its eigen-decomposition, new (d, rho, t) and Wt for every (slot, replica) of the table: two launches.
 // Reads Y, the squared norms and the old d, rho; does not touch R.
 int ng_finish_zeig(const NgFoldTable& tb, int rank, int n, float eta, bool y64, double* Z, double* Wt, int bump, hipStream_t s) {
@@ -1009,22 +1234,10 @@ int ng_finish_zeig(const NgFoldTable& tb, int rank, int n, float eta, bool y64, 
     // workgroup of a GEMM fits beside it.
     const int need = ng_eig_smem_bytes(rank);
     const int smem = (tb.nslots * tb.batch <= kEigSoloMax && need < kEigSoloLds) ? kEigSoloLds : need;
-    if (smem > 64 * 1024) {
-        constexpr int kMaxDev = 64;
-        static int raised[kMaxDev] = {};    // per device, the largest size allowed so far (benign if two threads race: the call is idempotent)
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) dev = -1;
-        if (dev < 0 || raised[dev] < smem) {
-            NG_CHECK(note_hip_error(hipFuncSetAttribute(reinterpret_cast<const void*>(ng_eig_kernel<32>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem)));
-            NG_CHECK(note_hip_error(hipFuncSetAttribute(reinterpret_cast<const void*>(ng_eig_kernel<64>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem)));
-            if (dev >= 0) raised[dev] = smem;
-        }
-    }
+    NG_CHECK(ng_allow_lds(smem));
     const dim3 gz(rank * rank, tb.nslots, tb.batch);
-    if (y64) hipLaunchKernelGGL(ng_z_kernel<double>, gz, dim3(256), 0, s, tb, rank, Z);
-    else hipLaunchKernelGGL(ng_z_kernel<float>, gz, dim3(256), 0, s, tb, rank, Z);
+    if (y64) hipLaunchKernelGGL(ng_z_kernel<double>, gz, dim3(256), 0, s, tb, rank, Z, nullptr, 0, nullptr);
+    else hipLaunchKernelGGL(ng_z_kernel<float>, gz, dim3(256), 0, s, tb, rank, Z, nullptr, 0, nullptr);
     NG_LAUNCHED();
     if (rank <= 32) hipLaunchKernelGGL(ng_eig_kernel<32>, dim3(tb.nslots * tb.batch), dim3(kEigThreads<32>), smem, s, tb, rank, n, eta, Z, Wt, bump);
     else hipLaunchKernelGGL(ng_eig_kernel<64>, dim3(tb.nslots * tb.batch), dim3(kEigThreads<64>), smem, s, tb, rank, n, eta, Z, Wt, bump);
@@ -1061,12 +1274,13 @@ int ng_slots_norms(const NgSlots& t, int which, float alpha, float eta, hipStrea
 
 // Hout = X R^T for every slot: one launch over the chunks of all contractions (P: [chunk][replica][n x ldr]
 // partial products), then their sums
-int ng_slots_gemm_H(const NgSlots& t, float* P, float* Hout, hipStream_t s, bool combine = false) {
+// (kc: steps per chunk, 0: ng_chunk_len; `table`, if asked for: the sums are left to the caller)
+int ng_slots_gemm_H(const NgSlots& t, float* P, float* Hout, hipStream_t s, bool combine = false, int chunk = 0, NgChunkTable* table = nullptr) {
     GemmDesc g[kThinMaxProblems];
     NgChunkTable ct = {};
     int np = 0, pi = 0;                               // descriptors pending, problems so far
     for (int j = 0; j < t.nslots; ++j) {
-        const int dim = t.dim[j], kc = ng_chunk_len(dim), nch = ng_chunk_count(dim);
+        const int dim = t.dim[j], kc = chunk > 0 ? chunk : ng_chunk_len(dim), nch = (dim + kc - 1) / kc;
         ct.first[j] = pi; ct.count[j] = nch;
         for (int c = 0; c < nch; ++c, ++pi) {
             GemmDesc& q = g[np];
@@ -1083,6 +1297,10 @@ int ng_slots_gemm_H(const NgSlots& t, float* P, float* Hout, hipStream_t s, bool
         }
     }
     if (np > 0) NG_CHECK(gemm_launch_grouped(g, np, s, true));
+    if (table) {
+        *table = ct;
+        return 0;
+    }
     int64_t gx = ((int64_t)t.n * t.ldr / 4 + 255) / 256;
     if (gx > 64) gx = 64;
     hipLaunchKernelGGL(ng_sum_chunks_slots_kernel, dim3((unsigned)gx, t.nslots, t.batch), dim3(256), 0, s, t, ct, P, Hout, combine ? 1 : 0);
@@ -1174,6 +1392,38 @@ int ng_run(const NgCall& c, hipStream_t s) {
         tb.nslots = 1; tb.batch = c.batch; tb.first = 0;
         return ng_finish(tb, c.rank, c.n, c.eta, y64, Z, Wt, bump, s);
     };
+    // One matrix, applied to and folded in: seven launches, of which the longest does the fold's decomposition and the rest of the apply
+    // (see ng_tail_body).  The chunks of H's contraction give the chip about 128 workgroups; their partial products have all of the scratch that
+    // only the float64 folds of a first minibatch use besides.
+    const int slabs = (c.n + 31) / 32;
+    if (c.mode == 1 && c.scale && c.batch == 1 && !c.defer_Y && c.n <= kTailRowsMost) {
+        const int64_t room = (w.off_gemm - w.off_H64) / w.H_b;
+        int nch = (int)std::min<int64_t>(room, std::max(1, 128 / (slabs * (c.rank <= 32 ? 1 : 2))));
+        nch = std::max(std::min(nch, c.dim / 128), 1);
+        const int kc = std::max((int)round_up((c.dim + nch - 1) / nch, 16), (int)round_up((c.dim + kThinMaxProblems - 1) / kThinMaxProblems, 16));
+        NgChunkTable ct;
+        P = c.ws + w.off_H64;
+        NG_CHECK(ng_slots_gemm_H(t, P, t.H, s, false, (c.dim + kc - 1) / kc <= room ? kc : 0, &ct));
+        int nsum = (int)std::min<int64_t>(((int64_t)c.n * w.ldr / 4 + 255) / 256, 64);
+        hipLaunchKernelGGL(ng_head_slots_kernel, dim3(nsum + kHeadShares + 1, 1, 1), dim3(256), 0, s, t, ct, P, t.H, nsum, c.alpha, c.eta);
+        NG_LAUNCHED();
+        NG_CHECK(gemm_Y());
+        NgFoldTable tb;
+        tb.state[0] = c.state; tb.st_b = c.st_b; tb.dim[0] = c.dim; tb.scal[0] = scal;
+        tb.Y[0] = Y; tb.y_b[0] = w.RY_b;
+        tb.nslots = 1; tb.batch = 1; tb.first = 0;
+        hipLaunchKernelGGL(ng_z_kernel<float>, dim3(c.rank * c.rank + 1, 1, 1), dim3(256), 0, s, tb, c.rank, Z, t.part, kHeadShares, scal);
+        NG_LAUNCHED();
+        const int eig = ng_eig_smem_bytes(c.rank), tail = c.rank <= 32 ? kTailLds<1> : kTailLds<2>, smem = eig > tail ? eig : tail;
+        NG_CHECK(ng_allow_lds(smem));
+        if (c.rank <= 32) hipLaunchKernelGGL(ng_eig_tail_kernel<32>, dim3(1 + slabs), dim3(512), smem, s, tb, t, c.eta, Z, Wt);
+        else hipLaunchKernelGGL(ng_eig_tail_kernel<64>, dim3(1 + slabs), dim3(512), smem, s, tb, t, c.eta, Z, Wt);
+        NG_LAUNCHED();
+        const int nnew = (c.dim + 3 + 31) / 32;
+        hipLaunchKernelGGL(ng_newr_scale_kernel, dim3(nnew + std::min(c.n, 1024)), dim3(256), 0, s, tb, t, Wt, nnew, slabs);
+        NG_LAUNCHED();
+        return 0;
+    }
     NG_CHECK(ng_slots_norms(t, 0, c.alpha, c.eta, s));              // ||X||^2 and the coefficients of the state
     if (c.mode == 2) {
         for (int f = 0; f < kInitFolds; ++f) {      // in float64: see ng_h64_kernel
