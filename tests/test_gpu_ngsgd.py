@@ -96,6 +96,32 @@ def test_eigen_solver_at_the_edges_of_its_groups(n, dim, rank):
     test_precondition_sequence_matches_oracle(n, dim, rank)
 
 
+# One launch decomposes and finishes the apply in slabs of 32 rows and blocks of 32 columns: edges of both, rows that no vector load
+# may touch (ldx not a multiple of 4), both sizes of the rank
+@pytest.mark.parametrize("n,dim,rank,pad", [(1, 20, 3, 0), (31, 33, 8, 0), (32, 32, 5, 4), (33, 65, 30, 1), (65, 130, 31, 2), (97, 257, 32, 3), (70, 99, 40, 1), (256, 300, 64, 0)])
+def test_updating_call_applies_as_the_other_one_does(n, dim, rank, pad):
+    import torch
+    from paper_1507_01239_amd import binding as B
+    st = torch.zeros(B.ngsgd_state_bytes(dim, rank), dtype=torch.uint8, device="cuda")
+    B.ngsgd_state_init(st, dim, rank)
+    ws = workspace(B.ngsgd_workspace_bytes(dim, rank, max(n, 128)))
+    x0 = torch.zeros(128, dim, device="cuda")
+    x0[:] = dev(_data(128, dim, 5, 0))
+    B.ngsgd_precondition(st, dim, rank, x0, dim, 128, 4.0, 0.2, B.NG_INIT_UPDATE, ws)
+    outs = []
+    for mode in (B.NG_APPLY, B.NG_UPDATE):
+        x = torch.full((n, dim + pad), 7.0, device="cuda")
+        x[:, :dim] = dev(_data(n, dim, 5, 1))
+        B.ngsgd_precondition(st, dim, rank, x, dim + pad, n, 4.0, 0.2, mode, ws)
+        torch.cuda.synchronize()
+        assert (x[:, dim:] == 7.0).all()
+        outs.append(host(x)[:, :dim].astype(np.float64))
+    # float32 products in another order; what is left after two projections is amplified by ||X|| / ||Xh||
+    X = _data(n, dim, 5, 1).astype(np.float64)
+    assert np.abs(outs[1] - outs[0]).max() <= 1e-4 * np.abs(outs[0]).max()
+    assert abs(np.linalg.norm(outs[1]) / np.linalg.norm(X) - 1) < 1e-5
+
+
 def test_ngsgd_validation_on_device_side_arguments():
     from paper_1507_01239_amd import binding as B
     A = 1 << 20
