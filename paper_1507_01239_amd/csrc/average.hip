@@ -5,7 +5,9 @@
 //   k >= 6 : two passes -- (a) k reads, the mean written to replica 0; (b) replica 0 copied to the other
 //            k-1 replicas.  That moves (2k+1)/(2k) of the one-pass bytes, but a read-mostly pass and a
 //            write-mostly pass each run close to copy speed, while 2k interleaved read and write streams do
-//            not (measured at k = 8, 38.3 M parameters: 0.41 ms against 0.44 ms).
+//            not (measured at k = 8, 38.3 M parameters: 0.41 ms against 0.44 ms).  Up to kAvgOnePassBytes of parameters, where
+//            the launches are what a call takes, one pass here too: k = 8 with 400 thousand parameters 10.0 against 7.5 us, 16
+//            with as many 20.4 against 8.8; 4 million 45.3 against 46.1.
 // Workgroups are 64 threads (one wavefront) with two columns per thread, one chunk per workgroup and no
 // grid-stride loop: this was the fastest launch shape of those tried.
 #include <hip/hip_runtime.h>
@@ -18,6 +20,7 @@ namespace mavg {
 
 constexpr int kAvgBS = 64;     // threads per workgroup
 constexpr int kAvgU = 2;       // 16-byte columns per thread
+constexpr int64_t kAvgOnePassBytes = (int64_t)64 << 20;
 
 typedef float float4v __attribute__((ext_vector_type(4)));
 
@@ -65,10 +68,10 @@ __global__ __launch_bounds__(kAvgBS) void average_kernel(float* __restrict__ the
         }
 }
 
-// 8 < k <= 64, first pass: blocks of 8 replicas are tree-summed, then the (up to 8) block sums are combined as a
+// 8 < k <= 64: blocks of 8 replicas are tree-summed, then the (up to 8) block sums are combined as a
 // balanced tree too: ((b0+b1)+(b2+b3))+((b4+b5)+(b6+b7)), built with a binary counter of partial sums so
-// that only one block of loads is in flight at a time.  The mean goes to replica 0.
-__global__ __launch_bounds__(kAvgBS) void average_any_kernel(float* __restrict__ theta, int64_t stride, int64_t n4, int k, float inv) {
+// that only one block of loads is in flight at a time.  The mean goes to the first `out` replicas.
+__global__ __launch_bounds__(kAvgBS) void average_any_kernel(float* __restrict__ theta, int64_t stride, int64_t n4, int k, int out, float inv) {
     const float4v zero = {0.f, 0.f, 0.f, 0.f};
     const int64_t q = (int64_t)blockIdx.x * kAvgBS + threadIdx.x;
     if (q >= n4) return;
@@ -90,7 +93,8 @@ __global__ __launch_bounds__(kAvgBS) void average_any_kernel(float* __restrict__
         if ((g & 4) == 0) { l2 = b; continue; }
         total = l2 + b;
     }
-    reinterpret_cast<float4v*>(theta)[q] = total * inv;
+    total *= inv;
+    for (int j = 0; j < out; ++j) reinterpret_cast<float4v*>(theta + j * stride)[q] = total;
 }
 
 // second pass: replica 0 -> replicas 1..k-1
@@ -142,20 +146,28 @@ extern "C" int32_t replicas_average(float* theta, int64_t theta_stride, int64_t 
     if (n4 > 0) {
         const int64_t per_wg = kAvgBS * kAvgU;
         const dim3 grid((unsigned)((n4 + per_wg - 1) / per_wg)), block(kAvgBS);
-        bool broadcast = false;
+        const bool broadcast = k > 5 && (int64_t)k * count * 4 > kAvgOnePassBytes;
         switch (k) {
         case 1: hipLaunchKernelGGL((average_kernel<1, 1>), grid, block, 0, s, theta, theta_stride, n4, inv); break;
         case 2: hipLaunchKernelGGL((average_kernel<2, 2>), grid, block, 0, s, theta, theta_stride, n4, inv); break;
         case 3: hipLaunchKernelGGL((average_kernel<3, 3>), grid, block, 0, s, theta, theta_stride, n4, inv); break;
         case 4: hipLaunchKernelGGL((average_kernel<4, 4>), grid, block, 0, s, theta, theta_stride, n4, inv); break;
         case 5: hipLaunchKernelGGL((average_kernel<5, 5>), grid, block, 0, s, theta, theta_stride, n4, inv); break;
-        case 6: hipLaunchKernelGGL((average_kernel<6, 1>), grid, block, 0, s, theta, theta_stride, n4, inv); broadcast = true; break;
-        case 7: hipLaunchKernelGGL((average_kernel<7, 1>), grid, block, 0, s, theta, theta_stride, n4, inv); broadcast = true; break;
-        case 8: hipLaunchKernelGGL((average_kernel<8, 1>), grid, block, 0, s, theta, theta_stride, n4, inv); broadcast = true; break;
+        case 6:
+            if (broadcast) hipLaunchKernelGGL((average_kernel<6, 1>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            else hipLaunchKernelGGL((average_kernel<6, 6>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            break;
+        case 7:
+            if (broadcast) hipLaunchKernelGGL((average_kernel<7, 1>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            else hipLaunchKernelGGL((average_kernel<7, 7>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            break;
+        case 8:
+            if (broadcast) hipLaunchKernelGGL((average_kernel<8, 1>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            else hipLaunchKernelGGL((average_kernel<8, 8>), grid, block, 0, s, theta, theta_stride, n4, inv);
+            break;
         default:
             hipLaunchKernelGGL(average_any_kernel, dim3((unsigned)((n4 + kAvgBS - 1) / kAvgBS)), block, 0, s, theta, theta_stride, n4,
-                               (int)k, inv);
-            broadcast = true;
+                               (int)k, broadcast ? 1 : (int)k, inv);
             break;
         }
         if (note_hip_error(hipGetLastError()) != 0) return MAVG_E_LAUNCH;

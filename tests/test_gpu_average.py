@@ -67,3 +67,19 @@ def test_full_size_eight_replicas():
     ref = src.astype(np.float64).sum(axis=0) / K
     assert rel_err(out[0], ref) < 1e-6
     assert all(np.array_equal(out[0], out[r]) for r in range(1, K))
+
+
+@pytest.mark.parametrize("K", [6, 7, 8, 9, 16])
+@pytest.mark.parametrize("over", [0, 1])
+def test_one_pass_and_two_on_either_side_of_64_mib(K, over):
+    import torch
+    from paper_1507_01239_amd import binding as B
+    count = (64 << 20) // (4 * K) + 4 * over
+    stride = (count + 3) // 4 * 4
+    g = torch.Generator(device="cuda").manual_seed(K)
+    t = torch.randn(K, stride, device="cuda", generator=g)
+    src = t[:, :count].double()
+    B.replicas_average(t, stride, count, K)
+    torch.cuda.synchronize()
+    assert ((t[0, :count].double() - src.mean(0)).norm() / src.mean(0).norm()).item() < 1e-6
+    assert all(torch.equal(t[0, :count], t[r, :count]) for r in range(1, K))
