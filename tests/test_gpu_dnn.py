@@ -405,6 +405,14 @@ def test_networks_of_narrow_layers(dims, n, k, hidden, mean):
         assert abs(host(g.loss)[r] - loss) <= 1e-5 * abs(loss) + 1e-6
 
 
+# Staged in LDS or not: eight layers and nine, parameters that just fit and that do not (five layers of 64; four fit the forward pass, and the
+# backward one at 16 rows), launches of more workgroups than are staged, 16-byte rows and others.
+@pytest.mark.parametrize("dims,n,k", [([20] * 9, 31, 2), ([20] * 10, 31, 2), ([64] * 6, 16, 2), ([64] * 5, 16, 2), ([64] * 5, 64, 2), ([3, 4, 5], 33, 520),
+                                      ([22, 31, 12, 9], 64, 3), ([63, 61, 64, 62], 48, 2)])
+def test_networks_of_narrow_layers_staged_and_not(dims, n, k):
+    test_networks_of_narrow_layers(dims, n, k, "tanh" if len(dims) > 5 else "sigmoid", True)
+
+
 # Inputs and labels shared by all replicas (strides of 0), and labels that name no class: such a row has no target and no
 # loss.  33 and 64 rows: the one-launch backward pass, 65: the general one.
 @pytest.mark.parametrize("n", [33, 64, 65])
