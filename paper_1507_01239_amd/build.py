@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmavg.so")
 SPLIT = [f"gemm_split{t}{p}.hip" for p in ("_by_data", "", "_three") for t in ("256", "128", "64x128", "64", "32x64", "_grouped")]
-SOURCES = SPLIT + ["gemm_dma64.hip", "gemm_kg.hip", "gemm_legacy.hip", "gemm_packed.hip", "gemm.hip", "elementwise.hip", "average.hip", "dnn.hip",
+SOURCES = SPLIT + ["gemm_dma64.hip", "gemm_kg.hip", "gemm_legacy.hip", "gemm_packed.hip", "gemm_kg64.hip", "gemm.hip", "elementwise.hip", "average.hip", "dnn.hip",
                    "narrow.hip", "rbm.hip", "ngsgd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-std=c++17", "-O3", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -3,12 +3,12 @@
 //
 // This file: the plan (kernel family, tile shape, splits), the dispatch to the kernel families, the split-contraction
 // reducer and the exported entry points.  The kernels live in gemm_device.h and gemm_split.h and are instantiated per
-// family in gemm_split*.hip, gemm_dma64.hip, gemm_kg.hip and gemm_legacy.hip (separate files so that they compile in
+// family in gemm_split*.hip, gemm_dma64.hip, gemm_kg.hip, gemm_kg64.hip and gemm_legacy.hip (separate files so that they compile in
 // parallel).  They share the epilogues, the tile order and the split-contraction reducer:
 //  - gemm_split_kernel: every fp32 element in two fp16 parts, three fp16 MFMAs (v_mfma_f32_32x32x16_f16) per product, or in
 //    three bf16 parts, six bf16 MFMAs; tiles from 32x64 to 256x128, any alignment: everything large, and everything the next two
 //    cannot take;
-//  - gemm_dma_kernel (v_mfma_f32_32x32x2_f32) and gemm_dma_kg_kernel (two fp16 parts, made when a wavefront reads its operands back,
+//  - gemm_dma_kernel (v_mfma_f32_32x32x2_f32), gemm_dma_kg_kernel and gemm_kg64_kernel (two fp16 parts, made when a wavefront reads its operands back,
 //    or the same MFMA):
 //    operands go from global memory straight into an LDS ring (global_load_lds_dwordx4): problems that do not fill the chip
 //    with large tiles, 16-byte aligned rows;
@@ -79,9 +79,10 @@ static const TileCfg kCfgs[CFG_COUNT] = {
     {32, 64, 16, 512},     // CFG_KG_32x64
     {32, 32, 16, 256},     // CFG_KG_32x32
     {32, 64, 16, 512},     // CFG_S32x64
+    {64, 64, 16, 256},     // CFG_KG_64x64
 };
 constexpr int kNumCfgs = CFG_COUNT;
-static inline bool cfg_kg(int cfg) { return cfg == CFG_KG_32x64 || cfg == CFG_KG_32x32; }
+static inline bool cfg_kg(int cfg) { return cfg == CFG_KG_32x64 || cfg == CFG_KG_32x32 || cfg == CFG_KG_64x64; }
 static inline bool cfg_split(int cfg) { return (cfg >= CFG_S256 && cfg <= CFG_S128) || cfg == CFG_S32x64; }
 static inline int64_t tiles_of(int cfg, int M, int N, int batch) {
     return (int64_t)((M + kCfgs[cfg].bm - 1) / kCfgs[cfg].bm) * ((N + kCfgs[cfg].bn - 1) / kCfgs[cfg].bn) * batch;
@@ -339,6 +340,19 @@ static bool short_three(const GemmDesc& d, bool ragged) {
     return ragged && d.K < (d.parts == kPartsByData ? 384 : 192) && tiles_of(CFG_S32x64, d.M, d.N, d.batch) <= kNumCU;
 }
 
+// 64x64 tiles split four ways inside the workgroup, for products that have more of these tiles than half the compute units, and no more than
+// all (one of its workgroups fills a compute unit's LDS; with fewer, 32x64 or 32x32 tiles leave none idle), and contractions in which the
+// in-workgroup sum's few microseconds don't count while the partial sums and the reducer of a split across workgroups do.  Over 60 shapes of
+// 100 to 256 tiles and 400 to 8200 steps, two fp16 parts, us without / with:
+//   131 - 256 tiles, 512 - 2304 steps: 0.68 - 0.93 of the time (512x2048x2048 33.0 / 24.0, n-contiguous B 33.8 / 25.1; 384x2048x2048 29.8 / 22.2;
+//   512x2048x1024 20.6 / 14.5; 1769x296x1264 21.0 / 15.8; 232x3388x608 13.6 / 12.7)      280 - 464 steps: 1.03 - 1.2
+//   (from HBM 0.83 - 0.93 where those are 0.73: 33.7 / 30.0)
+//   2400 - 4224 steps: 0.74 - 1.14       4300 steps and more: 0.88 - 1.4      100 - 126 tiles: 1.2 - 1.4      316 tiles and more: 1.03 - 1.9
+static bool kg64_takes(const GemmDesc& d) {
+    const int64_t tiles = tiles_of(CFG_KG_64x64, d.M, d.N, d.batch);
+    return d.force_cfg < 0 && d.force_splits <= 1 && 2 * tiles > kNumCU && tiles <= kNumCU && d.K >= 512 && d.K <= 2304;
+}
+
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {
     if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return 0;
     if (d.epi.rowsum_dst != nullptr && d.a_kc) return note_hip_error(hipErrorInvalidValue);
@@ -350,7 +364,8 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     if (!rowsum && split_eligible(d)) {
         const bool ragged = !dma_eligible(d, p);
         three = three || (d.force_cfg < 0 && short_three(d, ragged));
-        pl = gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
+        pl = !three && !ragged && kg64_takes(d) ? gemm_plan_direct(d.M, d.N, d.K, d.batch, CFG_KG_64x64, 1)
+                                                : gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
         p = fill_params(d, pl, ws);
     }
     if ((cfg_split(pl.cfg) && !split_eligible(d)) ||
@@ -369,7 +384,8 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
                             k32x64[] = {launch_split32x64_three, launch_split32x64, launch_split32x64_by_data};      // (in the order of SplitParts)
         const Launch* of = pl.cfg == CFG_S256 ? k256 : pl.cfg == CFG_S64x128 ? k64x128 : pl.cfg == CFG_S64 ? k64 : pl.cfg == CFG_S32x64 ? k32x64 : k128;
         of[three ? kThreeParts : d.parts](p, d.a_kc, d.b_kc, grid, stream);
-    } else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
+    } else if (pl.cfg == CFG_KG_64x64) launch_kg64(p, d.a_kc, d.b_kc, grid, stream);
+    else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else if (pl.cfg != CFG_64_REG && dma_eligible(d, p)) launch_dma64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else launch_legacy(p, d.a_kc, d.b_kc, grid, stream);
     hipError_t e = hipGetLastError();
@@ -643,7 +659,7 @@ using namespace mavg;
 
 extern "C" int64_t mavg_gemm_workspace_bytes(int32_t m, int32_t n, int32_t k, int32_t cfg, int32_t splits) {
     if (m < 1 || n < 1 || k < 0) return MAVG_E_DIM;
-    if (cfg >= kNumCfgs || splits < 0) return MAVG_E_FLAG;
+    if (cfg > CFG_S32x64 || splits < 0) return MAVG_E_FLAG;
     return gemm_ws_floats(m, n, k, 1, cfg, splits) * 4 + 256;
 }
 
@@ -662,7 +678,7 @@ extern "C" int32_t mavg_gemm_parts(const float* a, int64_t lda, int32_t a_kc, co
     if (parts < MAVG_PARTS_THREE || parts > MAVG_PARTS_BY_DATA || a_exp < -60 || a_exp > 60 || b_exp < -60 || b_exp > 60) return MAVG_E_FLAG;
     if (!a || !b || !c) return MAVG_E_NULL;
     if (m < 1 || n < 1 || k < 0) return MAVG_E_DIM;
-    if (cfg >= kNumCfgs || splits < 0 || epi < EPI_STORE || epi > EPI_AXPBY) return MAVG_E_FLAG;
+    if (cfg > CFG_S32x64 || splits < 0 || epi < EPI_STORE || epi > EPI_AXPBY) return MAVG_E_FLAG;
     if ((epi == EPI_BIAS || epi == EPI_BIAS_SIGMOID) && !bias) return MAVG_E_NULL;
     if (epi == EPI_MUL_DSIGMOID && !aux) return MAVG_E_NULL;
     if (lda < (a_kc ? k : m) || ldb < (b_kc ? k : n) || ldc < n || (epi == EPI_MUL_DSIGMOID && ldaux < n)) return MAVG_E_ALIGN;

@@ -279,3 +279,42 @@ def test_short_ragged_products_take_no_longer_with_two_parts(m, n, k):
     call = lambda parts: lambda: B.mavg_gemm_parts(a, k, 1, b, n, 0, c, n, m, n, k, 0, None, None, 0, 1.0, 0.0, -1, 0, parts, 5, 5, ws)
     three, two, by_data = _graph_us([call(0), call(TWO), call(BY_DATA)])
     assert two < 1.04 * three and by_data < 1.04 * three, (three, two, by_data)
+
+
+@pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
+@pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (1, 8260, 516), (1024, 1024, 2304), (68, 4164, 1000), (2052, 196, 1337), (640, 640, 576), (576, 1000, 2060)])
+def test_64x64_tiles_split_inside_the_workgroup(m, n, k, a_kc, b_kc):
+    # 129 to 256 tiles of 64x64, the shortest and longest contractions that go there, remainders of k-tiles (4, 8, 9 steps), numbers of k-tiles that four
+    # wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2304 additions rounding by 2^-24 each give 3e-6 if all
+    # round alike, 2e-7 if they round at random.
+    import torch
+    from paper_1507_01239_amd import binding as B
+    rng = np.random.default_rng(m + k)
+    m, n = m if a_kc else (m + 3) // 4 * 4, n if b_kc else (n + 3) // 4 * 4      # (rows that are not 16-byte aligned go elsewhere)
+    A, Bt = rng.standard_normal((m, k)).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
+    pad = -k % 4
+    stored = [np.pad(x, ((0, 0), (0, pad)), constant_values=np.nan) if kc else x.T for x, kc in ((A, a_kc), (Bt, b_kc))]
+    a, b = dev(np.ascontiguousarray(stored[0])), dev(np.ascontiguousarray(stored[1]))
+    bias = rng.standard_normal(n).astype(np.float32)
+
+    def run(epi, a=a, b=b):
+        c = torch.full((m, n + 4), 7.0, device="cuda")
+        B.mavg_gemm_parts(a, a.shape[1], a_kc, b, b.shape[1], b_kc, c, n + 4, m, n, k, epi, dev(bias), None, 0, 1.0, 0.0, -1, 0, TWO, 0, 0,
+                          workspace(B.mavg_gemm_workspace_bytes(m, n, k)))
+        assert (c[:, n:] == 7.0).all()
+        return host(c)[:, :n].astype(np.float64)
+    want = _ref(A, Bt)
+    first = run(0)
+    assert rel_err(first, want) < 4e-7
+    assert rel_err(run(2), 1 / (1 + np.exp(-want - bias))) < 2e-6      # (sigmoid: sums of magnitude 40 off by 2e-7 of that)
+    assert np.array_equal(first, run(0))
+    # one block of rows with an infinity, one with a NaN, one of nothing but small elements, and the others as before
+    hurt = a.clone()
+    rows = (lambda i: hurt[i]) if a_kc else (lambda i: hurt[:, i])
+    rows(0)[k - 1], rows(m // 2)[1] = float("inf"), float("nan")
+    if m > 200:
+        rows(m - 1)[:k] *= 2.0**-60
+    got, ref = run(0, a=hurt), (hurt[:, :k] if a_kc else hurt.T).double().cpu().numpy() @ Bt.astype(np.float64).T
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    fine = np.isfinite(ref).all(1)
+    assert (np.linalg.norm(got[fine] - ref[fine], axis=1) <= 2e-6 * np.linalg.norm(ref[fine], axis=1)).all()
