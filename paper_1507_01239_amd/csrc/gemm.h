@@ -100,8 +100,9 @@ enum GemmCfg : int {
     CFG_KG_32x64 = 7,    // 32x64 tile, contraction split eight ways inside the workgroup, one wavefront each
     CFG_KG_32x32 = 8,    // 32x32 tile, likewise, four ways
     CFG_S32x64 = 9,      // split-operand kernel, 32x64 tiles with eight k-groups of one wavefront
-    CFG_KG_64x64 = 10,   // 64x64 tile, four ways, one wavefront each (chosen only, not an argument)
-    CFG_COUNT = 11
+    CFG_KG_64x64 = 10,   // 64x64 tile, four ways, one wavefront each (this and the next: chosen only, not an argument)
+    CFG_KG_64x128 = 11,  // 64x128 tile, likewise
+    CFG_COUNT = 12
 };
 
 struct GemmPlan { int cfg; int splits; int bm, bn; };

@@ -80,9 +80,10 @@ static const TileCfg kCfgs[CFG_COUNT] = {
     {32, 32, 16, 256},     // CFG_KG_32x32
     {32, 64, 16, 512},     // CFG_S32x64
     {64, 64, 16, 256},     // CFG_KG_64x64
+    {64, 128, 16, 256},    // CFG_KG_64x128
 };
 constexpr int kNumCfgs = CFG_COUNT;
-static inline bool cfg_kg(int cfg) { return cfg == CFG_KG_32x64 || cfg == CFG_KG_32x32 || cfg == CFG_KG_64x64; }
+static inline bool cfg_kg(int cfg) { return cfg == CFG_KG_32x64 || cfg == CFG_KG_32x32 || cfg >= CFG_KG_64x64; }
 static inline bool cfg_split(int cfg) { return (cfg >= CFG_S256 && cfg <= CFG_S128) || cfg == CFG_S32x64; }
 static inline int64_t tiles_of(int cfg, int M, int N, int batch) {
     return (int64_t)((M + kCfgs[cfg].bm - 1) / kCfgs[cfg].bm) * ((N + kCfgs[cfg].bn - 1) / kCfgs[cfg].bn) * batch;
@@ -340,17 +341,24 @@ static bool short_three(const GemmDesc& d, bool ragged) {
     return ragged && d.K < (d.parts == kPartsByData ? 384 : 192) && tiles_of(CFG_S32x64, d.M, d.N, d.batch) <= kNumCU;
 }
 
-// 64x64 tiles split four ways inside the workgroup, for products that have more of these tiles than half the compute units, and no more than
-// all (one of its workgroups fills a compute unit's LDS; with fewer, 32x64 or 32x32 tiles leave none idle), and contractions in which the
-// in-workgroup sum's few microseconds don't count while the partial sums and the reducer of a split across workgroups do.  Over 60 shapes of
-// 100 to 256 tiles and 400 to 8200 steps, two fp16 parts, us without / with:
+// 64x64 or 64x128 tiles split four ways inside the workgroup, where there are more of these tiles than half the compute units, and no more than
+// all (one of its workgroups fills a compute unit's LDS; with fewer, smaller tiles leave none idle), and contractions in which the
+// in-workgroup sum's few microseconds don't count while the partial sums and the reducer of a split across workgroups do, or the rounds and
+// fixed costs of the split-operand kernels.  Two fp16 parts, us without / with:
+// 64x64, 60 shapes of 100 to 256 tiles and 400 to 8200 steps:
 //   131 - 256 tiles, 512 - 2304 steps: 0.68 - 0.93 of the time (512x2048x2048 33.0 / 24.0, n-contiguous B 33.8 / 25.1; 384x2048x2048 29.8 / 22.2;
 //   512x2048x1024 20.6 / 14.5; 1769x296x1264 21.0 / 15.8; 232x3388x608 13.6 / 12.7)      280 - 464 steps: 1.03 - 1.2
 //   (from HBM 0.83 - 0.93 where those are 0.73: 33.7 / 30.0)
 //   2400 - 4224 steps: 0.74 - 1.14       4300 steps and more: 0.88 - 1.4      100 - 126 tiles: 1.2 - 1.4      316 tiles and more: 1.03 - 1.9
-static bool kg64_takes(const GemmDesc& d) {
-    const int64_t tiles = tiles_of(CFG_KG_64x64, d.M, d.N, d.batch);
-    return d.force_cfg < 0 && d.force_splits <= 1 && 2 * tiles > kNumCU && tiles <= kNumCU && d.K >= 512 && d.K <= 2304;
+// 64x128 (where the 64x64 tiles are too many), 60 shapes of 110 to 520 tiles and 300 to 8000 steps:
+//   133 - 256 tiles, 332 - 2656 steps: 0.78 - 0.94 of the time (1024x2048x2048 48.1 / 41.8, n-contiguous B 48.1 / 38.6, from HBM 49.6 / 43.5, 49.5 / 39.2;
+//   768x2048x2048 40.0 / 34.2; 448x3776x880 26.4 / 21.0; 1024x2048x440 21.9 / 20.1)      2768 - 8000 steps: 0.87 - 1.17
+//   270 tiles and more: 1.04 - 1.4
+static int kg64_plan(const GemmDesc& d) {
+    const int64_t t64 = tiles_of(CFG_KG_64x64, d.M, d.N, d.batch), t128 = tiles_of(CFG_KG_64x128, d.M, d.N, d.batch);
+    if (d.force_cfg >= 0 || d.force_splits > 1 || 2 * t64 <= kNumCU) return CFG_AUTO;
+    if (t64 <= kNumCU) return d.K >= 512 && d.K <= 2304 ? CFG_KG_64x64 : CFG_AUTO;
+    return 2 * t128 > kNumCU && t128 <= kNumCU && d.K >= 320 && d.K <= 2656 ? CFG_KG_64x128 : CFG_AUTO;
 }
 
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {
@@ -364,8 +372,9 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     if (!rowsum && split_eligible(d)) {
         const bool ragged = !dma_eligible(d, p);
         three = three || (d.force_cfg < 0 && short_three(d, ragged));
-        pl = !three && !ragged && kg64_takes(d) ? gemm_plan_direct(d.M, d.N, d.K, d.batch, CFG_KG_64x64, 1)
-                                                : gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
+        const int kg64 = three || ragged ? CFG_AUTO : kg64_plan(d);
+        pl = kg64 != CFG_AUTO ? gemm_plan_direct(d.M, d.N, d.K, d.batch, kg64, 1)
+                              : gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
         p = fill_params(d, pl, ws);
     }
     if ((cfg_split(pl.cfg) && !split_eligible(d)) ||
@@ -384,7 +393,7 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
                             k32x64[] = {launch_split32x64_three, launch_split32x64, launch_split32x64_by_data};      // (in the order of SplitParts)
         const Launch* of = pl.cfg == CFG_S256 ? k256 : pl.cfg == CFG_S64x128 ? k64x128 : pl.cfg == CFG_S64 ? k64 : pl.cfg == CFG_S32x64 ? k32x64 : k128;
         of[three ? kThreeParts : d.parts](p, d.a_kc, d.b_kc, grid, stream);
-    } else if (pl.cfg == CFG_KG_64x64) launch_kg64(p, d.a_kc, d.b_kc, grid, stream);
+    } else if (pl.cfg >= CFG_KG_64x64) launch_kg64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else if (cfg_kg(pl.cfg)) launch_kg(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else if (pl.cfg != CFG_64_REG && dma_eligible(d, p)) launch_dma64(pl.cfg, p, d.a_kc, d.b_kc, grid, stream);
     else launch_legacy(p, d.a_kc, d.b_kc, grid, stream);

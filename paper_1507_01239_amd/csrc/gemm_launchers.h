@@ -13,8 +13,8 @@ void launch_dma64(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid
 void launch_grouped_dma(const GemmGroupParams& gp, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 // contraction split inside the workgroup: 32x64 tiles (CFG_KG_32x64) or 32x32 tiles (CFG_KG_32x32); thin grouped problems
 void launch_kg(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
-// ... and of 64x64 tiles (CFG_KG_64x64)
-void launch_kg64(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
+// ... and of 64x64 and 64x128 tiles (CFG_KG_64x64, CFG_KG_64x128)
+void launch_kg64(int cfg, const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);
 // split-operand kernels: two fp16 parts per fp32 element, three bf16 parts, or as the data ask for; grouped: m- and n-contiguous
 // operands only, `wide`: 256x128 tiles
 void launch_split256(const GemmKParams& p, bool a_kc, bool b_kc, dim3 grid, hipStream_t s);

@@ -282,11 +282,12 @@ def test_short_ragged_products_take_no_longer_with_two_parts(m, n, k):
 
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
-@pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (1, 8260, 516), (1024, 1024, 2304), (68, 4164, 1000), (2052, 196, 1337), (640, 640, 576), (576, 1000, 2060)])
-def test_64x64_tiles_split_inside_the_workgroup(m, n, k, a_kc, b_kc):
-    # 129 to 256 tiles of 64x64, the shortest and longest contractions that go there, remainders of k-tiles (4, 8, 9 steps), numbers of k-tiles that four
-    # wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2304 additions rounding by 2^-24 each give 3e-6 if all
-    # round alike, 2e-7 if they round at random.
+@pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (1, 8260, 516), (1024, 1024, 2304), (68, 4164, 1000), (2052, 196, 1337), (640, 640, 576), (576, 1000, 2060),
+                                   (1024, 2048, 320), (4164, 260, 333), (513, 1924, 1100), (129, 8196, 1020), (1, 16516, 325), (770, 2048, 2656)])
+def test_64x64_and_64x128_tiles_split_inside_the_workgroup(m, n, k, a_kc, b_kc):
+    # 129 to 256 tiles of 64x64, and of 64x128 where those of 64x64 are more, the shortest and longest contractions that go there, remainders of k-tiles
+    # (4, 8, 9 steps), numbers of k-tiles that four wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2656 additions
+    # rounding by 2^-24 each give 3e-6 if all round alike, 2e-7 if they round at random.
     import torch
     from paper_1507_01239_amd import binding as B
     rng = np.random.default_rng(m + k)
