@@ -341,24 +341,23 @@ static bool short_three(const GemmDesc& d, bool ragged) {
     return ragged && d.K < (d.parts == kPartsByData ? 384 : 192) && tiles_of(CFG_S32x64, d.M, d.N, d.batch) <= kNumCU;
 }
 
-// 64x64 or 64x128 tiles split four ways inside the workgroup, where there are more of these tiles than half the compute units, and no more than
-// all (one of its workgroups fills a compute unit's LDS; with fewer, smaller tiles leave none idle), and contractions in which the
-// in-workgroup sum's few microseconds don't count while the partial sums and the reducer of a split across workgroups do, or the rounds and
-// fixed costs of the split-operand kernels.  Two fp16 parts, us without / with:
-// 64x64, 60 shapes of 100 to 256 tiles and 400 to 8200 steps:
-//   131 - 256 tiles, 512 - 2304 steps: 0.68 - 0.93 of the time (512x2048x2048 33.0 / 24.0, n-contiguous B 33.8 / 25.1; 384x2048x2048 29.8 / 22.2;
-//   512x2048x1024 20.6 / 14.5; 1769x296x1264 21.0 / 15.8; 232x3388x608 13.6 / 12.7)      280 - 464 steps: 1.03 - 1.2
-//   (from HBM 0.83 - 0.93 where those are 0.73: 33.7 / 30.0)
-//   2400 - 4224 steps: 0.74 - 1.14       4300 steps and more: 0.88 - 1.4      100 - 126 tiles: 1.2 - 1.4      316 tiles and more: 1.03 - 1.9
-// 64x128 (where the 64x64 tiles are too many), 60 shapes of 110 to 520 tiles and 300 to 8000 steps:
-//   133 - 256 tiles, 332 - 2656 steps: 0.78 - 0.94 of the time (1024x2048x2048 48.1 / 41.8, n-contiguous B 48.1 / 38.6, from HBM 49.6 / 43.5, 49.5 / 39.2;
-//   768x2048x2048 40.0 / 34.2; 448x3776x880 26.4 / 21.0; 1024x2048x440 21.9 / 20.1)      2768 - 8000 steps: 0.87 - 1.17
-//   270 tiles and more: 1.04 - 1.4
+// 64x64 or 64x128 tiles split four ways inside the workgroup, where that leaves few compute units idle and asks none to take a second turn (one
+// of its workgroups fills a compute unit's LDS), for contractions in which the in-workgroup sum's few microseconds don't count while the
+// partial sums and the reducer of a split across workgroups do, or the rounds and fixed costs of the split-operand kernels.  Two fp16 parts, time
+// with / without over 200 shapes of 64 to 2900 rows, B from the last-level cache or from HBM:
+// 64x64, 131 - 256 tiles, 512 - 2304 steps: 0.68 - 0.97, two shapes 1.00 (512x2048x2048 24.0 / 33.0 us, n-contiguous B 25.1 / 33.8, from HBM
+//   30.0 / 33.7, 29.0 / 34.0; 384x2048x2048 22.2 / 29.8; 1769x296x1264 15.8 / 21.0); where 32x64 tiles need one turn 1.26 - 1.41;
+//   280 - 464 steps 1.03 - 1.2; 2400 - 4224 steps 0.74 - 1.14, 4300 and more 0.88 - 1.4; 100 - 126 tiles 1.2 - 1.4; 316 and more 1.03 - 1.9
+// 64x128 (where the 64x64 tiles are too many), 192 - 256 tiles, 512 - 2304 steps, rows that begin at 64-byte boundaries: 0.79 - 0.97, one shape 1.02
+//   (1024x2048x2048 41.8 / 48.1 us, n-contiguous B 38.6 / 48.1, from HBM 43.5 / 49.6, 39.2 / 49.5; 768x2048x2048 34.2 / 40.0); other
+//   rows, whose 64-byte pieces lie in two cache lines, up to 1.07; 130 - 188 tiles 0.80 - 1.28; 320 - 500 steps 0.9 - 1.14; 2400 and more
+//   0.9 - 1.17; 270 tiles and more 1.04 - 1.4
 static int kg64_plan(const GemmDesc& d) {
+    if (d.force_cfg >= 0 || d.force_splits > 1 || d.K < 512 || d.K > 2304) return CFG_AUTO;
     const int64_t t64 = tiles_of(CFG_KG_64x64, d.M, d.N, d.batch), t128 = tiles_of(CFG_KG_64x128, d.M, d.N, d.batch);
-    if (d.force_cfg >= 0 || d.force_splits > 1 || 2 * t64 <= kNumCU) return CFG_AUTO;
-    if (t64 <= kNumCU) return d.K >= 512 && d.K <= 2304 ? CFG_KG_64x64 : CFG_AUTO;
-    return 2 * t128 > kNumCU && t128 <= kNumCU && d.K >= 320 && d.K <= 2656 ? CFG_KG_64x128 : CFG_AUTO;
+    if (t64 <= kNumCU) return 2 * t64 > kNumCU && tiles_of(CFG_KG_32x64, d.M, d.N, d.batch) > kNumCU ? CFG_KG_64x64 : CFG_AUTO;
+    auto starts_at_64 = [](const float* q, int64_t ld, int64_t stride) { return ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld * 4 | (uintptr_t)stride * 4) & 63) == 0; };
+    return 4 * t128 >= 3 * kNumCU && t128 <= kNumCU && starts_at_64(d.A, d.lda, d.a_bstride) && starts_at_64(d.B, d.ldb, d.b_bstride) ? CFG_KG_64x128 : CFG_AUTO;
 }
 
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {

@@ -282,18 +282,19 @@ def test_short_ragged_products_take_no_longer_with_two_parts(m, n, k):
 
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
-@pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (1, 8260, 516), (1024, 1024, 2304), (68, 4164, 1000), (2052, 196, 1337), (640, 640, 576), (576, 1000, 2060),
-                                   (1024, 2048, 320), (4164, 260, 333), (513, 1924, 1100), (129, 8196, 1020), (1, 16516, 325), (770, 2048, 2656)])
+@pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (65, 8132, 516), (1024, 1024, 2304), (100, 5188, 1000), (2052, 196, 1337), (832, 640, 576), (576, 1000, 2060),
+                                   (1024, 2048, 512), (4161, 260, 533), (769, 1928, 1100), (130, 8196, 1020), (33, 24576, 517), (770, 2048, 2304)])
 def test_64x64_and_64x128_tiles_split_inside_the_workgroup(m, n, k, a_kc, b_kc):
-    # 129 to 256 tiles of 64x64, and of 64x128 where those of 64x64 are more, the shortest and longest contractions that go there, remainders of k-tiles
-    # (4, 8, 9 steps), numbers of k-tiles that four wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2656 additions
+    # 129 to 256 tiles of 64x64, and 192 to 256 of 64x128, the shortest and longest contractions that go there, remainders of k-tiles (4, 5, 8, 9, 12
+    # steps), numbers of k-tiles that four wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2304 additions
     # rounding by 2^-24 each give 3e-6 if all round alike, 2e-7 if they round at random.
     import torch
     from paper_1507_01239_amd import binding as B
     rng = np.random.default_rng(m + k)
-    m, n = m if a_kc else (m + 3) // 4 * 4, n if b_kc else (n + 3) // 4 * 4      # (rows that are not 16-byte aligned go elsewhere)
+    whole = 4 if -(-m // 64) * -(-n // 64) <= 256 else 16      # (rows that do not begin at 16, or 64, bytes go elsewhere)
+    m, n = m if a_kc else -(-m // whole) * whole, n if b_kc else -(-n // whole) * whole
     A, Bt = rng.standard_normal((m, k)).astype(np.float32), rng.standard_normal((n, k)).astype(np.float32)
-    pad = -k % 4
+    pad = -k % whole
     stored = [np.pad(x, ((0, 0), (0, pad)), constant_values=np.nan) if kc else x.T for x, kc in ((A, a_kc), (Bt, b_kc))]
     a, b = dev(np.ascontiguousarray(stored[0])), dev(np.ascontiguousarray(stored[1]))
     bias = rng.standard_normal(n).astype(np.float32)
