@@ -547,24 +547,29 @@ int64_t gemm_packed_floats(int M, int N, int K, int batch, int pieces) {
     return batch * (a.floats + a.exps + b.floats + b.exps) + (pieces > 1 ? (N / kPackWidthLeast + 64) / 64 * 64 : 0);
 }
 
-// From kSplitGroupedMinK steps on, where fp16 parts sum no less exactly than fp32 MFMAs, and where the launch that packs (5 - 9 us) is worth it:
-// large updates, whose time is the parameters' way through memory, and the products of long enough contractions.  Grouped launch that splits as it
-// goes / packed, us, both launches:
-//   440-6x2048-8000: 128 rows 116 / 82, 256 145 / 100, 512 202 / 175, 1024 338 / 295        640-3x2048-9000 at 80 rows: 61 / 57
-//   2048 x 2048: 128 rows 16.0 / 16.3, 200 21.7 / 19.2, 320 27.5 / 25.1, 512 38.6 / 30.0    1500 x 1500: 128 14.0 / 14.6, 200 18.8 / 17.1, 512 30.6 / 26.7
-//   440-512-512-1000: 200 10.7 / 14.2, 512 16.1 / 20.6, 1000 27.3 / 26.9                    440-6x512-9000: 128 22.5 / 25.9, 200 33.3 / 30.2
-//   429-3x1021-3003: 128 26.2 / 26.5, 200 31.6 / 27.5, 512 50.2 / 43.3                      512 x 4000 and 300 x 512: 512 22.9 / 23.6, 1000 40.0 / 32.9
+// From kSplitGroupedMinK steps on, where fp16 parts sum no less exactly than fp32 MFMAs, and where the launch that packs (5 - 9 us, and some 3 us
+// for the dependence between the two) is worth it: large updates, whose time is the parameters' way through memory, and the products of
+// long contractions with a tile of 128x128 or more per compute unit.  A training step, us, without / with (rows, replicas):
+//   440-6x2048-8000 (2352 tiles): 128 rows 368 / 337, 256 444 / 417           429-3x2047-8001 (1792 tiles): 128 rows 292 / 272
+//   440-3x2048 (576): 256 134 / 133, 512 205 / 190       440-2048-2048 (320): 200 74.5 / 78.2, 512 120 / 117, 1024 203 / 180
+//   440-3x1024-3000 (352): 200 124 / 127, 320 138 / 139, 512 180 / 168, 1024 295 / 265; 2 replicas (704) 256 183 / 186
+//   440-3x1500 (336): 512 167 / 163, 1024 295 / 283      440-1024-1024, 4 replicas (384): 256 93.8 / 97.7, 512 150 / 145
+//   440-3x512-4000 (176): 640 146 / 151, 1280 222 / 224
+//   rows that are not 16-byte aligned: 429-3x1021-3003 (352) 200 167 / 172, 1000 309 / 312, 2000 471 / 463; 301-3x701-2005, 2 replicas (372) 512 230 / 240
 // Of two pieces (statistics of an RBM) packing replaces the launch for the visible bias: 440 x 2048 with 2 x 256 rows 22 / 18.
 bool gemm_packed_takes(const GemmDesc* d, int count, int pieces) {
     double flop = 0;
     int least = INT32_MAX;
+    bool aligned = true;
     for (int i = 0; i < count; ++i) {
         if (d[i].a_kc || d[i].b_kc || d[i].epi.kind != EPI_AXPBY || !split_eligible(d[i])) return false;
         if (d[i].K * pieces < least) least = d[i].K * pieces;
         flop += 2.0 * d[i].M * d[i].N * d[i].K * pieces * d[i].batch;
+        aligned = aligned && d[i].lda % 4 == 0 && d[i].ldb % 4 == 0;
     }
     if (count < 1 || least < kSplitGroupedMinK) return false;
-    return grouped_tiles128(d, count) >= 4 * kNumCU || (least >= 192 && flop >= (pieces > 1 ? 0.7e9 : 1.6e9));
+    const int64_t tiles = grouped_tiles128(d, count);
+    return tiles >= 4 * kNumCU || (pieces > 1 ? least >= 192 && flop >= 0.7e9 : aligned && least >= 448 && tiles >= kNumCU);
 }
 
 // Tiles: 64x64 below one tile of 128x128 per compute unit (440 x 2048 at 512 rows 11.4 us, 64x128 14.8), 128x128 for long contractions in
