@@ -4,7 +4,7 @@
 A step = dnn_forward + dnn_backward_update (fused SGD update) on one 256-frame minibatch of the
 440-6x2048-8000 sigmoid/softmax DNN, fp32, synthetic speech-shaped inputs already resident in HBM.
 Prints ONE JSON line: whole-job train frames/s, the roofline record of the dominant kernel of the step (the
-grouped weight-gradient + SGD-update launch, timed live with HIP events on the launch stream), and the CPU oracle
+grouped weight-gradient + SGD update, timed live with HIP events on the launch stream), and the CPU oracle
 timed beside it on a bounded sample.  `extras` carries every GEMM of the step timed by itself, per-step statistics,
 the cold (no clock warm-up) figure and the side measurements: replica averaging, CD-1, the RBM stack, the averaging
 sweep, the paper's own shape, NG-SGD (one replica, and 8 replicas averaged every 5 minibatches), and the tile plan
@@ -35,7 +35,11 @@ PEAK_HBM_GBPS = 8000.0
 ALL_EXTRAS = ("kernels", "stats", "averaging", "cd1", "stack", "sweep", "paper", "ngsgd", "ngsgd8", "plan")
 # rocprofv3 counter summary of the roofline kernel: bench.py takes `traffic` from the record this file carries
 ROOFLINE_PROFILE = os.path.join(ROOT, "profiles", "weight_update_grouped_mb256_hbm_counters.md")
-# by what mavg_gemm_grouped_kernel answers for its largest problem: kernel, its form, peak
+# what the weight update of this network runs on.  From 80 rows on: operands packed into fp16 parts by a launch of their own, two tile forms; below:
+# by what mavg_gemm_grouped_kernel answers for its largest problem.  Kernel, its form, peak
+PACKED_LEAST_ROWS, PACKED_WIDE_ROWS = 80, 768
+ROOFLINE_PACKED = ("gemm_packed_grouped_kernel", ("<1,2,4,3> behind pack_kernel, fp32 in two fp16 parts", "<2,2,5,2> behind pack_kernel, fp32 in two fp16 parts"),
+                   PEAK_SPLIT_MFMA_TFLOPS)
 ROOFLINE_KERNELS = {0: ("gemm_split_grouped_kernel", "<2,128,128,2,2,1,2,false,false> fp32 in two fp16 parts", PEAK_SPLIT_MFMA_TFLOPS),
                     1: ("gemm_dma_grouped_kernel", "<1,1,3,false,false> fp32", PEAK_FP32_MFMA_TFLOPS),
                     2: ("gemm_grouped_kernel", "<64,64,16,2,2,4,false,false> fp32", PEAK_FP32_MFMA_TFLOPS)}
@@ -47,7 +51,7 @@ def log(msg):
 
 def traffic_from_profile(kernel: str, minibatch: int):
     """HBM bytes per launch of `kernel` as the committed counter summary states them (FETCH_SIZE + WRITE_SIZE,
-    scaled against a plain copy), or None when there is no summary for this kernel and minibatch."""
+    scaled against a plain copy; with the launch that packs), or None when there is no summary for this kernel and minibatch."""
     try:
         m = re.search(r"<!--\s*bench:\s*(\{.*?\})\s*-->", open(ROOFLINE_PROFILE).read(), re.S)
         rec = json.loads(m.group(1))
@@ -234,17 +238,26 @@ def main():
                              alpha=-1e-6, beta=1.0, rowsum_dst=bl[l], rowsum_alpha=-1e-6, rowsum_beta=1.0, a_pad4=True)
               for l in range(1, L + 1)]
 
-    def dw():       # W_l <- W_l - lr D_l^T A_{l-1}, b_l <- b_l - lr colsum(D_l), all layers in one launch
-        B.mavg_gemm_grouped_parts(update, 0, 0, B.PARTS_BY_DATA, D_EXP, a_exp(0))
+    packed = n >= PACKED_LEAST_ROWS
+    pws = torch.empty(B.mavg_gemm_grouped_packed_bytes(update), dtype=torch.uint8, device="cuda") if packed else None
+
+    def dw():       # W_l <- W_l - lr D_l^T A_{l-1}, b_l <- b_l - lr colsum(D_l), all layers in one launch (packed: and the one before it)
+        if packed:
+            B.mavg_gemm_grouped_packed(update, -1, pws)
+        else:
+            B.mavg_gemm_grouped_parts(update, 0, 0, B.PARTS_BY_DATA, D_EXP, a_exp(0))
 
     # ---- roofline of the dominant kernel of the step: the grouped weight update -------------------------
     dw_flop = 2.0 * n * sum(dims[l] * dims[l - 1] for l in range(1, L + 1))
     dw_ms = event_ms(dw, 100, warm=5, burst=0.3)
     dw_tflops = dw_flop / (dw_ms * 1e-3) / 1e12
-    dw_kernel, dw_form, dw_peak = ROOFLINE_KERNELS[B.mavg_gemm_grouped_kernel(update, 0, 0, L - 1)]
+    if packed:
+        dw_kernel, dw_form, dw_peak = ROOFLINE_PACKED[0], ROOFLINE_PACKED[1][n >= PACKED_WIDE_ROWS], ROOFLINE_PACKED[2]
+    else:
+        dw_kernel, dw_form, dw_peak = ROOFLINE_KERNELS[B.mavg_gemm_grouped_kernel(update, 0, 0, L - 1)]
     roofline = {"bound": "mfma",
                 "kernel": f"{dw_kernel}{dw_form}: weight gradients + SGD update + bias row sums of all {L} layers "
-                          f"in one launch (contraction = minibatch {n})",
+                          f"(contraction = minibatch {n})",
                 "achieved": round(dw_tflops, 3), "peak": dw_peak, "unit": "TFLOP/s", "frac": round(dw_tflops / dw_peak, 4),
                 "traffic": traffic_from_profile(dw_kernel, n), "avg_launch_us": round(dw_ms * 1e3, 2),
                 "flop_per_launch": dw_flop}
