@@ -243,9 +243,14 @@ __global__ __launch_bounds__(kThreads) void argmax_correct_kernel(const float* _
     const float* r = p + (int64_t)b * bstride + (int64_t)row * ld;
     float best = -INFINITY;
     int idx = 0x7fffffff;
-    for (int j = threadIdx.x; j < cols; j += kThreads) {
-        const float v = r[j];
-        if (v > best) { best = v; idx = j; }       // ascending j per thread: the first maximum is kept
+    constexpr int AHEAD = 8;      // columns requested together: 1999 x 8000 (64 MB) 11.0 us, 5.8 TB/s (one after the other 15.8, sixteen 12.3)
+    for (int j0 = threadIdx.x; j0 < cols; j0 += AHEAD * kThreads) {
+        float v[AHEAD];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) v[i] = r[min(j0 + i * kThreads, cols - 1)];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+            if (j0 + i * kThreads < cols && v[i] > best) { best = v[i]; idx = j0 + i * kThreads; }       // ascending per thread: the first maximum is kept
     }
     for (int off = 32; off > 0; off >>= 1) {
         const float ov = __shfl_down(best, off, 64);

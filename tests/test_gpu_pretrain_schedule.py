@@ -126,6 +126,31 @@ def test_arg_max_takes_the_lowest_index_among_equal_posteriors():
         assert int(correct.item()) == want
 
 
+@pytest.mark.parametrize("cols", [1, 255, 257, 2047, 2048, 2049, 4353])
+def test_arg_max_at_the_edges_of_what_is_requested_together(cols):
+    # 2048 columns at a time: maxima in the first and last column, in every pass, ties between passes, a NaN (never a maximum)
+    import torch
+    from paper_1507_01239_amd import binding as B
+    dims = [4, 3, cols]
+    shape = B.Shape(dims)
+    rows = [{0: 1.0}, {cols - 1: 1.0}, {cols // 2: 1.0, cols - 1: 1.0}, {0: float("nan"), cols - 1: 0.5}]
+    acts = torch.zeros(B.mavg_act_count(shape, len(rows)), device="cuda")
+    post = acts[len(rows) * 3:].view(len(rows), cols)
+    want = []
+    for i, r in enumerate(rows):
+        for j, v in r.items():
+            post[i, j] = v
+        x = np.nan_to_num(host(post[i]), nan=-1.0)
+        want.append(int(np.argmax(x)))
+    if cols == 1:
+        rows, want = rows[:3], want[:3]
+    correct = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for labels, hits in ((want, len(want)), ([w + 1 for w in want], 0)):
+        y = np.array(labels + [cols] * (4 - len(labels)), np.int32)
+        B.dnn_count_correct(shape, 1, acts, 0, dev(y), 0, 4, correct)
+        assert int(correct.item()) == hits
+
+
 def test_full_width_stack_of_six_rbms_and_initialisation():
     # Sec. 5.1 at size: 440 -> 2048 and five RBMs of 2048 -> 2048, minibatch 256, two CD-1 updates per RBM from the
     # same start on both sides (a longer run is a free-running comparison: see the 500-minibatch test of the single
