@@ -120,7 +120,7 @@ static GemmPlan gemm_plan_direct(int M, int N, int K, int batch, int force_cfg, 
     pl.bm = kCfgs[cfg].bm; pl.bn = kCfgs[cfg].bn;
     const int bk = kCfgs[cfg].bk;
     const int64_t tiles = (int64_t)((M + pl.bm - 1) / pl.bm) * ((N + pl.bn - 1) / pl.bn) * batch;
-    int splits = cfg_kg(cfg) ? 1 : force_splits;      // these split the contraction inside the workgroup only
+    int splits = cfg_kg(cfg) ? (cfg == CFG_KG_64x128 && force_splits > 1 ? force_splits : 1) : force_splits;      // the others split the contraction inside the workgroup only
     if (splits <= 0) {
         // A launch takes about as long as the workgroups of its fullest compute unit one after the other: in units of
         // contraction steps, ceil(tiles * splits / compute units) * K / splits; a compute unit with a single, short
@@ -352,12 +352,26 @@ static bool short_three(const GemmDesc& d, bool ragged) {
 //   (1024x2048x2048 41.8 / 48.1 us, n-contiguous B 38.6 / 48.1, from HBM 43.5 / 49.6, 39.2 / 49.5; 768x2048x2048 34.2 / 40.0); other
 //   rows, whose 64-byte pieces lie in two cache lines, up to 1.07; 130 - 188 tiles 0.80 - 1.28; 320 - 500 steps 0.9 - 1.14; 2400 and more
 //   0.9 - 1.17; 270 tiles and more 1.04 - 1.4
-static int kg64_plan(const GemmDesc& d) {
-    if (d.force_cfg >= 0 || d.force_splits > 1 || d.K < 512 || d.K > 2304) return CFG_AUTO;
+// 64x128 and n-contiguous B (a back-propagated error by its weights), contractions of more than 2304 steps, from HBM, over 60 shapes:
+//   unsplit 0.75 - 0.95 (1024x2048x8000 117 / 124 us); two splits across workgroups of 1240 - 2048 steps each 0.80 - 0.93 (192x4480x2880 38 / 45), longer ones
+//   0.75 - 1.04; four of 1200 steps and more 0.82 - 0.97 (256x2048x8000 47 / 51), shorter ones 0.88 - 1.28.  (k-contiguous B: 0.9 - 1.17)
+// Returns the configuration, CFG_AUTO for none, and the splits.
+static int kg64_plan(const GemmDesc& d, int64_t ws_floats, int& splits) {
+    splits = 1;
+    if (d.force_cfg >= 0 || d.force_splits > 1 || d.K < 512 || d.K > 9000) return CFG_AUTO;
     const int64_t t64 = tiles_of(CFG_KG_64x64, d.M, d.N, d.batch), t128 = tiles_of(CFG_KG_64x128, d.M, d.N, d.batch);
-    if (t64 <= kNumCU) return 2 * t64 > kNumCU && tiles_of(CFG_KG_32x64, d.M, d.N, d.batch) > kNumCU ? CFG_KG_64x64 : CFG_AUTO;
+    auto full_round = [&](int sp) { return 4 * t128 * sp >= 3 * kNumCU && t128 * sp <= kNumCU; };
     auto starts_at_64 = [](const float* q, int64_t ld, int64_t stride) { return ((reinterpret_cast<uintptr_t>(q) | (uintptr_t)ld * 4 | (uintptr_t)stride * 4) & 63) == 0; };
-    return 4 * t128 >= 3 * kNumCU && t128 <= kNumCU && starts_at_64(d.A, d.lda, d.a_bstride) && starts_at_64(d.B, d.ldb, d.b_bstride) ? CFG_KG_64x128 : CFG_AUTO;
+    const bool lines = starts_at_64(d.A, d.lda, d.a_bstride) && starts_at_64(d.B, d.ldb, d.b_bstride);
+    if (d.K > 2304) {
+        if (d.b_kc || !lines) return CFG_AUTO;
+        if (full_round(1)) return CFG_KG_64x128;
+        if (full_round(2) && d.K >= 2 * 1240 && d.K <= 2 * 2048) splits = 2;
+        else if (full_round(4) && d.K >= 4 * 1200) splits = 4;
+        return splits > 1 && d.force_splits == 0 && (int64_t)splits * d.batch * d.M * d.N <= ws_floats ? CFG_KG_64x128 : CFG_AUTO;
+    }
+    if (t64 <= kNumCU) return 2 * t64 > kNumCU && tiles_of(CFG_KG_32x64, d.M, d.N, d.batch) > kNumCU ? CFG_KG_64x64 : CFG_AUTO;
+    return full_round(1) && lines ? CFG_KG_64x128 : CFG_AUTO;
 }
 
 int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t stream) {
@@ -371,8 +385,9 @@ int gemm_launch(const GemmDesc& d, float* ws, int64_t ws_floats, hipStream_t str
     if (!rowsum && split_eligible(d)) {
         const bool ragged = !dma_eligible(d, p);
         three = three || (d.force_cfg < 0 && short_three(d, ragged));
-        const int kg64 = three || ragged ? CFG_AUTO : kg64_plan(d);
-        pl = kg64 != CFG_AUTO ? gemm_plan_direct(d.M, d.N, d.K, d.batch, kg64, 1)
+        int kg64_splits = 1;
+        const int kg64 = three || ragged ? CFG_AUTO : kg64_plan(d, ws ? ws_floats : 0, kg64_splits);
+        pl = kg64 != CFG_AUTO ? gemm_plan_direct(d.M, d.N, d.K, d.batch, kg64, kg64_splits)
                               : gemm_plan(d.M, d.N, d.K, d.batch, d.force_cfg, d.force_splits, ragged, ws ? ws_floats : 0, three);
         p = fill_params(d, pl, ws);
     }

@@ -17,12 +17,14 @@ __device__ __forceinline__ void wait_kg64() { asm volatile("s_waitcnt vmcnt(%0)"
 // from HBM, the former 25 / 26 otherwise.)
 // 64x128 tiles (768 bytes per step for twice the output; 256 accumulation registers, so one set of sums): 1024 x 2048 x 2048 42 / 39 us, from HBM
 // 43 / 39, where the split-operand kernel's 64x128 tiles take 48 / 48 and 50 / 50.
+// The contraction may be split across workgroups too (fewer tiles, long contractions): 256 x 2048 x 8000, four ways, 42 us and the reducer's 6.6, 128x128 tiles
+// in eight splits 48 and 7.6.
 // A wavefront's two 32-row blocks of A and two of B make
 // four products of every part, so that an element is split half as often per product as in 32x32 blocks side by side, and a compute unit
 // reads a third less for the same output than with 32x64 tiles.  A wavefront has its SIMD and 512 registers to itself: k-tile t's
 // twelve MFMAs run with the split of tile t + 1 between them, whose raw operands tile t + 2's replace as they are used up.
 template <bool AKC, bool BKC, int TN>
-__device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int tile, const int b) {
+__device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int tile, const int bz) {
     // 2 blocks of 32 rows of A, TN blocks of 32 columns of B; sums of even and odd k-tiles apart where there are registers for it (they round less)
     constexpr int KG = kKg64Groups, NST = TN == 2 ? 5 : 3, BK = kDmaBK, BM = 64, BN = 32 * TN, TILE_A = BM * BK, TILE_B = BN * BK;
     constexpr int A_LOADS = 4, B_LOADS = 2 * TN, LOADS = A_LOADS + B_LOADS, BLOCKS = 2 + TN, PRODUCTS = 2 * TN, SETS = TN == 2 ? 2 : 1;
@@ -31,13 +33,14 @@ __device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int t
     static_assert(NST * (TILE_A + TILE_B) >= PRODUCTS * 1024, "a k-group's rings must hold its accumulators for the final sum");
     const int tid = threadIdx.x, lane = tid & 63, kg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lrow = lane >> 5, lcol = lane & 31;
+    const int b = bz / p.splits, split = bz - b * p.splits;
     int tm_i, tn_i;
     tile_coords(p, tile, tm_i, tn_i);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
     // every KG-th k-tile: what the groups read at a time are neighbouring pieces of the same cache lines
-    const int nkt_all = p.K / BK;
+    const int kfirst = split * p.kper, kend = min(p.K, kfirst + p.kper), nkt_all = (kend - kfirst) / BK, ktail = kfirst + nkt_all * BK;
     const int nkt = __builtin_amdgcn_readfirstlane((nkt_all - kg + KG - 1) / KG);
-    const int kbeg = kg * BK;
+    const int kbeg = kfirst + kg * BK;
 
     auto lane_offset = [&](bool kc, int unit, int BR, int r0, int R, int64_t ld) -> uint32_t {      // (as in gemm_dma_kg_body)
         if (kc) {
@@ -120,7 +123,7 @@ __device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int t
 
     // Contraction steps past the last whole k-tile: the last k-group's, requested ahead of every direct load (see gemm_dma_kg_body), or behind
     // the loop where it leaves no registers for them.
-    const bool has_tail = kg == KG - 1 && nkt_all * BK < p.K;
+    const bool has_tail = kg == KG - 1 && ktail < kend;
     float tail[BLOCKS][8];
     auto request_tail = [&]() {
         if (!has_tail) return;
@@ -131,7 +134,7 @@ __device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int t
             const int m = min(m0 + 32 * blk + lcol, p.M - 1), n = min(n0 + 32 * (blk - 2) + lcol, p.N - 1);
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                const int k = nkt_all * BK + 8 * (c / 4) + 4 * lrow + c % 4;
+                const int k = ktail + 8 * (c / 4) + 4 * lrow + c % 4;
                 if constexpr (blk < 2) tail[blk][c] = k < p.K ? (AKC ? Ab[(int64_t)m * p.lda + k] : Ab[(int64_t)k * p.lda + m]) : 0.f;
                 else tail[blk][c] = k < p.K ? (BKC ? Bb[(int64_t)n * p.ldb + k] : Bb[(int64_t)k * p.ldb + n]) : 0.f;
             }
@@ -238,8 +241,16 @@ __device__ __forceinline__ void gemm_kg64_body(const GemmKParams& p, const int t
         for (int g = 1; g < KG; ++g) r += S[g][at];
         sum[0][e][v] = r;
     });
-    const EpiCtx c = epi_ctx(p.epi, p.C, p.c_bstride, b);
     const int mb = m0 + 32 * (kg * MINE / TN), nb = n0 + 32 * (kg * MINE % TN);
+    if (p.splits > 1) {
+        Epilogue raw{};
+        EpiCtx c{};
+        c.alpha = 1.f;
+        c.C = p.ws + ((int64_t)bz * p.M) * p.N;
+        write_tile<EPI_STORE, 1, MINE>(sum, raw, c, p.N, p.M, p.N, mb, nb, lrow, lcol);
+        return;
+    }
+    const EpiCtx c = epi_ctx(p.epi, p.C, p.c_bstride, b);
     MAVG_EPI_DISPATCH(p.epi.kind, (write_tile<KIND, 1, MINE>(sum, p.epi, c, p.ldc, p.M, p.N, mb, nb, lrow, lcol)))
 }
 

@@ -283,11 +283,13 @@ def test_short_ragged_products_take_no_longer_with_two_parts(m, n, k):
 
 @pytest.mark.parametrize("a_kc,b_kc", LAYOUTS)
 @pytest.mark.parametrize("m,n,k", [(513, 1020, 512), (65, 8132, 516), (1024, 1024, 2304), (100, 5188, 1000), (2052, 196, 1337), (832, 640, 576), (576, 1000, 2060),
-                                   (1024, 2048, 512), (4161, 260, 533), (769, 1928, 1100), (130, 8196, 1020), (33, 24576, 517), (770, 2048, 2304)])
+                                   (1024, 2048, 512), (4161, 260, 533), (769, 1928, 1100), (130, 8196, 1020), (33, 24576, 517), (770, 2048, 2304),
+                                   (594, 2768, 2389), (190, 4480, 2485), (130, 2512, 4816), (1, 6160, 4805)])
 def test_64x64_and_64x128_tiles_split_inside_the_workgroup(m, n, k, a_kc, b_kc):
     # 129 to 256 tiles of 64x64, and 192 to 256 of 64x128, the shortest and longest contractions that go there, remainders of k-tiles (4, 5, 8, 9, 12
     # steps), numbers of k-tiles that four wavefronts share unevenly, and partial tiles; an odd k by row strides.  Tolerance: 2304 additions
-    # rounding by 2^-24 each give 3e-6 if all round alike, 2e-7 if they round at random.
+    # rounding by 2^-24 each give 3e-6 if all round alike, 2e-7 if they round at random.  The last four, with n-contiguous B: longer ones, unsplit and split
+    # across workgroups in two and four.
     import torch
     from paper_1507_01239_amd import binding as B
     rng = np.random.default_rng(m + k)
